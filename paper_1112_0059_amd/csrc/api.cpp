@@ -313,22 +313,34 @@ static bool variant_serves(int v, int mode, int fmt, int kp)
     return !(variant(v).pl && mode == LNBNN_FP8_RERANK_2K);
 }
 
-static int default_variant(int mode, int fmt, int kp)
+static int default_variant(int mode, int fmt, int kp, bool over)
 {
-    // the shapes the tuner picked on the 15.36M-reference workloads: pair
-    // lists (one list per query) with 8 waves x 64 queries, 8-tile stages
-    // for the 4-5 KB tiles; the FP8 top-4k candidate lists without the
-    // next-tile prefetch; the union-of-halves FP8 rule on per-half lists
-    if (fmt == FMT_I8 || fmt == FMT_I8N) return 16;
+    // Shared lists of tiles wherever the rule allows them.  16x16 blocks (64
+    // queries per wave on four query tiles) beat 32x32 pair lists at every batch
+    // size measured: INT8, one image of 2,251 descriptors against 15.36M
+    // references 4.27 ms against 4.35, 32 images against 2.27M 10.96 against
+    // 11.3, the two-class sweep 2.83 against 3.01; FP16, k = 20, 20.3 against
+    // 22.0; original NBNN 11.6 against 12.4.  FP8 keeps the 32x32 form, whose keys
+    // the re-rank's candidates are defined by.
+    if (fmt == FMT_I8) return 25;
+    if (fmt == FMT_I8N) return 15;
     if (fmt == FMT_I8L) return 19;
-    if (fmt == FMT_F16 || fmt == FMT_BF16) return 17;
+    if (fmt == FMT_F16 || fmt == FMT_BF16) return 26;
     const int b = kp_bucket(kp, fmt);
-    if (mode == LNBNN_FP8_RERANK_2K) return b <= 20 ? 8 : b <= 40 ? 11 : 0;
-    return b <= 20 ? 16 : b <= 40 ? 21 : 0;
+    // the union-of-halves rule keeps per-half lists of rows, whose insertions are
+    // most of its time: one query tile per wave (no spills) beats two, 24.2 ms
+    // against 30.1 for 48,000 descriptors over 2.27M references, k = 10
+    if (mode == LNBNN_FP8_RERANK_2K) return b <= 40 ? 11 : 0;
+    // 44-64 entries (k = 11..16): one wave per SIMD, 77 ms against 253 on
+    // per-half lists for 18,000 descriptors over 15.36M references, k = 16;
+    // beyond k = 16 the rule itself is that of per-half lists
+    return b <= 40 ? 16 : !over ? 18 : 0;
 }
 
-int make_plan(lnbnn_index *ix, int mode, int kp, int64_t q_cap, int forced_variant, Plan *out)
+int make_plan(lnbnn_index *ix, int mode, int k, int64_t q_cap, int64_t n_q, int max_lists, Plan *out)
 {
+    const int kp = dist_list_len(mode, k);
+    const bool over = mode == LNBNN_FP8_RERANK && fp8_candidates(k) > kp;   // lists shorter than 4k
     const int fmt = index_fmt(ix, mode);
     const int kpb = kp_bucket(kp, fmt);
     if (kpb == 0) return set_err(LNBNN_EINVAL, "k + 1 = %d is not supported by mode %d", kp, mode);
@@ -338,29 +350,93 @@ int make_plan(lnbnn_index *ix, int mode, int kp, int64_t q_cap, int forced_varia
         auto it = ix->pinned.find({mode, kpb});
         if (it != ix->pinned.end() && q_cap >= it->second.min_q) tu = it->second.t;
     }
-    int v = forced_variant >= 0 ? forced_variant : tu.variant;
-    if (v < 0) v = default_variant(mode, fmt, kp);
+    const int v = tu.variant >= 0 ? tu.variant : default_variant(mode, fmt, kp, over);
     if (!variant_serves(v, mode, fmt, kp))
         return set_err(LNBNN_EINVAL, "variant %d cannot serve mode %d with k + 1 = %d", v, mode, kp);
     const Variant var = variant(v);
     const int64_t qb = (int64_t)var.waves * var.qt * var.nt;
-    const int groups = var.pl ? 1 : 64 / var.qt;  // lists per query and slice
-    const int64_t n_qb = std::max<int64_t>(1, (q_cap + qb - 1) / qb);
     const int64_t n_tiles = ix->rows[fmt] / kTileRows;
     const int bpc = blocks_per_cu(ix, v, fmt, kpb);
     int64_t resident = (int64_t)ix->cu_count * bpc;
     if (tu.max_workgroups > 0) resident = std::min<int64_t>(resident, tu.max_workgroups);
-    // Split the reference set only when the query blocks alone cannot keep
-    // every workgroup slot busy twice over; each split costs one more
-    // partial list per lane group (the merge takes at most kMaxLists lists
-    // per query).  The split is the one whose (query block, slice) items
-    // fill the resident workgroups most evenly: estimated time = rounds of
-    // items x (tiles per slice + a start-up cost per item), fewest slices on
-    // a tie.
-    auto slice_tiles = [&](int64_t s) {
-        const int64_t t = (n_tiles + s - 1) / s;
-        return std::max<int64_t>(8, (t + 7) / 8 * 8);
-    };
+    auto up8 = [](int64_t t) { return std::max<int64_t>(8, (t + 7) / 8 * 8); };
+    Plan p;
+    p.variant = v;
+    p.fmt = fmt;
+    p.kpb = kpb;
+    p.pl = var.pl;
+    p.block = (int)qb;
+    p.max_lists = max_lists;
+    p.q_cap = q_cap;
+    if (p.pl || fmt == FMT_I8N) {
+        // Shared lists (and the original NBNN, whose pieces combine by atomic
+        // minima): whole blocks in full rounds of the grid, then the R
+        // remaining blocks, cut into slices or equal runs (see k_dist_topk).
+        // Every piece costs its tiles and the start of a fresh list, about
+        // kStart tiles' time (nearly every tile inserts until 64 k tiles are
+        // seen).  K rounds of (block, slice) items: K x (tiles per slice +
+        // start).  Runs: one piece, or two where a block ends inside, per
+        // workgroup, whatever R is; but each workgroup then reads other tiles
+        // at any time, and the L2 and the infinity cache serve nobody twice
+        // (kRunCost).  Without a cut a batch just past a multiple of 256 blocks
+        // ran one more whole round: 563 blocks of 512 queries over 15.36M
+        // references took 526 ms instead of 431 ms.
+        constexpr double kStart = 128, kRunCost = 1.08;
+        const int64_t n_qb = std::max<int64_t>(1, (n_q + qb - 1) / qb);
+        const int64_t grid = resident, full = n_qb / grid, rem = n_qb % grid;
+        int64_t slices = rem > 0 ? 1 : 0, tiles = n_tiles, pieces = rem;
+        if (rem > 0 && max_lists > 1) {
+            double best = (double)n_tiles;
+            for (int64_t rounds = 1; rounds <= 8; ++rounds) {
+                const int64_t t = up8((n_tiles + rounds * grid / rem - 1) / (rounds * grid / rem));
+                const int64_t n = (n_tiles + t - 1) / t;
+                const double cost = (double)((rem * n + grid - 1) / grid) * ((double)t + kStart);
+                if (n > 1 && n <= max_lists && cost < best) {
+                    best = cost;
+                    slices = n;
+                    tiles = t;
+                    pieces = rem * n;
+                }
+            }
+            const int64_t run = up8((rem * n_tiles + grid - 1) / grid);
+            if (run < n_tiles && (n_tiles - 1) / run + 2 <= max_lists && ((double)run + 2 * kStart) * kRunCost < best) {
+                slices = 0;
+                tiles = run;
+                pieces = rem + (rem * n_tiles + run - 1) / run;
+            }
+        }
+        const bool cut = rem > 0 && tiles < n_tiles;
+        p.grid = (int)grid;
+        p.walk.full_rounds = (int)full;
+        p.walk.rem_slices = (int)slices;
+        p.walk.slice_tiles = (int)tiles;
+        p.lists = cut ? (full * grid + pieces) * qb : std::max<int64_t>(n_q, 1);
+        p.n_slices = (int)((n_tiles + tiles - 1) / tiles);
+        p.n_lists = 1;
+        p.chunk_tiles = (int)(tu.chunk_tiles > 0 ? std::min<int64_t>(tu.chunk_tiles, n_tiles) : n_tiles);
+        *out = p;
+        return LNBNN_OK;
+    }
+    // One list per lane group: the reference set is split into equal slices
+    // only when the query blocks alone cannot keep every workgroup slot busy
+    // twice over; each split costs one more partial list per lane group (the
+    // merge takes at most kMaxLists lists per query).  The split is the one
+    // whose (query block, slice) items fill the resident workgroups most
+    // evenly: estimated time = rounds of items x (tiles per slice + a start-up
+    // cost per item), fewest slices on a tie.  It depends on the capacity
+    // bucket alone, and for the default shape of the union-of-halves FP8 rule
+    // (whose candidates are those of the slices' lists) on blocks of 512
+    // queries, one workgroup per CU, whatever shape runs it.
+    const int groups = 64 / var.qt;                      // lists per query and slice
+    const bool by512 = mode == LNBNN_FP8_RERANK_2K && kpb <= 20 && tu.variant < 0;
+    const int64_t slice_qb = by512 ? 512 : qb;
+    const int64_t resident_wg = resident;
+    if (by512) {
+        resident = ix->cu_count;
+        if (tu.max_workgroups > 0) resident = std::min<int64_t>(resident, tu.max_workgroups);
+    }
+    const int64_t n_qb = std::max<int64_t>(1, (q_cap + slice_qb - 1) / slice_qb);
+    auto slice_tiles = [&](int64_t s) { return up8((n_tiles + s - 1) / s); };
     int64_t tps = slice_tiles(1);
     if (n_qb < 2 * resident) {
         constexpr int64_t kItemStartTiles = 32;
@@ -377,29 +453,37 @@ int make_plan(lnbnn_index *ix, int mode, int kp, int64_t q_cap, int forced_varia
         }
     }
     const int64_t S = (n_tiles + tps - 1) / tps;
-    out->variant = v;
-    out->fmt = fmt;
-    out->kpb = kpb;
-    out->n_slices = (int)S;
-    out->n_lists = (int)S * groups;
-    out->tiles_per_slice = (int)tps;
-    out->grid = (int)std::max<int64_t>(1, std::min<int64_t>(n_qb * S, resident));
+    p.n_slices = (int)S;
+    p.n_lists = (int)S * groups;
+    p.walk.n_slices = (int)S;
+    p.walk.tiles_per_slice = (int)tps;
+    p.grid = (int)std::max<int64_t>(1, std::min<int64_t>((q_cap + qb - 1) / qb * S, resident_wg));
     // By default an item sweeps its whole slice with its lists in registers;
     // a tuned chunk length makes workgroups that own several items walk the
     // slice chunk by chunk instead (lists saved between chunks), which keeps
     // the workgroups of an XCD on the same references at the same time.
-    out->chunk_tiles = tu.chunk_tiles > 0 ? (int)std::min<int64_t>(tu.chunk_tiles, tps) : (int)tps;
-    out->q_cap = q_cap;
+    p.chunk_tiles = tu.chunk_tiles > 0 ? (int)std::min<int64_t>(tu.chunk_tiles, tps) : (int)tps;
+    *out = p;
     return LNBNN_OK;
 }
 
-int64_t part_elems(const Plan &p, int64_t q_cap) { return (int64_t)p.n_lists * q_cap * p.kpb; }
+int64_t batch_elems(const lnbnn_index *ix, const Plan &p, int64_t q_cap)
+{
+    // the original NBNN mode keeps its per-class minima in part_i
+    if (p.fmt == FMT_I8N) return (int64_t)ix->n_classes * q_cap;
+    if (p.pl) return p.lists * p.kpb;
+    return (int64_t)p.n_lists * q_cap * p.kpb;
+}
 
 int64_t work_elems(const lnbnn_index *ix, const Plan &p, int64_t q_cap)
 {
-    // the original NBNN mode keeps its per-class minima in part_i
-    if (p.fmt == FMT_I8N) return std::max(part_elems(p, q_cap), (int64_t)ix->n_classes * q_cap);
-    return part_elems(p, q_cap);
+    if (!p.pl || p.fmt == FMT_I8N) return batch_elems(ix, p, q_cap);
+    // whole blocks have one list per query; the remaining ones, fewer than a
+    // grid, at most 8 rounds of (block, slice) items or one piece more than
+    // blocks and workgroups, and at most max_lists per block
+    const int64_t n_qb = std::max<int64_t>(1, (q_cap + p.block - 1) / p.block);
+    const int64_t rem = std::min<int64_t>(n_qb, p.grid);
+    return (n_qb + std::min<int64_t>(8 * (int64_t)p.grid, rem * p.max_lists)) * p.block * p.kpb;
 }
 
 int enqueue_batch(lnbnn_index *ix, const Plan &p, const BatchIO &io, hipStream_t s, hipEvent_t *kev)
@@ -409,7 +493,7 @@ int enqueue_batch(lnbnn_index *ix, const Plan &p, const BatchIO &io, hipStream_t
     // every buffer the launches write must hold what this plan writes
     const Workspace *w = io.ws;
     const bool nbnn = p.fmt == FMT_I8N;
-    if (!w || io.q_cap > w->q_cap || io.img_cap > w->img_cap || work_elems(ix, p, io.q_cap) > w->part_cap ||
+    if (!w || io.q_cap > w->q_cap || io.img_cap > w->img_cap || batch_elems(ix, p, io.q_cap) > w->part_cap ||
         !w->status)
         return set_err(LNBNN_EINVAL, "internal: workspace smaller than the plan");
     if (fp8 && (io.q_cap > w->q8_cap || io.q_cap * fp8_candidates(io.k) > w->cand_cap ||
@@ -430,11 +514,8 @@ int enqueue_batch(lnbnn_index *ix, const Plan &p, const BatchIO &io, hipStream_t
     // never read by the unscaled formats; any valid address keeps the
     // kernel's pointer arithmetic defined
     a.row_scale = ix->row_scale ? ix->row_scale : reinterpret_cast<const int32_t *>(a.seed);
-    a.parity = nbnn ? ix->parity_n : ix->parity;
-    if (!a.parity) a.parity = reinterpret_cast<const uint32_t *>(a.seed);
+    a.odd_tile0 = ix->odd_tile0;
     a.n_tiles = ix->rows[p.fmt] / kTileRows;
-    a.tiles_per_slice = p.tiles_per_slice;
-    a.n_slices = p.n_slices;
     a.chunk_tiles = p.chunk_tiles;
     a.q_cap = io.q_cap;
     a.part_d = io.part_d;
@@ -446,6 +527,15 @@ int enqueue_batch(lnbnn_index *ix, const Plan &p, const BatchIO &io, hipStream_t
     if (kev) LN_HIP(hipEventRecord(kev[0], s));
     LN_HIP(launch_dist_topk(p.variant, p.fmt, p.kpb, a, p.grid, s));
     if (kev) LN_HIP(hipEventRecord(kev[1], s));
+    RefineArgs t{};
+    t.q = a.q;
+    t.q_scale = a.q_scale;
+    t.frag = a.frag;
+    t.seed = a.seed;
+    t.row_scale = a.row_scale;
+    t.odd_tile0 = a.odd_tile0;
+    t.n_need = dist_list_len(io.mode, io.k);
+    t.map = SlotMap{a.n_tiles, p.block, p.grid};
     if (fp8) {
         RerankArgs r{};
         r.bd = io.bd;
@@ -466,6 +556,10 @@ int enqueue_batch(lnbnn_index *ix, const Plan &p, const BatchIO &io, hipStream_t
         r.upd_delta = io.upd_delta;
         r.totals_f64 = io.totals_f64;
         r.status = w->status;
+        if (p.pl)
+            LN_HIP(launch_refine_fp8(t, r, io.q_cap, s));
+        else
+            LN_HIP(launch_cand_merge(r, io.q_cap, s));
         LN_HIP(launch_rerank(r, io.q_cap, io.img_cap, s));
     } else if (nbnn) {
         NbnnArgs n{};
@@ -484,6 +578,8 @@ int enqueue_batch(lnbnn_index *ix, const Plan &p, const BatchIO &io, hipStream_t
         f.bd = io.bd;
         f.offsets = io.offsets;
         f.labels = ix->labels;
+        f.perm = p.fmt == FMT_I8 || p.fmt == FMT_I8L ? ix->perm : nullptr;
+        f.n_rows = ix->rows[p.fmt];
         f.n_refs = ix->n_refs;
         f.n_lists = p.n_lists;
         f.kp_stride = p.kpb;
@@ -494,7 +590,10 @@ int enqueue_batch(lnbnn_index *ix, const Plan &p, const BatchIO &io, hipStream_t
         f.part_i = io.part_i;
         f.totals = io.totals;
         f.status = w->status;
-        LN_HIP(launch_finish(f, io.q_cap, s));
+        if (p.pl)
+            LN_HIP(launch_refine(p.fmt, t, f, io.q_cap, s));
+        else
+            LN_HIP(launch_finish(f, io.q_cap, s));
         LN_HIP(launch_argmin(io.totals, io.bd, io.img_cap, ix->n_classes, s));
     }
     return LNBNN_OK;
@@ -519,10 +618,8 @@ static int free_index_buffers(lnbnn_index *ix)
     if (ix->seed[FMT_I8L]) (void)hipFree(ix->seed[FMT_I8L]);
     if (ix->seed[FMT_I8N]) (void)hipFree(ix->seed[FMT_I8N]);
     for (int f = 0; f < kNumFmt; ++f) ix->seed[f] = nullptr;
-    if (ix->parity) (void)hipFree(ix->parity);
-    ix->parity = nullptr;
-    if (ix->parity_n) (void)hipFree(ix->parity_n);
-    ix->parity_n = nullptr;
+    if (ix->perm) (void)hipFree(ix->perm);
+    ix->perm = nullptr;
     if (ix->tile_class) (void)hipFree(ix->tile_class);
     ix->tile_class = nullptr;
     if (ix->labels) (void)hipFree(ix->labels);
@@ -587,18 +684,52 @@ static int build_nbnn_layout(lnbnn_index *ix, const uint8_t *d_refs, const int32
     if ((rc = grow(ix, (void **)&ix->frag[FMT_I8N], n_nb * kDim, 1))) return rc;
     if ((rc = grow(ix, (void **)&iseed, n_nb, 4))) return rc;
     ix->seed[FMT_I8N] = reinterpret_cast<float *>(iseed);
-    if ((rc = grow(ix, (void **)&ix->parity_n, n_nb / kTileRows, 4))) return rc;
-    *bytes = n_nb * (kDim + 4) + n_nb / kTileRows * 8;
+    *bytes = n_nb * (kDim + 4) + n_nb / kTileRows * 4;
     LN_HIP(hipMallocAsync((void **)&d_perm, n_nb * 4, s));
     hipError_t e = hipMemcpyAsync(d_perm, h.perm.data(), n_nb * 4, hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
         e = hipMemcpyAsync(ix->tile_class, h.tile_class.data(), h.tile_class.size() * 4, hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
-        e = launch_pack_i8(d_refs, ix->n_refs, n_nb, kDim, ix->frag[FMT_I8N], iseed, ix->parity_n, s, d_perm);
+        e = launch_pack_i8(d_refs, n_nb, kDim, ix->frag[FMT_I8N], iseed, s, d_perm);
     (void)hipFreeAsync(d_perm, s);
     if (e != hipSuccess) return hip_err(e, "class-sorted pack");
     ix->rows[FMT_I8N] = n_nb;
     return LNBNN_OK;
+}
+
+// The INT8 copy of the index: rows by parity of ||r - 128||^2 (the even ones
+// first, each part in reference order and padded to 256 rows), their seeds and
+// the reference of every packed row.
+static int build_i8(lnbnn_index *ix, const uint8_t *d_refs, int fmt, hipStream_t s, int64_t *bytes)
+{
+    const int64_t n = ix->n_refs, n_blocks = (n + 255) / 256;
+    uint8_t *d_par = nullptr;            // parity of every reference, then the blocks' odd counts
+    const int64_t cnt_at = (n + 3) / 4 * 4;
+    LN_HIP(hipMallocAsync((void **)&d_par, cnt_at + (n_blocks + 1) * 4, s));
+    int32_t *block_odd = reinterpret_cast<int32_t *>(d_par + cnt_at);
+    int32_t n_odd = 0;
+    hipError_t e = launch_row_parity(d_refs, n, ix->dim, d_par, s);
+    if (e == hipSuccess) e = launch_parity_count(d_par, n, block_odd, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(&n_odd, block_odd + n_blocks, 4, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    auto up = [](int64_t r) { return (r + kPadRows - 1) / kPadRows * kPadRows; };
+    const int64_t even_pad = up(n - n_odd), n_pad = even_pad + up(n_odd);
+    int32_t *iseed = nullptr;
+    int rc = e == hipSuccess ? LNBNN_OK : hip_err(e, "row parity");
+    if (!rc) rc = grow(ix, (void **)&ix->frag[fmt], n_pad * ix->dim, 1);
+    if (!rc) rc = grow(ix, (void **)&iseed, n_pad, 4);
+    if (!rc) ix->seed[fmt] = reinterpret_cast<float *>(iseed);
+    if (!rc) rc = grow(ix, (void **)&ix->perm, n_pad, 4);
+    if (!rc) {
+        e = launch_parity_perm(d_par, n, block_odd, even_pad, n_pad, ix->perm, s);
+        if (e == hipSuccess) e = launch_pack_i8(d_refs, n_pad, ix->dim, ix->frag[fmt], iseed, s, ix->perm);
+        if (e != hipSuccess) rc = hip_err(e, "pack i8");
+    }
+    (void)hipFreeAsync(d_par, s);
+    ix->rows[fmt] = n_pad;
+    ix->odd_tile0 = (int32_t)(even_pad / kTileRows);
+    *bytes += n_pad * (ix->dim + 8);
+    return rc;
 }
 
 extern "C" int lnbnn_build_index(const void *refs, int dtype, int64_t n_refs, int32_t dim,
@@ -731,22 +862,9 @@ extern "C" int lnbnn_build_index(const void *refs, int dtype, int64_t n_refs, in
         seeded = true;
         ix->seed[fmt] = seed;
     }
-    if (!rc && dtype == LNBNN_U8 && (mode_mask & LNBNN_MODE_BIT(LNBNN_EXACT_I8))) {
-        // INT8 mode: its own fragments, seeds and parity masks
-        const int f8 = index_fmt(ix.get(), LNBNN_EXACT_I8);
-        int32_t *iseed = nullptr;
-        rc = grow(ixp, (void **)&ix->frag[f8], ix->n_pad * dim, 1);
-        if (!rc) rc = grow(ixp, (void **)&iseed, ix->n_pad, 4);
-        if (!rc) ix->seed[f8] = reinterpret_cast<float *>(iseed);
-        if (!rc) rc = grow(ixp, (void **)&ix->parity, ix->n_pad / kTileRows, 4);
-        if (!rc) {
-            bytes += ix->n_pad * (dim + 4) + ix->n_pad / kTileRows * 4;
-            hipError_t e = launch_pack_i8(static_cast<const uint8_t *>(d_refs), n_refs, ix->n_pad, dim, ix->frag[f8],
-                                          iseed, ix->parity, s);
-            if (e != hipSuccess) rc = hip_err(e, "pack i8");
-        }
-    }
     for (int f = 0; f < kNumFmt; ++f) ix->rows[f] = ix->n_pad;
+    if (!rc && dtype == LNBNN_U8 && (mode_mask & LNBNN_MODE_BIT(LNBNN_EXACT_I8)))
+        rc = build_i8(ixp, static_cast<const uint8_t *>(d_refs), index_fmt(ixp, LNBNN_EXACT_I8), s, &bytes);
     NbnnHost nbh;   // host arrays of the class-sorted copy: alive until the sync below
     if (!rc && (mode_mask & LNBNN_MODE_BIT(LNBNN_NBNN_I8))) {
         int64_t nb_bytes = 0;
@@ -847,7 +965,7 @@ std::string lnbnn::graph_key(const Plan &p, const BatchIO &io)
     // bound (all kernel arguments frozen into the graph); the caller's
     // queries and outputs travel in the batch descriptor
     std::ostringstream o;
-    o << wait_spin_limit() << '/' << p.variant << '/' << p.fmt << '/' << p.kpb << '/' << p.n_slices << '/' << p.tiles_per_slice << '/' << p.chunk_tiles << '/'
+    o << wait_spin_limit() << '/' << p.variant << '/' << p.fmt << '/' << p.kpb << '/' << p.n_lists << '/' << p.chunk_tiles << '/'
       << p.grid << '/' << io.q_cap << '/' << io.img_cap << '/' << io.k << '/' << io.mode << '/' << io.offsets << '/'
       << io.bd << '/' << io.totals << '/' << io.totals_f64 << '/' << io.part_d << '/' << io.part_i << '/' << io.q8
       << '/' << io.cand;
@@ -903,10 +1021,10 @@ static int classify_per_image(lnbnn_index *ix, const void *dq, const int64_t *of
 {
     Workspace &ws = ix->ws;
     const int kp = k + 1;
-    const int list_len = dist_list_len(mode, k);
     std::vector<Plan> plans(n_images);
     for (int32_t m = 0; m < n_images; ++m) {
-        int rc = make_plan(ix, mode, list_len, std::max<int64_t>(1, off[m + 1] - off[m]), -1, &plans[m]);
+        const int64_t nm = off[m + 1] - off[m];
+        int rc = make_plan(ix, mode, k, std::max<int64_t>(1, nm), nm, kSplitLists, &plans[m]);
         if (rc) return rc;
     }
     const int64_t rb = row_bytes(ix->dtype, ix->dim);
@@ -919,6 +1037,7 @@ static int classify_per_image(lnbnn_index *ix, const void *dq, const int64_t *of
         bds[m].cls = cls + m;
         bds[m].nbr_idx = nbr_idx ? nbr_idx + off[m] * kp : nullptr;
         bds[m].nbr_dist = nbr_dist ? nbr_dist + off[m] * kp : nullptr;
+        bds[m].walk = plans[m].walk;
         offs[2 * m] = 0;
         offs[2 * m + 1] = bds[m].n_q;
     }
@@ -976,7 +1095,6 @@ extern "C" int lnbnn_classify(lnbnn_index *ix, const void *queries, int dtype, c
     const bool direct = (flags & LNBNN_NO_GRAPH) || timed;   // events inside a graph cannot be read back
     const int kp = k + 1;
     const bool fp8 = is_fp8_mode(mode);
-    const int list_len = dist_list_len(mode, k);   // what the distance kernel keeps
     const int64_t n_q = img_offsets[n_images];
     const int64_t rb = row_bytes(dtype, ix->dim);
     const int64_t nc = ix->n_classes;
@@ -990,15 +1108,15 @@ extern "C" int lnbnn_classify(lnbnn_index *ix, const void *queries, int dtype, c
         for (int32_t m = 0; m < n_images; ++m) {
             Plan pm;
             const int64_t nm = std::max<int64_t>(1, img_offsets[m + 1] - img_offsets[m]);
-            if ((rc = make_plan(ix, mode, list_len, nm, -1, &pm))) return rc;
-            part = std::max(part, work_elems(ix, pm, pm.q_cap));
+            if ((rc = make_plan(ix, mode, k, nm, img_offsets[m + 1] - img_offsets[m], kSplitLists, &pm))) return rc;
+            part = std::max(part, batch_elems(ix, pm, pm.q_cap));
             q_max = std::max(q_max, nm);
         }
         q_cap = std::max<int64_t>(1, n_q);
     } else {
         q_cap = cap_bucket(n_q, 1024);
         img_cap = cap_bucket(n_images, 8);
-        if ((rc = make_plan(ix, mode, list_len, q_cap, -1, &plan))) return rc;
+        if ((rc = make_plan(ix, mode, k, q_cap, n_q, kSplitLists, &plan))) return rc;
         part = work_elems(ix, plan, plan.q_cap);
         q_max = plan.q_cap;
     }
@@ -1040,7 +1158,7 @@ extern "C" int lnbnn_classify(lnbnn_index *ix, const void *queries, int dtype, c
         rc = classify_per_image(ix, dq, img_offsets, n_images, k, mode, d_cls, d_nbr_i, d_nbr_d, s, kev);
         if (rc) return rc;
     } else {
-        BatchDesc hb{n_q, n_images, dq, d_cls, d_nbr_i, d_nbr_d};
+        BatchDesc hb{n_q, n_images, dq, d_cls, d_nbr_i, d_nbr_d, plan.walk};
         LN_HIP(hipMemcpyAsync(ws.bd, &hb, sizeof hb, hipMemcpyHostToDevice, s));
         LN_HIP(hipMemcpyAsync(ws.offsets, img_offsets, (size_t)(n_images + 1) * 8, hipMemcpyHostToDevice, s));
         BatchIO io;

@@ -121,9 +121,9 @@ struct FloatKeys {
         return fmin_acc(fmin_acc(fmin_acc(a[4 * g], a[4 * g + 1]), a[4 * g + 2]), a[4 * g + 3]);
     }
     static __device__ __forceinline__ float gate_thr(float thr) { return thr; }
-    static __device__ __forceinline__ float key(const f32x16 &acc, int r, uint32_t, int) { return acc[r]; }
-    // key of one accumulator value of tile row `row` (one list per query)
-    static __device__ __forceinline__ float key_at(float v, int, uint32_t) { return v; }
+    static __device__ __forceinline__ float key(const f32x16 &acc, int r, int) { return acc[r]; }
+    // key of a value that passed the gate, in a tile of parity `par`
+    static __device__ __forceinline__ float tile_key(float v, int) { return v; }
 };
 
 struct OpF16 : FloatKeys {
@@ -241,11 +241,13 @@ struct OpFP8 : FloatKeys {
 //     D = floor(||s||^2 / 2) - t.s,   key = 2 D + b,   b = ||s||^2 mod 2,
 // from the seed floor(||s||^2 / 2) + sum(s) and the query operand
 // u = 127 - q = -t - 1 (so u.s = -t.s - sum(s)).  |D| < 2^22, so every
-// key is an exact FP32 integer.  The per-row bit b lives in a per-tile
-// mask that only the (rare) insertion path reads.  A K step covers 32
+// key is an exact FP32 integer.  The packed index holds the rows of even
+// ||s||^2 first and those of odd ||s||^2 from tile odd_tile0 on, each part in
+// reference order, so b is a property of the tile, and rows of equal keys
+// (which share b) still stand in reference order.  A K step covers 32
 // elements: lane l supplies 16 bytes of row (l & 31), K elements
 // 32*s + 16*(l >> 5) + e.  Padding rows carry the seed 2^30, whose D never
-// makes a key (see key()).  S K steps: S = 4 for 128-element rows, S = 5
+// passes a gate (see gate_thr()).  S K steps: S = 4 for 128-element rows, S = 5
 // for the 160-element location-augmented rows (|D| < 2^23 there, and every
 // key and distance stays below 2^24, still exact in FP32).
 // NBN: the class-sorted index of the original NBNN rule (Algorithm 1): the
@@ -276,21 +278,17 @@ struct OpI8T {
     {
         return min(min(min(a[4 * g], a[4 * g + 1]), a[4 * g + 2]), a[4 * g + 3]);
     }
-    // key = 2D + b < thr implies D < ceil(thr / 2); no bound while the list
-    // is not full (thr = +inf)
+    // key = 2D + b < thr implies D < ceil(thr / 2); every real row passes
+    // while the list is not full (thr = +inf), and no padding row ever does
     static __device__ __forceinline__ int gate_thr(float thr)
     {
-        return thr < 1e30f ? (int)__builtin_ceilf(0.5f * thr) : 0x7fffffff;
+        return thr < 1e30f ? (int)__builtin_ceilf(0.5f * thr) : (1 << 29);
     }
-    static __device__ __forceinline__ float key(const i32x16 &acc, int r, uint32_t parity, int h)
+    static __device__ __forceinline__ float tile_key(int d, int par) { return (float)(2 * d + par); }
+    static __device__ __forceinline__ float key(const i32x16 &acc, int r, int par)
     {
         const int d = acc[r];
-        const int row = 8 * (r >> 2) + 4 * h + (r & 3);
-        return d >= (1 << 29) ? __builtin_inff() : (float)(2 * d + (int)((parity >> row) & 1u));
-    }
-    static __device__ __forceinline__ float key_at(int d, int row, uint32_t parity)
-    {
-        return d >= (1 << 29) ? __builtin_inff() : (float)(2 * d + (int)((parity >> row) & 1u));
+        return d >= (1 << 29) ? __builtin_inff() : tile_key(d, par);
     }
     static __device__ __forceinline__ void load_b(const void *q, const int32_t *, int64_t qi, bool ok, int h,
                                                   uint4 (&b)[kSteps][kBU], int &sb)
@@ -365,11 +363,10 @@ struct OpI8Q : OpI8T<4, FMT, NBN> {
     {
         return min(min(min(a[4 * g], a[4 * g + 1]), a[4 * g + 2]), a[4 * g + 3]);
     }
-    static __device__ __forceinline__ float key(const i32x8 &acc, int r, uint32_t parity, int h)
+    static __device__ __forceinline__ float key(const i32x8 &acc, int r, int par)
     {
         const int d = acc[r];
-        const int row = 16 * (r >> 2) + 4 * h + (r & 3);
-        return d >= (1 << 29) ? __builtin_inff() : (float)(2 * d + (int)((parity >> row) & 1u));
+        return d >= (1 << 29) ? __builtin_inff() : Base::tile_key(d, par);
     }
     static __device__ __forceinline__ void load_b(const void *q, const int32_t *, int64_t qi, bool ok, int h,
                                                   uint4 (&b)[kSteps][kBU], int &sb)
@@ -410,7 +407,7 @@ struct FloatQ : Base {
     {
         return fmin_acc(fmin_acc(fmin_acc(a[4 * g], a[4 * g + 1]), a[4 * g + 2]), a[4 * g + 3]);
     }
-    static __device__ __forceinline__ float key(const f32x8 &acc, int r, uint32_t, int) { return acc[r]; }
+    static __device__ __forceinline__ float key(const f32x8 &acc, int r, int) { return acc[r]; }
 };
 
 template <class Base16, bool BF>
@@ -507,13 +504,34 @@ template <> struct Square16<OpFP8> { using type = OpFP8Q; };
 // registers, column l & 31, register r being row 8*(r/4) + 4*(l/32) + r%4;
 // in the 16x16 shape 8 registers, column l & 15, row 16*(r/4) + 4*(l/16) + r%4.
 //
-// Selection.  Each lane keeps a sorted register list of the KP best
-// (d', index) pairs of its query among the rows it has seen (the kGroups
-// lanes of a query each see their share of every tile and keep separate
-// lists).  A tile is gated by the minimum of the lane's values: only when
-// some lane of the wave beats its current KP-th value does the wave walk the
-// registers and insert.  Rows reach a lane in increasing index order, so "strictly less
-// than" on d' alone realises the (distance, index) order.
+// Selection, shared lists (PL).  The kGroups lanes of a query keep one list,
+// held by one of them, over NT = kGroups query tiles: lane l owns query (tile
+// l / kQT, column l % kQT).  The list holds the KP best *tiles* by (smallest
+// key of the tile's 32 rows for this query, tile), and k_refine (refine.hip)
+// recomputes the rows of the best k + 1 of them.  That is enough: take a row
+// of the true top k + 1 by (key, row).  If its tile were not among the k + 1
+// best tiles, each of those would hold a row of a smaller key, or of the same
+// key in an earlier tile; these k + 1 rows would all come before it.
+// The gate is the smallest accumulator value of a tile, which the lane needs
+// anyway; the lanes of a query exchange it (v_permlane32_swap, and
+// v_permlane16_swap with 16x16 blocks), so each lane compares one value with
+// its own threshold.  What passes is appended to a small LDS buffer of the lane;
+// when some lane's buffer is full the wave merges all of them into the register
+// lists at once, so the KP-step insertion runs with most lanes active
+// instead of one.
+//   What it replaced: the gate's passing tiles were transposed across the lane
+// groups (16-32 permlane swaps) and walked row by row with one KP-step insertion
+// per passing row.  While a sweep is short (the first 64 KP tiles of a wave's
+// 64 queries pass almost always) that was most of the time.
+//   Tiles reach a lane in increasing order, so "strictly less than" on the key
+// alone realises the (key, tile) order.
+//
+// Selection, one list per lane group (not PL).  Each lane keeps a sorted
+// register list of the KP best (d', row) pairs of its query among the rows it
+// has seen (its share of every tile).  A tile is gated by the minimum of the
+// lane's values: only when some lane of the wave beats its current KP-th value
+// does the wave walk the registers and insert.  The union-of-halves FP8 rule is
+// defined on these lists.
 //
 // Original NBNN (Op::kNbnn, Algorithm 1).  The index holds the references
 // sorted by class, every class padded to a multiple of 8 tiles, so a class
@@ -542,10 +560,25 @@ static __device__ __forceinline__ void list_insert(float v, int idx, float (&ld)
     thr = ld[KP - 1];
 }
 
-// Load through the scalar cache (uniform index).
-static __device__ __forceinline__ uint32_t load_uniform(const uint32_t *p, int i)
+// The same with one v_med3 per key (a position takes the median of its
+// neighbour, itself and the new key).  Only the buffered lists take it: on the
+// row walk below, the 20-entry FP8 lists spilled 2,090 registers with it and 7
+// with the form above.
+template <int KP>
+static __device__ __forceinline__ void list_insert_med(float v, int idx, float (&ld)[KP], int (&li)[KP],
+                                                       float &thr)
 {
-    return ((const __attribute__((address_space(4))) uint32_t *)p)[i];
+#pragma unroll
+    for (int p = KP - 1; p > 0; --p) {
+        const bool shift = v < ld[p - 1];
+        const bool here = v < ld[p];
+        ld[p] = __builtin_amdgcn_fmed3f(ld[p - 1], v, ld[p]);
+        li[p] = shift ? li[p - 1] : (here ? idx : li[p]);
+    }
+    const bool first = v < ld[0];
+    ld[0] = first ? v : ld[0];
+    li[0] = first ? idx : li[0];
+    thr = ld[KP - 1];
 }
 
 // Insert every key of one tile that beats the list's current KP-th key;
@@ -553,11 +586,9 @@ static __device__ __forceinline__ uint32_t load_uniform(const uint32_t *p, int i
 template <class Op, int KP>
 static __device__ __forceinline__ void tile_insert(const typename Op::acc_t &acc, float &thr,
                                                    typename Op::gate_t &gt,
-                                                   float (&ld)[KP], int (&li)[KP], int row0, int h,
-                                                   const uint32_t *parity)
+                                                   float (&ld)[KP], int (&li)[KP], int row0, int odd_tile0)
 {
-    uint32_t pm = 0;
-    if constexpr (Op::kParity) pm = load_uniform(parity, __builtin_amdgcn_readfirstlane(row0 >> 5));
+    const int par = Op::kParity && __builtin_amdgcn_readfirstlane(row0 >> 5) >= odd_tile0;
     // the row base is made opaque here so the 16 index computations stay on
     // this (rarely taken) path instead of being hoisted into the gate
     int base = row0;
@@ -570,7 +601,7 @@ static __device__ __forceinline__ void tile_insert(const typename Op::acc_t &acc
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int r = 4 * g + i;
-            const float v = Op::key(acc, r, pm, h);
+            const float v = Op::key(acc, r, par);
             const bool take = v < thr;
             if (__builtin_amdgcn_ballot_w64(take) != 0) {
                 if (take) list_insert<KP>(v, base + Op::kRowStride * g + i, ld, li, thr);
@@ -580,7 +611,7 @@ static __device__ __forceinline__ void tile_insert(const typename Op::acc_t &acc
     gt = Op::gate_thr(thr);
 }
 
-static __device__ __forceinline__ float lmin(float a, float b) { return __builtin_fminf(a, b); }
+static __device__ __forceinline__ float lmin(float a, float b) { return fmin_acc(a, b); }
 static __device__ __forceinline__ int lmin(int a, int b) { return min(a, b); }
 
 template <class Op> using AccT = typename Op::acc_t;
@@ -591,106 +622,78 @@ template <class Op, int NT> using AccArr = typename Op::acc_t[NT];
 template <bool PL, int NT>
 constexpr int lists_per_lane() { return PL ? 1 : NT; }
 
-// Shared lists: the kGroups lanes of a query (2 with 32x32 blocks, 4 with
-// 16x16) keep one list, held by one of them, over NT = kGroups query tiles:
-// lane l owns the list of query (tile l / kQT, column l % kQT), which sees
-// every row of every tile.  Its values of a tile sit in the kGroups lanes of
-// its column, each in the accumulator of its query tile, so the insertion
-// path first transposes the accumulators across the lane groups in place
-// (the accumulators are dead after their gate): one v_permlane32_swap round
-// for two groups; for four, a v_permlane32_swap round (tiles j, j+2) and a
-// v_permlane16_swap round (tiles 2k, 2k+1).  Then every lane holds its own
-// query's values, acc[j] register r being row kRowStride*(r/4) + 4j + r%4.
-// The gate needs no exchange: each lane compares its values of tile nt with
-// the gate threshold of that tile's query (gq[nt], exchanged after every
-// insertion).
-template <class Op>
-static __device__ __forceinline__ void swap_lanes32(AccT<Op> &x, AccT<Op> &y)
+// Entries of a lane's append buffer.  Four: with 64 lanes the first buffer
+// fills after about 50 appends, so a merge (4 KP-step insertions) costs each
+// append a fraction of an insertion, and 8 waves' buffers are 16 KB, which the
+// deepest stage shapes leave free.
+constexpr int kBufEntries = 4;
+
+// min of x across lanes l, l + 32 for y's tile and x's: after the swap lanes
+// 0-31 hold both halves of x, lanes 32-63 both halves of y.
+template <class E>
+static __device__ __forceinline__ E half_min(E x, E y)
 {
-    using E = typename Op::gate_t;                 // accumulator element type
-#pragma unroll
-    for (int r = 0; r < Op::kAccN; ++r) {
-        const auto p = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, (E)x[r]),
-                                                        __builtin_bit_cast(uint32_t, (E)y[r]), false, false);
-        x[r] = __builtin_bit_cast(E, (uint32_t)p[0]);
-        y[r] = __builtin_bit_cast(E, (uint32_t)p[1]);
-    }
+    const auto p = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, y),
+                                                    false, false);
+    return lmin(__builtin_bit_cast(E, (uint32_t)p[0]), __builtin_bit_cast(E, (uint32_t)p[1]));
 }
 
-template <class Op>
-static __device__ __forceinline__ void swap_lanes16(AccT<Op> &x, AccT<Op> &y)
+template <class E>
+static __device__ __forceinline__ E quarter_min(E x, E y)
 {
-    using E = typename Op::gate_t;
-#pragma unroll
-    for (int r = 0; r < Op::kAccN; ++r) {
-        const auto p = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, (E)x[r]),
-                                                        __builtin_bit_cast(uint32_t, (E)y[r]), false, false);
-        x[r] = __builtin_bit_cast(E, (uint32_t)p[0]);
-        y[r] = __builtin_bit_cast(E, (uint32_t)p[1]);
-    }
+    const auto p = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, y),
+                                                    false, false);
+    return lmin(__builtin_bit_cast(E, (uint32_t)p[0]), __builtin_bit_cast(E, (uint32_t)p[1]));
 }
 
-// the gate thresholds of the query tiles' queries, from their owner lanes
+// The smallest value of the tile's 32 rows for the query this lane owns.
 template <class Op, int NT>
-static __device__ __forceinline__ void share_gate_thr(typename Op::gate_t gt, typename Op::gate_t (&gq)[NT], int col)
-{
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) gq[nt] = __shfl(gt, Op::kQT * nt + col);
-}
-
-template <class Op, int KP, int NT>
-static __device__ __forceinline__ void tile_insert_pl(AccArr<Op, NT> &acc, float &thr, typename Op::gate_t &gt,
-                                                      typename Op::gate_t (&gq)[NT], float (&ld)[KP], int (&li)[KP],
-                                                      int row0, int col, const uint32_t *parity)
+static __device__ __forceinline__ typename Op::gate_t owned_min(const AccArr<Op, NT> &acc)
 {
     static_assert(NT == Op::kGroups && (NT == 2 || NT == 4), "one query tile per lane group");
     if constexpr (NT == 2) {
-        swap_lanes32<Op>(acc[0], acc[1]);
+        return half_min(Op::gate_min(acc[0]), Op::gate_min(acc[1]));
     } else {
-        swap_lanes32<Op>(acc[0], acc[2]);
-        swap_lanes32<Op>(acc[1], acc[3]);
-        swap_lanes16<Op>(acc[0], acc[1]);
-        swap_lanes16<Op>(acc[2], acc[3]);
+        return quarter_min(half_min(Op::gate_min(acc[0]), Op::gate_min(acc[2])),
+                           half_min(Op::gate_min(acc[1]), Op::gate_min(acc[3])));
     }
-    uint32_t pm = 0;
-    if constexpr (Op::kParity) pm = load_uniform(parity, __builtin_amdgcn_readfirstlane(row0 >> 5));
-    int base = row0;                               // opaque, as in tile_insert
-    asm volatile("" : "+v"(base));
-#pragma unroll
-    for (int g = 0; g < Op::kAccN / 4; ++g) {
-        typename Op::gate_t m = Op::group_min(acc[0], g);
-#pragma unroll
-        for (int j = 1; j < NT; ++j) m = lmin(m, Op::group_min(acc[j], g));
-        if (__builtin_amdgcn_ballot_w64(m < gt) == 0) continue;
-#pragma unroll
-        for (int j = 0; j < NT; ++j)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int row = Op::kRowStride * g + 4 * j + i;
-                const float v = Op::key_at(acc[j][4 * g + i], row, pm);
-                const bool take = v < thr;
-                if (__builtin_amdgcn_ballot_w64(take) != 0) {
-                    if (take) list_insert<KP>(v, base + row, ld, li, thr);
-                }
-            }
+}
+
+// A lane's append buffer in LDS: entry j at byte 512 j from its base, so a
+// wave's appends of equal fill are consecutive.
+struct TileBuf {
+    uint2 *base;
+    int cnt;
+};
+
+// Merge the wave's append buffers into its register lists.
+template <class Op, int KP>
+static __device__ __forceinline__ void buf_merge(TileBuf &buf, float &thr, typename Op::gate_t &gt, float (&ld)[KP],
+                                                 int (&li)[KP])
+{
+#pragma unroll 1
+    for (int j = 0; j < kBufEntries; ++j) {
+        const uint2 e = buf.base[j * 64];
+        const float v = __builtin_bit_cast(float, e.x);
+        const bool take = j < buf.cnt && v < thr;
+        if (__builtin_amdgcn_ballot_w64(take) == 0) continue;
+        if (take) list_insert_med<KP>(v, (int)e.y, ld, li, thr);
     }
+    buf.cnt = 0;
     gt = Op::gate_thr(thr);
-    share_gate_thr<Op, NT>(gt, gq, col);
 }
 
 // Gate of the NT query tiles of one reference tile: does some lane hold a
 // value below its list's gate threshold?  (Shared lists: one answer for all
-// tiles, in any[0].)
+// tiles, in any[0], and the lane's value in m.)
 template <class Op, int NT, bool PL>
 static __device__ __forceinline__ void gate_any(const typename Op::acc_t (&acc)[NT],
                                                 const typename Op::gate_t (&gt)[lists_per_lane<PL, NT>()],
-                                                const typename Op::gate_t (&gq)[NT], bool (&any)[NT])
+                                                bool (&any)[NT], typename Op::gate_t &m)
 {
     if constexpr (PL) {
-        bool below = Op::gate_min(acc[0]) < gq[0];
-#pragma unroll
-        for (int nt = 1; nt < NT; ++nt) below = below | (Op::gate_min(acc[nt]) < gq[nt]);
-        any[0] = __builtin_amdgcn_ballot_w64(below) != 0;
+        m = owned_min<Op, NT>(acc);
+        any[0] = __builtin_amdgcn_ballot_w64(m < gt[0]) != 0;
 #pragma unroll
         for (int nt = 1; nt < NT; ++nt) any[nt] = false;
     } else {
@@ -699,25 +702,31 @@ static __device__ __forceinline__ void gate_any(const typename Op::acc_t (&acc)[
     }
 }
 
-// Insertions for the tiles whose gate passed (rare).
+// Insertions for the tiles whose gate passed (rare).  pos: the tile (shared
+// lists) or the lane's first row.
 template <class Op, int KP, int NT, bool PL>
-static __device__ __forceinline__ void gate_insert(AccArr<Op, NT> &acc, const bool (&any)[NT],
+static __device__ __forceinline__ void gate_insert(AccArr<Op, NT> &acc, const bool (&any)[NT], typename Op::gate_t m,
                                                    float (&thr)[lists_per_lane<PL, NT>()],
-                                                   typename Op::gate_t (&gt)[lists_per_lane<PL, NT>()],
-                                                   typename Op::gate_t (&gq)[NT],
+                                                   typename Op::gate_t (&gt)[lists_per_lane<PL, NT>()], TileBuf &buf,
                                                    float (&ld)[lists_per_lane<PL, NT>()][KP],
-                                                   int (&li)[lists_per_lane<PL, NT>()][KP], int row0, int h,
-                                                   const uint32_t *parity)
+                                                   int (&li)[lists_per_lane<PL, NT>()][KP], int pos, int odd_tile0)
 {
     if constexpr (PL) {
-        if (__builtin_expect(any[0], 0))
-            tile_insert_pl<Op, KP, NT>(acc, thr[0], gt[0], gq, ld[0], li[0], row0,
-                                       (int)(threadIdx.x & (Op::kQT - 1)), parity);
+        if (__builtin_expect(any[0], 0)) {
+            const int par = Op::kParity && pos >= odd_tile0;
+            if (m < gt[0]) {
+                const float key = Op::tile_key(m, par);
+                buf.base[buf.cnt * 64] = make_uint2(__builtin_bit_cast(uint32_t, key), (uint32_t)pos);
+                buf.cnt += 1;
+            }
+            if (__builtin_amdgcn_ballot_w64(buf.cnt == kBufEntries) != 0)
+                buf_merge<Op, KP>(buf, thr[0], gt[0], ld[0], li[0]);
+        }
     } else {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
             if (__builtin_expect(any[nt], 0))
-                tile_insert<Op, KP>(acc[nt], thr[nt], gt[nt], ld[nt], li[nt], row0, h, parity);
+                tile_insert<Op, KP>(acc[nt], thr[nt], gt[nt], ld[nt], li[nt], pos, odd_tile0);
     }
 }
 
@@ -747,17 +756,18 @@ template <class Op, int KP, int NT, bool PL>
 static __device__ __forceinline__ void tiles_select(AccArr<Op, NT> &acc,
                                                     float (&thr)[lists_per_lane<PL, NT>()],
                                                     typename Op::gate_t (&gt)[lists_per_lane<PL, NT>()],
-                                                    typename Op::gate_t (&gq)[NT],
+                                                    typename Op::gate_t (&mk)[NT], TileBuf &buf,
                                                     float (&ld)[lists_per_lane<PL, NT>()][KP],
-                                                    int (&li)[lists_per_lane<PL, NT>()][KP], int row0, int h,
-                                                    const uint32_t *parity, int nb_par = 0)
+                                                    int (&li)[lists_per_lane<PL, NT>()][KP], int pos, int odd_tile0,
+                                                    int nb_par = 0)
 {
     if constexpr (Op::kNbnn) {
-        nbnn_tile_min<Op, NT>(acc, gq, nb_par);
+        nbnn_tile_min<Op, NT>(acc, mk, nb_par);
     } else {
         bool any[NT];
-        gate_any<Op, NT, PL>(acc, gt, gq, any);
-        gate_insert<Op, KP, NT, PL>(acc, any, thr, gt, gq, ld, li, row0, h, parity);
+        typename Op::gate_t m{};
+        gate_any<Op, NT, PL>(acc, gt, any, m);
+        gate_insert<Op, KP, NT, PL>(acc, any, m, thr, gt, buf, ld, li, pos, odd_tile0);
     }
 }
 
@@ -1011,9 +1021,8 @@ static __device__ __forceinline__ void pipe_step(AccArr<Op, NT> &acc_new, AccArr
                                                  const uint4 (&bq)[NT][Op::kSteps][Op::kBU], const int (&sb)[NT],
                                                  const uint4 *frag, const float4 *seed, const int32_t *rsc, int lane,
                                                  int h, float (&thr)[NL], typename Op::gate_t (&gt)[NL],
-                                                 typename Op::gate_t (&gq)[NT], float (&ld)[NL][KP],
-                                                 int (&li)[NL][KP], int row_old, const uint32_t *parity,
-                                                 int nb_par = 0)
+                                                 typename Op::gate_t (&mk)[NT], TileBuf &buf, float (&ld)[NL][KP],
+                                                 int (&li)[NL][KP], int pos_old, int odd_tile0, int nb_par = 0)
 {
     using acc_t = typename Op::acc_t;
     constexpr int S = Op::kSteps;
@@ -1024,10 +1033,11 @@ static __device__ __forceinline__ void pipe_step(AccArr<Op, NT> &acc_new, AccArr
     tile_reads<Op>(frag, seed, rsc, lane, h, av, sd, sa);
     const acc_t seed_acc = __builtin_bit_cast(acc_t, sd);
     bool any[NT];
+    typename Op::gate_t m{};
     if constexpr (Op::kNbnn)
-        nbnn_tile_min<Op, NT>(acc_old, gq, nb_par);
+        nbnn_tile_min<Op, NT>(acc_old, mk, nb_par);
     else
-        gate_any<Op, NT, PL>(acc_old, gt, gq, any);
+        gate_any<Op, NT, PL>(acc_old, gt, any, m);
 #pragma unroll
     for (int s = 0; s < S; ++s) {
 #pragma unroll
@@ -1047,7 +1057,7 @@ static __device__ __forceinline__ void pipe_step(AccArr<Op, NT> &acc_new, AccArr
     // lists -1.9 %; the 16-bit and 16x16 FP8 kernels are no faster with it.
     if constexpr (!Op::kNbnn && Op::kScaled && Op::kQT == 32) pin_acc<Op, NT>(acc_new);
 #endif
-    if constexpr (!Op::kNbnn) gate_insert<Op, KP, NT, PL>(acc_old, any, thr, gt, gq, ld, li, row_old, h, parity);
+    if constexpr (!Op::kNbnn) gate_insert<Op, KP, NT, PL>(acc_old, any, m, thr, gt, buf, ld, li, pos_old, odd_tile0);
 }
 
 // Calls f(std::integral_constant<int, I>) for I = B .. E-1 (a loop whose
@@ -1113,20 +1123,20 @@ static __device__ __forceinline__ void tile_load(const uint4 *frag, const float4
 template <class Op, int KP, int NT, bool PL, int NL = lists_per_lane<PL, NT>()>
 static __device__ __forceinline__ void pipe_step_regs(AccArr<Op, NT> &acc_new, AccArr<Op, NT> &acc_old,
                                                       const uint4 (&bq)[NT][Op::kSteps][Op::kBU],
-                                                      const int (&sb)[NT], const TileRegs<Op> &cur, int h,
+                                                      const int (&sb)[NT], const TileRegs<Op> &cur,
                                                       float (&thr)[NL], typename Op::gate_t (&gt)[NL],
-                                                      typename Op::gate_t (&gq)[NT], float (&ld)[NL][KP],
-                                                      int (&li)[NL][KP], int row_old, const uint32_t *parity,
-                                                      int nb_par = 0)
+                                                      typename Op::gate_t (&mk)[NT], TileBuf &buf, float (&ld)[NL][KP],
+                                                      int (&li)[NL][KP], int pos_old, int odd_tile0, int nb_par = 0)
 {
     using acc_t = typename Op::acc_t;
     constexpr int S = Op::kSteps;
     const acc_t seed_acc = __builtin_bit_cast(acc_t, cur.sd);
     bool any[NT];
+    typename Op::gate_t m{};
     if constexpr (Op::kNbnn)
-        nbnn_tile_min<Op, NT>(acc_old, gq, nb_par);
+        nbnn_tile_min<Op, NT>(acc_old, mk, nb_par);
     else
-        gate_any<Op, NT, PL>(acc_old, gt, gq, any);
+        gate_any<Op, NT, PL>(acc_old, gt, any, m);
 #pragma unroll
     for (int s = 0; s < S; ++s) {
 #pragma unroll
@@ -1151,7 +1161,7 @@ static __device__ __forceinline__ void pipe_step_regs(AccArr<Op, NT> &acc_new, A
         __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);     // up to three vector ops
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);     // one MFMA
     }
-    if constexpr (!Op::kNbnn) gate_insert<Op, KP, NT, PL>(acc_old, any, thr, gt, gq, ld, li, row_old, h, parity);
+    if constexpr (!Op::kNbnn) gate_insert<Op, KP, NT, PL>(acc_old, any, m, thr, gt, buf, ld, li, pos_old, odd_tile0);
 }
 
 // Two waves per SIMD (256 registers each), except where the lists need one
@@ -1199,6 +1209,8 @@ void k_dist_topk(DistArgs a)
     // [0, NB): waves whose share of the buffer's current stage has landed;
     // [NB, 2NB): waves done reading it (counts accumulate over the item)
     __shared__ uint32_t s_cnt[2 * NB];
+    constexpr bool kTileLists = PL && !Op::kNbnn;       // lists of tiles, filled through append buffers
+    __shared__ uint2 s_buf[kTileLists ? W * kBufEntries * 64 : 1];
     auto cnt_signal = [&](int i) {
         asm volatile("" ::: "memory");
         if ((threadIdx.x & 63) == 0)
@@ -1223,55 +1235,118 @@ void k_dist_topk(DistArgs a)
     const int64_t n_q = a.bd->n_q;
     const void *q_src = a.q ? a.q : a.bd->q;
     const int64_t n_qb = (n_q + QB - 1) / QB;
-    const int64_t n_items = n_qb * a.n_slices;
-    const int n_chunks = (a.tiles_per_slice + a.chunk_tiles - 1) / a.chunk_tiles;
+    TileBuf tbuf{s_buf + (kTileLists ? wave * kBufEntries * 64 + lane : 0), 0};
 
-    // Walk: for every chunk of its slice, a workgroup runs all the (query
-    // block, slice) items it owns before moving to the next chunk.  With the
-    // default chunk (the whole slice) each item is one sweep with its lists in
-    // registers; shorter chunks keep the workgroups of an XCD on the same
-    // references at the same time, with the lists parked in the partial-list
-    // buffer between chunks.
-    for (int c = 0; c < n_chunks; ++c) {
-        for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
-            const int slice = (int)(item / n_qb);
-            const int64_t qb = item - (int64_t)slice * n_qb;
-            const int64_t ts0 = (int64_t)slice * a.tiles_per_slice;
-            const int64_t ts1 = min(ts0 + (int64_t)a.tiles_per_slice, a.n_tiles);
-            const int64_t t0 = ts0 + (int64_t)c * a.chunk_tiles;
-            if (t0 >= ts1) continue;                  // uniform: this slice has fewer chunks
-            const int64_t t1 = min(t0 + (int64_t)a.chunk_tiles, ts1);
-            const int n_t = (int)(t1 - t0);           // multiple of 8, so of MT
+    // Walk.  Every item is a query block and a range of reference tiles.
+    //
+    // Shared lists and the original NBNN: each workgroup first owns
+    // walk.full_rounds whole query blocks (block = workgroup + round * grid) and
+    // runs them chunk by chunk: for every chunk of the index all its blocks,
+    // with the lists parked in the partial-list buffer between chunks (by
+    // default one chunk: the whole index, lists in registers throughout).  The
+    // remaining R < grid blocks would leave workgroups idle for a whole sweep,
+    // so they are cut, in one of two ways:
+    //   slices: walk.rem_slices slices of walk.slice_tiles tiles per block; the
+    //     workgroups take (block, slice) items slice by slice, so those that run
+    //     together read the same tiles (list slot = block * slices + slice);
+    //   runs (rem_slices = 0): the blocks' tiles laid end to end and cut into
+    //     equal runs of walk.slice_tiles, one per workgroup; a run crosses from
+    //     one block into the next where a block ends, and each piece writes a
+    //     list of its own (slot = block + workgroup, unique because every cut
+    //     between pieces advances one of the two).
+    //
+    // One list per lane group: items are (query block, slice) with
+    // walk.n_slices slices of walk.tiles_per_slice tiles, walked chunk by chunk.
+    const int wg = blockIdx.x, grid = gridDim.x;
+    constexpr bool kWhole = PL || Op::kNbnn;
+    const int n_blk = (int)n_qb;
+    const int first_rem = kWhole ? a.bd->walk.full_rounds * grid : 0;      // first of the remaining blocks
+    const int64_t span = kWhole ? a.n_tiles : a.bd->walk.tiles_per_slice;
+    const int n_own = kWhole ? min(n_blk, first_rem) : n_blk * a.bd->walk.n_slices;      // items all workgroups own
+    const int n_chunks = (int)((span + a.chunk_tiles - 1) / a.chunk_tiles);
+    int c = 0, item = wg;                                  // next owned item
+    int64_t rem = wg;                                      // next (block, slice) item, or tile of the run
+    int64_t rem_end = 0;
+    if constexpr (kWhole) {
+        const int64_t n_rem = max(n_blk - first_rem, 0);
+        if (a.bd->walk.rem_slices > 0) {
+            rem_end = n_rem * a.bd->walk.rem_slices;
+        } else {
+            rem = (int64_t)wg * a.bd->walk.slice_tiles;
+            rem_end = min(rem + a.bd->walk.slice_tiles, n_rem * a.n_tiles);
+        }
+    }
+    for (;;) {
+        {
+            int64_t t0, t1;
+            int qb, slot;
+            bool resume = false;                           // lists parked by the chunk before
+            if (c < n_chunks && wg < n_own) {
+                const int slice = kWhole ? 0 : item / n_blk;
+                const int64_t ts0 = slice * span, ts1 = min(ts0 + span, a.n_tiles);
+                qb = item - slice * n_blk;
+                t0 = ts0 + (int64_t)c * a.chunk_tiles;
+                t1 = min(t0 + a.chunk_tiles, ts1);
+                slot = kWhole ? qb : slice;
+                resume = c > 0;
+                item += grid;
+                if (item >= n_own) {
+                    item = wg;
+                    ++c;
+                }
+                if (t0 >= ts1) continue;                   // uniform: this slice has fewer chunks
+            } else if constexpr (!kWhole) {
+                break;
+            } else {
+                if (rem >= rem_end) break;
+                const int slices = a.bd->walk.rem_slices;
+                if (slices > 0) {
+                    const int n_rem = n_blk - first_rem;
+                    const int slice = (int)rem / n_rem, b = (int)rem - slice * n_rem;
+                    t0 = (int64_t)slice * a.bd->walk.slice_tiles;
+                    t1 = min(t0 + a.bd->walk.slice_tiles, a.n_tiles);
+                    qb = first_rem + b;
+                    slot = first_rem + b * slices + slice;
+                    rem += grid;
+                } else {
+                    const int b = (int)(rem / a.n_tiles);
+                    t0 = rem - b * a.n_tiles;
+                    t1 = min(a.n_tiles, t0 + (rem_end - rem));
+                    rem += t1 - t0;
+                    qb = first_rem + b;
+                    slot = qb + wg;
+                }
+            }
+            const int n_t = (int)(t1 - t0);                // multiple of 8, so of MT
 
             uint4 bq[NT][S][Op::kBU];
             int sb[NT];
             int64_t qi[NT];
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
-                qi[nt] = qb * QB + wave * QW + nt * Op::kQT + col;
+                qi[nt] = (int64_t)qb * QB + wave * QW + nt * Op::kQT + col;
                 Op::load_b(q_src, a.q_scale, qi[nt], qi[nt] < n_q, h, bq[nt], sb[nt]);
             }
 
             // the query of list l, and its partial list's offset
             auto list_query = [&](int l) -> int64_t {
-                return PL ? qb * QB + wave * QW + h * Op::kQT + col : qi[l];
+                return PL ? (int64_t)qb * QB + wave * QW + h * Op::kQT + col : qi[l];
             };
             auto list_base = [&](int l) -> int64_t {
-                return PL ? ((int64_t)slice * a.q_cap + list_query(l)) * KP
-                          : ((int64_t)(slice * Op::kGroups + h) * a.q_cap + qi[l]) * KP;
+                return PL ? ((int64_t)slot * QB + wave * QW + h * Op::kQT + col) * KP
+                          : ((int64_t)(slot * Op::kGroups + h) * a.q_cap + qi[l]) * KP;
             };
             float ld[NL][KP];
             int li[NL][KP];
             float thr[NL];
             typename Op::gate_t gt[NL];
-            // shared lists: gate threshold of each query tile's query;
             // original NBNN: each query tile's running minimum key (the
             // lane's share of the rows)
-            typename Op::gate_t gq[NT];
+            typename Op::gate_t mk[NT];
 #pragma unroll
             for (int l = 0; l < NL; ++l) {
                 const int64_t base = list_base(l);
-                const bool load = !Op::kNbnn && c > 0 && list_query(l) < n_q;
+                const bool load = !Op::kNbnn && resume && list_query(l) < n_q;
 #pragma unroll
                 for (int p = 0; p < KP; ++p) {
                     ld[l][p] = load ? a.part_d[base + p] : __builtin_inff();
@@ -1280,10 +1355,7 @@ void k_dist_topk(DistArgs a)
                 thr[l] = ld[l][KP - 1];
                 gt[l] = Op::gate_thr(thr[l]);
             }
-            auto share_gates = [&]() {
-                if constexpr (PL) share_gate_thr<Op, NT>(gt[0], gq, col);
-            };
-            share_gates();
+            tbuf.cnt = 0;
             // A wave whose stage wait gave up marks its first list with a NaN
             // key in the last slot: its threshold turns NaN, so nothing more
             // is inserted, and the kernels that read the lists (merge, FP8
@@ -1306,19 +1378,19 @@ void k_dist_topk(DistArgs a)
                 cur_cls = enc0 >> 1;
                 p_cur = p_prev = enc0 & 1;
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt) gq[nt] = 0x7fffffff;
+                for (int nt = 0; nt < NT; ++nt) mk[nt] = 0x7fffffff;
             }
             auto nbnn_flush = [&]() {
                 if constexpr (Op::kNbnn) {
                     if (__builtin_isnan(ld[0][KP - 1]) && lane == 0) atomicOr(a.status, kStatusWaitGaveUp);
 #pragma unroll
                     for (int nt = 0; nt < NT; ++nt) {
-                        int key = gq[nt];
+                        int key = mk[nt];
 #pragma unroll
                         for (int o = Op::kQT; o < 64; o <<= 1) key = min(key, __shfl_xor(key, o));
                         if (h == 0 && qi[nt] < n_q && key < (1 << 29))
                             atomicMin(a.cls_min + (int64_t)cur_cls * a.q_cap + qi[nt], key);
-                        gq[nt] = 0x7fffffff;
+                        mk[nt] = 0x7fffffff;
                     }
                 }
             };
@@ -1361,7 +1433,11 @@ void k_dist_topk(DistArgs a)
             for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
                 for (int r = 0; r < Op::kAccN; ++r) acc1[nt][r] = Op::init();
-            int row_prev = 0;
+            // a tile's position in the gate: the tile (shared lists) or the
+            // lane's first row of it
+            constexpr int kPosStep = PL ? 1 : kTileRows;
+            auto pos_of = [&](int t) -> int { return ((int)t0 + t) * kPosStep + (PL ? 0 : 4 * h); };
+            int pos_prev = 0;
             int buf = 0;
             if constexpr (kCounters) {
                 // Stage s lives in buffer s % NB as that buffer's fill s / NB.
@@ -1397,7 +1473,7 @@ void k_dist_topk(DistArgs a)
                     }
                     static_for<0, MT>([&](auto M) {
                         constexpr int m = decltype(M)::value;
-                        const int row_t = (int)((t0 + (int64_t)st * MT + m) * kTileRows) + (PL ? 0 : 4 * h);
+                        const int pos_t = pos_of(st * MT + m);
                         if constexpr (m == kLandedAt) {
                             wait_vmcnt<(PF - 1) * LPS>();   // this wave's share of stage st + 1 landed
                             cnt_signal((st + 1) % NB);
@@ -1416,11 +1492,11 @@ void k_dist_topk(DistArgs a)
                         }
                         const int nb_par = m == 0 ? p_prev : p_cur;
                         if constexpr (m % 2 == 0)
-                            pipe_step_regs<Op, KP, NT, PL>(acc0, acc1, bq, sb, tr[0], h, thr, gt, gq, ld, li, row_prev,
-                                                           a.parity, nb_par);
+                            pipe_step_regs<Op, KP, NT, PL>(acc0, acc1, bq, sb, tr[0], thr, gt, mk, tbuf, ld, li,
+                                                           pos_prev, a.odd_tile0, nb_par);
                         else
-                            pipe_step_regs<Op, KP, NT, PL>(acc1, acc0, bq, sb, tr[1], h, thr, gt, gq, ld, li, row_prev,
-                                                           a.parity, nb_par);
+                            pipe_step_regs<Op, KP, NT, PL>(acc1, acc0, bq, sb, tr[1], thr, gt, mk, tbuf, ld, li,
+                                                           pos_prev, a.odd_tile0, nb_par);
                         // the step of a stage's first tile gated the previous
                         // stage's last tile: a new class starts after it
                         if constexpr (Op::kNbnn && m == 0) {
@@ -1429,7 +1505,7 @@ void k_dist_topk(DistArgs a)
                                 cur_cls = st_cls;
                             }
                         }
-                        row_prev = row_t;
+                        pos_prev = pos_t;
                     });
                 }
             } else if constexpr (kPrefetch) {
@@ -1458,7 +1534,7 @@ void k_dist_topk(DistArgs a)
                     }
                     static_for<0, MT>([&](auto M) {
                         constexpr int m = decltype(M)::value;
-                        const int row_t = (int)((t0 + (int64_t)st * MT + m) * kTileRows) + (PL ? 0 : 4 * h);
+                        const int pos_t = pos_of(st * MT + m);
                         if constexpr (m == MT - 1) {
                             wait_vmcnt<(PD - 1) * LPS>();       // stage st + 1 landed (this wave's part)
                             __builtin_amdgcn_s_waitcnt(0xc07f); // lgkmcnt(0): this wave's reads of stage st done
@@ -1475,18 +1551,18 @@ void k_dist_topk(DistArgs a)
                         }
                         const int nb_par = m == 0 ? p_prev : p_cur;
                         if constexpr (m % 2 == 0)
-                            pipe_step_regs<Op, KP, NT, PL>(acc0, acc1, bq, sb, tr[0], h, thr, gt, gq, ld, li, row_prev,
-                                                           a.parity, nb_par);
+                            pipe_step_regs<Op, KP, NT, PL>(acc0, acc1, bq, sb, tr[0], thr, gt, mk, tbuf, ld, li,
+                                                           pos_prev, a.odd_tile0, nb_par);
                         else
-                            pipe_step_regs<Op, KP, NT, PL>(acc1, acc0, bq, sb, tr[1], h, thr, gt, gq, ld, li, row_prev,
-                                                           a.parity, nb_par);
+                            pipe_step_regs<Op, KP, NT, PL>(acc1, acc0, bq, sb, tr[1], thr, gt, mk, tbuf, ld, li,
+                                                           pos_prev, a.odd_tile0, nb_par);
                         if constexpr (Op::kNbnn && m == 0) {
                             if (st_cls != cur_cls) {
                                 nbnn_flush();
                                 cur_cls = st_cls;
                             }
                         }
-                        row_prev = row_t;
+                        pos_prev = pos_t;
                     });
                     buf = (buf + 1) % NB;
                 }
@@ -1502,15 +1578,15 @@ void k_dist_topk(DistArgs a)
                 }
 #pragma unroll
                 for (int m = 0; m < MT; m += 2) {
-                    const int row_t = (int)((t0 + (int64_t)st * MT + m) * kTileRows) + (PL ? 0 : 4 * h);
+                    const int pos_t = pos_of(st * MT + m);
                     pipe_step<Op, KP, NT, PL>(acc0, acc1, bq, sb, s_frag[buf] + m * TILE_U4, s_seed[buf] + m * 8,
-                                              s_rsc[buf] + (Op::kScaled ? m * kTileRows : 0), lane, h, thr, gt, gq,
-                                              ld, li, row_prev, a.parity);
+                                              s_rsc[buf] + (Op::kScaled ? m * kTileRows : 0), lane, h, thr, gt, mk,
+                                              tbuf, ld, li, pos_prev, a.odd_tile0);
                     pipe_step<Op, KP, NT, PL>(acc1, acc0, bq, sb, s_frag[buf] + (m + 1) * TILE_U4,
                                               s_seed[buf] + (m + 1) * 8,
                                               s_rsc[buf] + (Op::kScaled ? (m + 1) * kTileRows : 0), lane, h, thr,
-                                              gt, gq, ld, li, row_t, a.parity);
-                    row_prev = row_t + kTileRows;
+                                              gt, mk, tbuf, ld, li, pos_t, a.odd_tile0);
+                    pos_prev = pos_t + kPosStep;
                 }
                 // Stage st + 1 has landed (this wave's part); after the barrier
                 // every wave's part has, and stage st has been read by all (the
@@ -1524,11 +1600,12 @@ void k_dist_topk(DistArgs a)
             }
             wait_vmcnt<0>();                    // drain the loads past the end of the chunk
             __syncthreads();
-            tiles_select<Op, KP, NT, PL>(acc1, thr, gt, gq, ld, li, row_prev, h, a.parity, p_cur);
+            tiles_select<Op, KP, NT, PL>(acc1, thr, gt, mk, tbuf, ld, li, pos_prev, a.odd_tile0, p_cur);
             if constexpr (Op::kNbnn) {
                 nbnn_flush();
                 continue;
             }
+            if constexpr (kTileLists) buf_merge<Op, KP>(tbuf, thr[0], gt[0], ld[0], li[0]);
 
 #pragma unroll
             for (int l = 0; l < NL; ++l) {

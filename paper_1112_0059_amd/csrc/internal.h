@@ -22,6 +22,18 @@ enum Fmt { FMT_F16 = 0, FMT_BF16 = 1, FMT_FP8 = 2, FMT_I8 = 3, FMT_I8L = 4, FMT_
 constexpr int kNumFmt = 6;
 constexpr int kNumModes = 6;             // search modes of include/lnbnn.h
 
+// Split of a batch over the distance kernel's workgroups (see k_dist_topk),
+// chosen for the batch's own size and read on the device.
+struct Walk {
+    // shared lists, original NBNN
+    int32_t full_rounds;        // whole query blocks per workgroup
+    int32_t rem_slices;         // slices per remaining block (0: equal runs)
+    int32_t slice_tiles;        // tiles per slice, or per workgroup's run (multiple of 8)
+    // one list per lane group
+    int32_t n_slices;           // reference slices per query block,
+    int32_t tiles_per_slice;    // and their length (multiple of 8)
+};
+
 // Batch shape and the batch's data pointers, read on the device, so one
 // captured launch sequence serves every batch (and any caller buffers) up
 // to the capacity it was captured for.
@@ -32,6 +44,7 @@ struct BatchDesc {
     int32_t *cls;       // [n_img] argmin class per image
     int32_t *nbr_idx;   // [n_q, k+1] neighbour indices, or null
     float *nbr_dist;    // [n_q, k+1] squared distances, or null
+    Walk walk;          // how the distance kernel's workgroups split the batch
 };
 
 // A distance-kernel variant: queries per wave = qt * nt, reference tiles
@@ -56,13 +69,13 @@ struct DistArgs {
     const uint4 *frag;          // packed reference fragments
     const float *seed;          // per-row accumulator seed (norm), +inf on padding
     const int32_t *row_scale;   // fp8: per-row exponent bias (else null)
-    const uint32_t *parity;     // int8: per-tile mask of the rows' ||r - 128||^2 parities
+    int32_t odd_tile0;          // int8: first tile of the rows of odd ||r - 128||^2
     int64_t n_tiles;            // 32-row tiles in the padded index (multiple of 8)
-    int32_t tiles_per_slice;    // multiple of 8
-    int32_t n_slices;
     int32_t chunk_tiles;        // tiles one item runs before the workgroup moves on (multiple of 8)
     int64_t q_cap;              // capacity: part buffers are laid out for q_cap queries
-    float *part_d;              // [n_slices * lists per query][q_cap][kp]
+    // partial lists of (key, row) [n_slices * lists per query][q_cap][kp], or
+    // (shared lists) of (key, tile) [slot][queries per block][kp]
+    float *part_d;
     int32_t *part_i;
     int32_t *status;            // bit 0: a bounded stage wait gave up (set by the kernels that
                                 // read the lists, which carry the mark as a NaN key)
@@ -73,6 +86,13 @@ struct DistArgs {
     // [n_classes][q_cap] (atomic minima)
     const int32_t *tile_class;
     int32_t *cls_min;
+};
+
+// Which partial lists hold a query's tiles (shared lists).
+struct SlotMap {
+    int64_t n_tiles;
+    int32_t block;              // queries per block
+    int32_t grid;               // workgroups of the distance kernel
 };
 
 struct NbnnArgs {
@@ -87,6 +107,7 @@ struct NbnnArgs {
 // Bits of the device status word of a launch sequence.
 constexpr int32_t kStatusWaitGaveUp = 1;
 
+// Result of the FP8 modes: exact re-rank of the candidates and per-image sums.
 struct RerankArgs {
     const BatchDesc *bd;
     const int64_t *offsets;     // device [n_img + 1]
@@ -115,6 +136,8 @@ struct FinishArgs {
     const BatchDesc *bd;
     const int64_t *offsets;     // device [n_img + 1]
     const int32_t *labels;      // [n_refs]
+    const int32_t *perm;        // reference of every packed row, or null (row r holds reference r)
+    int64_t n_rows;             // packed rows
     int64_t n_refs;
     int32_t n_lists;            // n_slices * lists per query (at most 64)
     int32_t kp_stride;          // list length in the part buffers
@@ -125,6 +148,18 @@ struct FinishArgs {
     const int32_t *part_i;
     unsigned long long *totals; // [n_img, n_classes] int64 (two's complement)
     int32_t *status;            // set when a list carries a stage-wait mark
+};
+
+// Rows of a query's best tiles, recomputed (shared lists).
+struct RefineArgs {
+    const void *q;              // as DistArgs
+    const int32_t *q_scale;
+    const uint4 *frag;
+    const float *seed;
+    const int32_t *row_scale;
+    int32_t odd_tile0;
+    int32_t n_need;             // tiles to recompute: k + 1, or the FP8 list length
+    SlotMap map;
 };
 
 // number of kernel variants and their parameters
@@ -171,14 +206,25 @@ int kp_bucket(int kp, int fmt);         // list length compiled for kp (0 = unsu
 // Upload-side packing.  refs_u8 / refs_f32 are device pointers.
 hipError_t launch_pack_u8(const uint8_t *refs, int64_t n_refs, int64_t n_pad, int fmt,
                           uint4 *frag, float *seed, hipStream_t s);
-// perm (device, may be null): row r of the packed index holds reference
-// perm[r], or padding where perm[r] < 0 (null: row r holds reference r)
-hipError_t launch_pack_i8(const uint8_t *refs, int64_t n_refs, int64_t n_pad, int dim, uint4 *frag,
-                          int32_t *seed, uint32_t *parity, hipStream_t s, const int32_t *perm = nullptr);
+// perm (device): row r of the packed index holds reference perm[r], or padding
+// where perm[r] < 0
+hipError_t launch_pack_i8(const uint8_t *refs, int64_t n_pad, int dim, uint4 *frag, int32_t *seed, hipStream_t s,
+                          const int32_t *perm);
+// Rows by parity of ||r - 128||^2: the even ones first, then, from row
+// even_pad, the odd ones, each part in reference order.  block_odd [n_blocks
+// + 1] receives the odd rows before each 256-row block (the last entry: all).
+hipError_t launch_parity_count(const uint8_t *par, int64_t n_refs, int32_t *block_odd, hipStream_t s);
+hipError_t launch_parity_perm(const uint8_t *par, int64_t n_refs, const int32_t *block_odd, int64_t even_pad,
+                              int64_t n_pad, int32_t *perm, hipStream_t s);
 hipError_t launch_fp8_index(const float *refs, int64_t n_refs, int64_t n_pad, uint4 *frag, float *seed,
                             int32_t *row_scale, hipStream_t s);
 hipError_t launch_fp8_qprep(const BatchDesc *bd, int64_t q_cap, uint4 *q8, int32_t *qsc, hipStream_t s);
+// merge of the candidate lists into a.cand (one list per lane group)
+hipError_t launch_cand_merge(const RerankArgs &a, int64_t q_cap, hipStream_t s);
 hipError_t launch_rerank(const RerankArgs &a, int64_t q_cap, int64_t img_cap, hipStream_t s);
+// shared lists: the exact formats' whole finish, and the FP8 candidates
+hipError_t launch_refine(int fmt, const RefineArgs &r, const FinishArgs &a, int64_t q_cap, hipStream_t s);
+hipError_t launch_refine_fp8(const RefineArgs &r, const RerankArgs &a, int64_t q_cap, hipStream_t s);
 int grid_for(int64_t n, int block, int cap);
 
 hipError_t launch_dist_topk(int variant, int fmt, int kp, const DistArgs &a, int grid,

@@ -3,7 +3,8 @@
 //
 // K0  pack        references -> MFMA A-fragment tiles + accumulator seeds
 // K2  finish      merge of the per-slice lists, background distance,
-//                 per-class update of the image totals (Algorithm 2 body)
+//                 per-class update of the image totals (Algorithm 2 body); the
+//                 shared-list variants finish in refine.hip
 // K3  argmin      per-image decision (Algorithm 2, return line)
 // plus the variant table and the dispatch to the K1 instances.  (The FP8
 // packing, candidate merge, exact re-rank and per-image reduction live in
@@ -15,82 +16,145 @@
 namespace lnbnn {
 
 // ---------------------------------------------------------------------------
-// K0: packing of u8 references ([n_refs, Op::kRow] bytes).  Fragment
-// u = (tile * kSteps + s) * 64 + lane holds the K elements lane `lane`
-// supplies at step s for row 32*tile + (lane & 31) (eight FP16/BF16 values,
-// or sixteen int8 values).  With `perm`, packed row r holds reference
-// perm[r] (padding where perm[r] < 0): the class-sorted copy of the index.
+// K0: packing of u8 references.
+//
+// k_pack_u8 (16-bit formats): fragment u = (tile * kSteps + s) * 64 + lane
+// holds the eight K elements lane `lane` supplies at step s for row 32*tile +
+// (lane & 31).
 // ---------------------------------------------------------------------------
-static __device__ __forceinline__ int64_t source_row(const int32_t *perm, int64_t row, int64_t n_refs)
-{
-    if (perm) return perm[row];
-    return row < n_refs ? row : -1;
-}
-
 template <class Op>
 __global__ void k_pack_u8(const uint8_t *__restrict__ refs, int64_t n_refs, int64_t n_frag,
-                          uint4 *__restrict__ frag, const int32_t *__restrict__ perm)
+                          uint4 *__restrict__ frag)
 {
     for (int64_t u = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; u < n_frag;
          u += (int64_t)gridDim.x * blockDim.x) {
         const int lane = (int)(u & 63);
         const int s = (int)((u >> 6) % Op::kSteps);
         const int64_t tile = (u >> 6) / Op::kSteps;
-        const int64_t src = source_row(perm, tile * kTileRows + (lane & 31), n_refs);
-        const bool ok = src >= 0;
+        const int64_t src = tile * kTileRows + (lane & 31);
+        const bool ok = src < n_refs;
         frag[u] = Op::pack_frag(refs + (ok ? src : 0) * Op::kRow, ok, s, lane >> 5);
     }
 }
 
-// INT8 seeds of [n_refs, dim] references: floor(||s||^2 / 2) + sum(s) with
-// s = r - 128 (stored as the int32 bit pattern), 2^30 on padding rows; and
-// per 32-row tile the mask of the rows' ||s||^2 parities (= parity of sum(r)).
-__global__ void k_seed_i8(const uint8_t *__restrict__ refs, int64_t n_refs, int64_t n_pad, int dim,
-                          int32_t *__restrict__ seed, uint32_t *__restrict__ parity,
-                          const int32_t *__restrict__ perm)
+// INT8 rows: fragments and seeds in one pass.  Packed row r holds reference
+// perm[r] (padding where perm[r] < 0).  G lanes share a row, one 16-byte chunk
+// each (lane c: K elements 16c..16c+15, fragment half c & 1 of step c >> 1), so a
+// row is read as one contiguous run, once.  Seeds: floor(||s||^2 / 2) + sum(s)
+// with s = r - 128 (stored as the int32 bit pattern), 2^30 on padding rows.
+template <class Op, int G>
+__global__ __launch_bounds__(256) void k_pack_i8(const uint8_t *__restrict__ refs, int64_t n_pad,
+                                                 uint4 *__restrict__ frag, int32_t *__restrict__ seed,
+                                                 const int32_t *__restrict__ perm)
 {
-    for (int64_t row = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; row < n_pad;
-         row += (int64_t)gridDim.x * blockDim.x) {
+    constexpr int C = Op::kRow / 16;
+    const int c = threadIdx.x % G;
+    for (int64_t row = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / G; row < n_pad;
+         row += (int64_t)gridDim.x * blockDim.x / G) {
+        const int32_t src = perm[row];
         int32_t sq = 0, sum = 0;
-        const int64_t src = source_row(perm, row, n_refs);
-        const bool real = src >= 0;
-        if (real) {
-            const uint4 *p = reinterpret_cast<const uint4 *>(refs + src * dim);
-            for (int c = 0; c < dim / 16; ++c) {
-                const uint4 v = p[c];
-                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-                for (int i = 0; i < 4; ++i)
-                    for (int b = 0; b < 4; ++b) {
-                        const int32_t x = (int32_t)((w[i] >> (8 * b)) & 0xffu) - 128;
-                        sq += x * x;
-                        sum += x;
-                    }
+        if (c < C) {
+            const uint4 v = Op::pack_frag(refs + (int64_t)(src < 0 ? 0 : src) * Op::kRow, src >= 0, c >> 1, c & 1);
+            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                sq = __builtin_amdgcn_sdot4((int)w[i], (int)w[i], sq, false);
+                sum = __builtin_amdgcn_sdot4((int)w[i], 0x01010101, sum, false);
             }
+            frag[((row / kTileRows) * Op::kSteps + (c >> 1)) * 64 + (row & 31) + 32 * (c & 1)] = v;
         }
-        seed[row] = real ? (sq >> 1) + sum : OpI8::kPadSeed;
-        // one 32-row tile per wave half: bit (row & 31) of its mask
-        const uint64_t bits = __builtin_amdgcn_ballot_w64(real && (sq & 1));
-        const int lane = threadIdx.x & 63;
-        if ((lane & 31) == 0) parity[row >> 5] = (uint32_t)(bits >> (lane & 32));
+#pragma unroll
+        for (int o = 1; o < G; o <<= 1) {
+            sq += __shfl_xor(sq, o);
+            sum += __shfl_xor(sum, o);
+        }
+        if (c == 0) seed[row] = src >= 0 ? (sq >> 1) + sum : Op::kPadSeed;
     }
 }
 
 // Parity of ||r - 128||^2 per reference row: the same as the parity of the
-// row's byte sum, since x^2 and x have the same parity and 128 is even.
-__global__ void k_row_parity(const uint8_t *__restrict__ refs, int64_t n_refs, int dim, uint8_t *__restrict__ out)
+// row's byte sum, since x^2 and x have the same parity and 128 is even; that
+// is the xor of the bytes' low bits.  Sixteen lanes per row (one 16-byte chunk
+// each), so rows are read as contiguous runs.
+__global__ __launch_bounds__(256) void k_row_parity(const uint8_t *__restrict__ refs, int64_t n_refs, int dim,
+                                                    uint8_t *__restrict__ out)
 {
-    for (int64_t row = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; row < n_refs;
-         row += (int64_t)gridDim.x * blockDim.x) {
-        const uint4 *p = reinterpret_cast<const uint4 *>(refs + row * dim);
+    const int c = threadIdx.x & 15;
+    for (int64_t row = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 4; row < n_refs;
+         row += ((int64_t)gridDim.x * blockDim.x) >> 4) {
         uint32_t x = 0;
-        for (int c = 0; c < dim / 16; ++c) {
-            const uint4 v = p[c];
-            x ^= v.x ^ v.y ^ v.z ^ v.w;
+        if (c < dim / 16) {
+            const uint4 v = reinterpret_cast<const uint4 *>(refs + row * dim)[c];
+            x = v.x ^ v.y ^ v.z ^ v.w;
         }
-        // the parity of the byte sum is the xor of the bytes' low bits
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) x ^= __shfl_xor(x, o);
         x ^= x >> 16;
         x ^= x >> 8;
-        out[row] = (uint8_t)(x & 1u);
+        if (c == 0) out[row] = (uint8_t)(x & 1u);
+    }
+}
+
+// Odd rows of each 256-row block.
+__global__ __launch_bounds__(256) void k_parity_blocks(const uint8_t *__restrict__ par, int64_t n_refs,
+                                                       int32_t *__restrict__ block_odd)
+{
+    __shared__ int s_n[4];
+    const int64_t row = blockIdx.x * (int64_t)256 + threadIdx.x;
+    const unsigned long long m = __builtin_amdgcn_ballot_w64(row < n_refs && par[row]);
+    if ((threadIdx.x & 63) == 0) s_n[threadIdx.x >> 6] = (int)__builtin_popcountll(m);
+    __syncthreads();
+    if (threadIdx.x == 0) block_odd[blockIdx.x] = s_n[0] + s_n[1] + s_n[2] + s_n[3];
+}
+
+// In-place exclusive prefix sums of v[0, n), the total into v[n].  One workgroup.
+__global__ __launch_bounds__(1024) void k_prefix(int32_t *__restrict__ v, int64_t n)
+{
+    __shared__ int s_w[16];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int base = 0;
+    for (int64_t at = 0; at < n; at += 1024) {
+        const int64_t i = at + threadIdx.x;
+        const int x = i < n ? v[i] : 0;
+        int inc = x;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(inc, o);
+            if (lane >= o) inc += y;
+        }
+        if (lane == 63) s_w[wave] = inc;
+        __syncthreads();
+        int before = 0, all = 0;
+        for (int w = 0; w < 16; ++w) {
+            before += w < wave ? s_w[w] : 0;
+            all += s_w[w];
+        }
+        if (i < n) v[i] = base + before + inc - x;
+        base += all;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) v[n] = base;
+}
+
+// The packed order: even rows from 0, odd rows from even_pad, padding between.
+__global__ __launch_bounds__(256) void k_parity_perm(const uint8_t *__restrict__ par, int64_t n_refs, int64_t n_blocks,
+                                                     const int32_t *__restrict__ block_odd, int64_t even_pad,
+                                                     int64_t n_pad, int32_t *__restrict__ perm)
+{
+    __shared__ int s_n[4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t row = blockIdx.x * (int64_t)256 + threadIdx.x;
+    const bool odd = row < n_refs && par[row];
+    const unsigned long long m = __builtin_amdgcn_ballot_w64(odd);
+    if (lane == 0) s_n[wave] = (int)__builtin_popcountll(m);
+    __syncthreads();
+    int64_t before = block_odd[blockIdx.x];          // odd rows before this one
+    for (int w = 0; w < wave; ++w) before += s_n[w];
+    before += __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+    if (row < n_refs) perm[odd ? even_pad + before : row - before] = (int32_t)row;
+    if (blockIdx.x == 0) {
+        const int64_t n_odd = block_odd[n_blocks];
+        for (int64_t r = n_refs - n_odd + threadIdx.x; r < even_pad; r += 256) perm[r] = -1;
+        for (int64_t r = even_pad + n_odd + threadIdx.x; r < n_pad; r += 256) perm[r] = -1;
     }
 }
 
@@ -136,6 +200,15 @@ static __device__ __forceinline__ bool pair_less(float d0, int i0, float d1, int
     return d0 < d1 || (d0 == d1 && (uint32_t)i0 < (uint32_t)i1);
 }
 
+// Reference of a packed row.  A row outside the packed set cannot occur; the
+// guards keep a defect visible as a wrong answer instead of a wild read.
+static __device__ __forceinline__ int reference_of(const FinishArgs &a, int row)
+{
+    if (row < 0 || row >= a.n_rows) return -1;
+    const int i = a.perm ? a.perm[row] : row;
+    return i < a.n_refs ? i : -1;
+}
+
 __global__ __launch_bounds__(256) void k_finish(FinishArgs a)
 {
     const int64_t n_q = a.bd->n_q;
@@ -169,7 +242,7 @@ __global__ __launch_bounds__(256) void k_finish(FinishArgs a)
             }
             heads[bl] += 1;
             dd[p] = bd;
-            ii[p] = bi;
+            ii[p] = reference_of(a, bi);
         }
         // ||q - shift||^2 turns the key back into the squared distance
         const uint4 *qr = reinterpret_cast<const uint4 *>(static_cast<const uint8_t *>(a.bd->q) + q * a.dim);
@@ -193,9 +266,7 @@ __global__ __launch_bounds__(256) void k_finish(FinishArgs a)
         const int db = (int)dd[a.k];
         int lab[kMaxKP];
         for (int j = 0; j < a.k; ++j) {
-            // an index outside the reference set cannot occur; the guard keeps
-            // a defect visible as a wrong answer instead of a wild read
-            const int c = (ii[j] >= 0 && ii[j] < a.n_refs) ? a.labels[ii[j]] : 0;
+            const int c = ii[j] >= 0 ? a.labels[ii[j]] : 0;
             lab[j] = c;
             bool first = true;
             for (int jj = 0; jj < j; ++jj) first = first && (lab[jj] != c);
@@ -464,10 +535,10 @@ hipError_t launch_pack_u8(const uint8_t *refs, int64_t n_refs, int64_t n_pad, in
     const int64_t n_tiles = n_pad / kTileRows;
     if (fmt == FMT_F16) {
         const int64_t n_frag = n_tiles * OpF16::kSteps * 64;
-        k_pack_u8<OpF16><<<grid_for(n_frag, 256, 65536), 256, 0, s>>>(refs, n_refs, n_frag, frag, nullptr);
+        k_pack_u8<OpF16><<<grid_for(n_frag, 256, 65536), 256, 0, s>>>(refs, n_refs, n_frag, frag);
     } else if (fmt == FMT_BF16) {
         const int64_t n_frag = n_tiles * OpBF16::kSteps * 64;
-        k_pack_u8<OpBF16><<<grid_for(n_frag, 256, 65536), 256, 0, s>>>(refs, n_refs, n_frag, frag, nullptr);
+        k_pack_u8<OpBF16><<<grid_for(n_frag, 256, 65536), 256, 0, s>>>(refs, n_refs, n_frag, frag);
     } else {
         return hipErrorInvalidValue;
     }
@@ -480,23 +551,33 @@ hipError_t launch_pack_u8(const uint8_t *refs, int64_t n_refs, int64_t n_pad, in
     return e;
 }
 
-hipError_t launch_pack_i8(const uint8_t *refs, int64_t n_refs, int64_t n_pad, int dim, uint4 *frag,
-                          int32_t *seed, uint32_t *parity, hipStream_t s, const int32_t *perm)
+hipError_t launch_pack_i8(const uint8_t *refs, int64_t n_pad, int dim, uint4 *frag, int32_t *seed, hipStream_t s,
+                          const int32_t *perm)
 {
-    if (dim == kDim) {
-        const int64_t n_frag = (n_pad / kTileRows) * OpI8::kSteps * 64;
-        k_pack_u8<OpI8><<<grid_for(n_frag, 256, 65536), 256, 0, s>>>(refs, n_refs, n_frag, frag, perm);
-    } else if (dim == kDimLoc) {
-        const int64_t n_frag = (n_pad / kTileRows) * OpI8L::kSteps * 64;
-        k_pack_u8<OpI8L><<<grid_for(n_frag, 256, 65536), 256, 0, s>>>(refs, n_refs, n_frag, frag, perm);
-    } else {
+    if (dim == kDim)
+        k_pack_i8<OpI8, 8><<<grid_for(n_pad * 8, 256, 65536), 256, 0, s>>>(refs, n_pad, frag, seed, perm);
+    else if (dim == kDimLoc)
+        k_pack_i8<OpI8L, 16><<<grid_for(n_pad * 16, 256, 65536), 256, 0, s>>>(refs, n_pad, frag, seed, perm);
+    else
         return hipErrorInvalidValue;
-    }
+    return hipGetLastError();
+}
+
+hipError_t launch_parity_count(const uint8_t *par, int64_t n_refs, int32_t *block_odd, hipStream_t s)
+{
+    const int64_t n_blocks = (n_refs + 255) / 256;
+    k_parity_blocks<<<(unsigned)n_blocks, 256, 0, s>>>(par, n_refs, block_odd);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // whole waves over whole tiles: n_pad is a multiple of 256, as is the
-    // grid stride
-    k_seed_i8<<<grid_for(n_pad, 256, 65536), 256, 0, s>>>(refs, n_refs, n_pad, dim, seed, parity, perm);
+    k_prefix<<<1, 1024, 0, s>>>(block_odd, n_blocks);
+    return hipGetLastError();
+}
+
+hipError_t launch_parity_perm(const uint8_t *par, int64_t n_refs, const int32_t *block_odd, int64_t even_pad,
+                              int64_t n_pad, int32_t *perm, hipStream_t s)
+{
+    const int64_t n_blocks = (n_refs + 255) / 256;
+    k_parity_perm<<<(unsigned)n_blocks, 256, 0, s>>>(par, n_refs, n_blocks, block_odd, even_pad, n_pad, perm);
     return hipGetLastError();
 }
 
@@ -538,7 +619,7 @@ hipError_t launch_nbnn_totals(const NbnnArgs &a, int64_t img_cap, hipStream_t s)
 // sequence is captured in a graph).
 hipError_t launch_row_parity(const uint8_t *refs, int64_t n_refs, int dim, uint8_t *out, hipStream_t s)
 {
-    k_row_parity<<<grid_for(n_refs, 256, 65536), 256, 0, s>>>(refs, n_refs, dim, out);
+    k_row_parity<<<grid_for(n_refs * 16, 256, 65536), 256, 0, s>>>(refs, n_refs, dim, out);
     return hipGetLastError();
 }
 

@@ -83,8 +83,8 @@ extern "C" int lnbnn_classify_noalloc(lnbnn_index *ix, const void *queries_dev, 
     const int64_t nc = ix->n_classes;
     const int64_t q_cap = std::max<int64_t>(1, n_q);
     Plan plan;
-    if ((rc = make_plan(ix, mode, dist_list_len(mode, k), q_cap, -1, &plan))) return rc;
-    const int64_t part = work_elems(ix, plan, q_cap);
+    if ((rc = make_plan(ix, mode, k, q_cap, n_q, kSplitLists, &plan))) return rc;
+    int64_t part = batch_elems(ix, plan, q_cap);
     const int n_cand = fp8_candidates(k);
 
     // measure, then carve
@@ -110,6 +110,14 @@ extern "C" int lnbnn_classify_noalloc(lnbnn_index *ix, const void *queries_dev, 
         int32_t *upd_cls = fp8 ? c.take<int32_t>(q_cap * k) : nullptr;
         double *upd_delta = fp8 ? c.take<double>(q_cap * k) : nullptr;
         if (pass == 0) {
+            if (c.used > kScratchBytes && plan.pl && plan.max_lists > 1) {
+                // fewer partial lists: at most as many as the other plans, then none but the blocks' own
+                if ((rc = make_plan(ix, mode, k, q_cap, n_q, plan.max_lists > kMaxLists ? kMaxLists : 1, &plan)))
+                    return rc;
+                part = batch_elems(ix, plan, q_cap);
+                --pass;
+                continue;
+            }
             if (c.used > kScratchBytes)
                 return set_err(LNBNN_ENOMEM,
                                "this batch (%lld descriptors, %d images, k = %d) needs %zu bytes of scratch; "
@@ -140,7 +148,8 @@ extern "C" int lnbnn_classify_noalloc(lnbnn_index *ix, const void *queries_dev, 
         io.upd_cls = upd_cls;
         io.upd_delta = upd_delta;
     }
-    const BatchDesc hb{n_q, n_images, queries_dev, out_class_dev, out_nbr_idx_dev, out_nbr_dist_dev};
+    const BatchDesc hb{n_q, n_images, queries_dev, out_class_dev, out_nbr_idx_dev, out_nbr_dist_dev,
+                       plan.walk};
     int result = LNBNN_OK;
     hipError_t e = hipMemcpyAsync(const_cast<BatchDesc *>(io.bd), &hb, sizeof hb, hipMemcpyHostToDevice, s);
     if (e == hipSuccess)

@@ -3,7 +3,8 @@
 //   k_fp8_rowprep   per reference: power-of-two scale, E8M0 exponent, seed
 //   k_fp8_pack      references -> FP8 A-fragment tiles
 //   k_fp8_qprep     queries -> FP8 codes of -q * 2^e_q and E8M0 2^(1-e_q)
-//   k_cand_merge    per query: 4k best candidates over the half/slice lists
+//   k_cand_merge    per query: 4k best candidates over the half/slice lists (the
+//                   shared-list variants find theirs in refine.hip)
 //   k_rerank        per query (one wave): exact FP32 squared distances of the
 //                   candidates, the k+1 nearest by (distance, index), and
 //                   Algorithm 2's per-class updates dist_C - dist_B
@@ -333,13 +334,16 @@ hipError_t launch_fp8_qprep(const BatchDesc *bd, int64_t q_cap, uint4 *q8, int32
     return hipGetLastError();
 }
 
-hipError_t launch_rerank(const RerankArgs &a, int64_t q_cap, int64_t img_cap, hipStream_t s)
+hipError_t launch_cand_merge(const RerankArgs &a, int64_t q_cap, hipStream_t s)
 {
     k_cand_merge<<<grid_for(q_cap, 256, 16384), 256, 0, s>>>(a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    return hipGetLastError();
+}
+
+hipError_t launch_rerank(const RerankArgs &a, int64_t q_cap, int64_t img_cap, hipStream_t s)
+{
     k_rerank<<<grid_for(q_cap, 4, 65536), 256, 0, s>>>(a);
-    e = hipGetLastError();
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     k_img_reduce<<<grid_for(img_cap, 1, 16384), 256, 0, s>>>(a);
     return hipGetLastError();

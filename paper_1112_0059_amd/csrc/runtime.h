@@ -72,13 +72,23 @@ struct Plan {
     int variant = 0;
     int fmt = 0;
     int kpb = 0;                // compiled list length
-    int n_slices = 1;
-    int n_lists = 2;            // partial lists per query: n_slices * lists per slice
-    int tiles_per_slice = 0;
+    bool pl = false;            // shared lists (of tiles)
+    int n_slices = 1;           // most pieces a query block's sweep is cut into
+    int n_lists = 2;            // one list per lane group: n_slices * lists per slice
+    Walk walk{};                // the split, chosen for the batch's own size
+    int block = 0;              // queries per block
     int grid = 1;
+    int max_lists = 0;          // shared lists: most partial lists per query
+    int64_t lists = 0;          // shared lists: partial lists this batch uses
     int chunk_tiles = 8;        // tiles per chunk of the chunk-major walk
     int64_t q_cap = 0;          // capacity the plan (and part buffers) serve
 };
+
+// Partial lists per query a shared-list plan may split into: one per
+// workgroup of a full grid where a call's own workspace holds them, and as
+// many as the one-list-per-lane-group plans where buffers are sized for
+// those (the serving slots' share of the budget).
+constexpr int kSplitLists = 256;
 
 // Everything a batch launch sequence needs; pointers are device pointers.
 struct BatchIO {
@@ -137,11 +147,14 @@ struct lnbnn_index {
     int32_t *labels = nullptr;
     float *ref_f32 = nullptr;       // FP8 mode: FP32 references for the re-rank
     int32_t *row_scale = nullptr;   // FP8 mode: E8M0 exponent of every padded row
-    uint32_t *parity = nullptr;     // INT8 mode: per-tile mask of ||r - 128||^2 parities
+    // INT8 mode: rows packed by the parity of ||r - 128||^2, the even ones
+    // first; the reference of every packed row (-1: padding), and the first
+    // tile of the odd ones
+    int32_t *perm = nullptr;
+    int32_t odd_tile0 = 0;
     // original NBNN mode: the class-sorted INT8 copy (each class's rows
     // grouped by the parity of ||r - 128||^2, every group padded to 256
-    // rows), its parity masks and 2 x class + parity of each of its tiles
-    uint32_t *parity_n = nullptr;
+    // rows), and 2 x class + parity of each of its tiles
     int32_t *tile_class = nullptr;
     int64_t rows[lnbnn::kNumFmt] = {};   // padded rows of each packed format
     int64_t device_bytes = 0;
@@ -183,10 +196,13 @@ int validate_classify(const lnbnn_index *ix, const void *queries, int dtype, con
 int mode_fmt(int mode);
 bool is_fp8_mode(int mode);
 int index_fmt(const lnbnn_index *ix, int mode);   // mode_fmt, with the 160-element INT8 tiles where they apply
-int make_plan(lnbnn_index *ix, int mode, int kp, int64_t q_cap, int forced_variant, Plan *out);
-int64_t part_elems(const Plan &p, int64_t q_cap);
-// Elements of part_d / part_i a plan needs (the lists, or the original NBNN
-// mode's per-class minima, whichever is larger).
+// Plan for a batch of n_q queries in buffers of q_cap.  max_lists: most
+// partial lists per query of a shared-list plan (1: no block is split).
+int make_plan(lnbnn_index *ix, int mode, int k, int64_t q_cap, int64_t n_q, int max_lists, Plan *out);
+// Elements of part_d / part_i the plan's batch needs (the lists, or the
+// original NBNN mode's per-class minima), and the most that any batch of up to
+// q_cap queries planned alike needs.
+int64_t batch_elems(const lnbnn_index *ix, const Plan &p, int64_t q_cap);
 int64_t work_elems(const lnbnn_index *ix, const Plan &p, int64_t q_cap);
 // Enqueue fill + distance kernel + finish + argmin for one batch (the data
 // pointers come from the batch descriptor io.bd).  When `kev` is not null,

@@ -132,10 +132,9 @@ static int setup_slot(Server *sv, Slot *sl)
     for (int mode = 0; mode < kNumModes; ++mode) {
         if (!(ix->modes & LNBNN_MODE_BIT(mode))) continue;
         for (int k = 1; k <= kmax; ++k) {
-            const int len = dist_list_len(mode, k);
             for (int64_t q = 1024; ; q = std::min(cap, q * 2)) {
                 Plan p;
-                if (make_plan(ix, mode, len, std::min(q, cap), -1, &p) == LNBNN_OK)
+                if (make_plan(ix, mode, k, std::min(q, cap), std::min(q, cap), kMaxLists, &p) == LNBNN_OK)
                     part = std::max(part, work_elems(ix, p, cap));
                 if (q >= cap) break;
             }
@@ -183,18 +182,18 @@ static int launch_slot(Server *sv, Slot *sl)
     }
     const int64_t n_img = (int64_t)sl->batch.size();
     Workspace &ws = sl->ws;
-    *sl->h_bd = BatchDesc{n_q, n_img, ws.q, ws.cls, nullptr, nullptr};
     LN_HIP(hipMemcpyAsync(ws.q, sl->h_q, (size_t)std::max<int64_t>(rb, n_q * rb), hipMemcpyHostToDevice, sl->stream));
     LN_HIP(hipMemcpyAsync(ws.offsets, sl->h_off, (size_t)(n_img + 1) * 8, hipMemcpyHostToDevice, sl->stream));
-    LN_HIP(hipMemcpyAsync(ws.bd, sl->h_bd, sizeof(BatchDesc), hipMemcpyHostToDevice, sl->stream));
-    // one captured sequence per power-of-two batch size, so small batches
-    // get a plan (reference split) that still fills the GPU
+    // planned for the batch's own size within its power-of-two bucket, so
+    // small batches get a split that still fills the GPU
     int64_t bucket = 1024;
     while (bucket < n_q) bucket *= 2;
     bucket = std::min(bucket, sv->max_batch_desc);
     Plan plan;
-    int rc = make_plan(ix, mode, dist_list_len(mode, k), std::max<int64_t>(1, bucket), -1, &plan);
+    int rc = make_plan(ix, mode, k, std::max<int64_t>(1, bucket), n_q, kMaxLists, &plan);
     if (rc) return rc;
+    *sl->h_bd = BatchDesc{n_q, n_img, ws.q, ws.cls, nullptr, nullptr, plan.walk};
+    LN_HIP(hipMemcpyAsync(ws.bd, sl->h_bd, sizeof(BatchDesc), hipMemcpyHostToDevice, sl->stream));
     BatchIO io;
     io.offsets = ws.offsets;
     io.bd = ws.bd;
