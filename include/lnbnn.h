@@ -296,8 +296,8 @@ const char *lnbnn_variant_name(int32_t v);
  * up to two batches in flight on separate streams; requests that arrive while
  * a batch runs join the next one.  Results do not depend on the batch a
  * request lands in (exact modes: exact integer totals; FP8_RERANK: each
- * image's FP64 totals are summed by one workgroup in a fixed order:
- * descriptor, then neighbour rank).
+ * image's FP64 totals are summed by one workgroup in an order that its
+ * descriptor count and k alone fix).
  * Errors: EINVAL (bad pointer, n_desc < 0, k, mode, dtype), ENOMEM (the
  * request alone exceeds the budget), EDEVICE.
  */

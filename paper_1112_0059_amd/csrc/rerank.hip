@@ -8,12 +8,12 @@
 //   k_rerank        per query (one wave): exact FP32 squared distances of the
 //                   candidates, the k+1 nearest by (distance, index), and
 //                   Algorithm 2's per-class updates dist_C - dist_B
-//   k_img_reduce    per image: per-class sums of the updates in descriptor
-//                   order, then neighbour order (FP64), and the argmin
+//   k_img_reduce    per image: per-class sums of the updates (FP64, in an order
+//                   the image's size alone fixes), and the argmin
 //
 // Every step depends only on the image's own descriptors, so an image's
 // result is the same whatever batch it is classified in.
-#include "internal.h"
+#include "wave_select.h"
 
 namespace lnbnn {
 
@@ -126,44 +126,32 @@ __global__ void k_fp8_qprep(const BatchDesc *bd, uint4 *__restrict__ q8, int32_t
     }
 }
 
-static __device__ __forceinline__ bool pair_less(float d0, int i0, float d1, int i1)
-{
-    return d0 < d1 || (d0 == d1 && (uint32_t)i0 < (uint32_t)i1);
-}
-
-// One thread per query: the n_cand best (key, index) pairs over the
-// n_lists sorted candidate lists of kp_stride entries each (together at
-// least n_cand; entries past a list's real rows carry +inf keys and lose).
+// One wave per query: the n_cand best (key, index) pairs over the n_lists
+// sorted candidate lists of kp_stride entries each (together at least n_cand;
+// entries past a list's real rows have index -1).  The lists are taken rank by
+// rank, 64 of them at a time, until a rank adds nothing.  With one thread per
+// query this merge was a chain of n_cand x n_lists dependent loads on a few
+// workgroups: 1.52 ms for 1,999 descriptors of 64 lists, now 45 us.
 __global__ __launch_bounds__(256) void k_cand_merge(RerankArgs a)
 {
+    constexpr int CAP = 192;        // 4 * 32 candidates + 64
+    __shared__ uint2 s_sel[4][CAP];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t n_q = a.bd->n_q;
-    for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < n_q;
-         q += (int64_t)gridDim.x * blockDim.x) {
-        int heads[kMaxLists];
-        bool marked = false;            // a list's last key is NaN: its stage wait gave up
-        for (int l = 0; l < a.n_lists; ++l) {
-            heads[l] = 0;
-            const float last = a.part_d[((int64_t)l * a.q_cap + q) * a.kp_stride + a.kp_stride - 1];
-            marked = marked || __builtin_isnan(last);
+    for (int64_t q = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(wave); q < n_q; q += (int64_t)gridDim.x * 4) {
+        const int64_t base = ((int64_t)min(lane, a.n_lists - 1) * a.q_cap + q) * a.kp_stride;
+        const bool in = lane < a.n_lists;
+        // a list's last key is NaN: its stage wait gave up
+        const bool marked = in && __builtin_isnan(a.part_d[base + a.kp_stride - 1]);
+        if (__builtin_amdgcn_ballot_w64(marked) != 0 && lane == 0) atomicOr(a.status, kStatusWaitGaveUp);
+        WaveSelect<CAP> sel(s_sel[wave], a.n_cand, __builtin_inff());
+        for (int p = 0; p < a.kp_stride; ++p) {
+            const int i = a.part_i[base + p];
+            if (!sel.add(a.part_d[base + p], i, in && i >= 0, lane)) break;
         }
-        if (marked) atomicOr(a.status, kStatusWaitGaveUp);
-        for (int p = 0; p < a.n_cand; ++p) {
-            float bd = __builtin_inff();
-            int bi = -1, bl = 0;
-            for (int l = 0; l < a.n_lists; ++l) {
-                if (heads[l] >= a.kp_stride) continue;
-                const int64_t o = ((int64_t)l * a.q_cap + q) * a.kp_stride + heads[l];
-                const float d = a.part_d[o];
-                const int i = a.part_i[o];
-                if (pair_less(d, i, bd, bi)) {
-                    bd = d;
-                    bi = i;
-                    bl = l;
-                }
-            }
-            heads[bl] += 1;
-            a.cand[q * a.n_cand + p] = bi;
-        }
+        sel.cut(lane);
+        for (int j = lane; j < a.n_cand; j += 64) a.cand[q * a.n_cand + j] = j < sel.n ? (int)sel.buf[j].y : -1;
+        wave_lds_fence();
     }
 }
 
@@ -259,49 +247,75 @@ __global__ __launch_bounds__(256) void k_rerank(RerankArgs a)
     }
 }
 
-// One workgroup per image: totals[c] = sum over the image's descriptors (in
-// order), then over ranks, of the updates of class c; argmin with the lowest
-// class on ties.  Classes with no update stay 0.
-__global__ __launch_bounds__(256) void k_img_reduce(RerankArgs a)
+// One workgroup per image: totals[c] = sum of the updates of class c over the
+// image's descriptors; argmin with the lowest class on ties.  Classes with no
+// update stay 0.
+//
+// A group of G lanes takes a contiguous share of the image's descriptors in
+// order, one lane per neighbour rank (a descriptor updates a class at most
+// once, so the lanes of a group never collide), and adds to sums of its own in
+// LDS; the groups' sums are then added in group order.  The order of every sum
+// depends on the image's descriptor count and k alone, so an image's totals are
+// the same in any batch.  Classes beyond the LDS window take another pass.
+//
+// Before, every thread owned a class and walked all the image's updates: 2.48 ms
+// for eight images of 500-4,000 descriptors (k = 10), one workgroup each, now
+// 32 us.
+template <int G>
+__global__ __launch_bounds__(512) void k_img_reduce(RerankArgs a)
 {
-    constexpr int CHUNK = 1024;
-    __shared__ int s_cls[CHUNK];
-    __shared__ double s_del[CHUNK];
-    __shared__ double s_bv[256];
-    __shared__ int s_bc[256];
-    const int tid = threadIdx.x;
+    constexpr int GROUPS = 512 / G;
+    constexpr int WINDOW = 8192 / GROUPS;           // classes per pass
+    constexpr int AHEAD = 4;                        // descriptors loaded ahead of their sums
+    __shared__ double s_sum[GROUPS][WINDOW];
+    __shared__ double s_bv[512];
+    __shared__ int s_bc[512];
+    const int tid = threadIdx.x, group = tid / G, j = tid % G;
     const int64_t n_img = a.bd->n_img;
     const int k = a.k;
     for (int64_t img = blockIdx.x; img < n_img; img += gridDim.x) {
-        const int64_t r0 = a.offsets[img] * k, r1 = a.offsets[img + 1] * k;
+        const int64_t q0 = a.offsets[img], n = a.offsets[img + 1] - q0;
+        const int64_t share = (n + GROUPS - 1) / GROUPS;
+        const int64_t g0 = q0 + min(n, group * share), g1 = q0 + min(n, (group + 1) * share);
         double best = __builtin_inf();
         int bc = 0x7fffffff;
-        for (int c0 = 0; c0 < a.n_classes; c0 += 256) {
-            const int c = c0 + tid;
-            double sum = 0.0;
-            for (int64_t base = r0; base < r1; base += CHUNK) {
-                const int n = (int)min((int64_t)CHUNK, r1 - base);
-                __syncthreads();
-                for (int i = tid; i < n; i += 256) {
-                    s_cls[i] = a.upd_cls[base + i];
-                    s_del[i] = a.upd_delta[base + i];
+        for (int c0 = 0; c0 < a.n_classes; c0 += WINDOW) {
+            for (int i = tid; i < GROUPS * WINDOW; i += 512) (&s_sum[0][0])[i] = 0.0;
+            __syncthreads();
+            for (int64_t q = g0; q < g1; q += AHEAD) {
+                int c[AHEAD];
+                double d[AHEAD];
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u) {
+                    const bool in = q + u < g1 && j < k;
+                    const int64_t o = (in ? q + u : q0) * k + (in ? j : 0);
+                    const int cls = a.upd_cls[o];
+                    d[u] = a.upd_delta[o];
+                    c[u] = in && cls >= c0 && cls < c0 + WINDOW ? cls - c0 : -1;
                 }
-                __syncthreads();
-                for (int i = 0; i < n; ++i)
-                    if (s_cls[i] == c) sum += s_del[i];
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u) {
+                    if (c[u] >= 0) s_sum[group][c[u]] += d[u];
+                    wave_lds_fence();
+                }
             }
-            if (c < a.n_classes) {
+            __syncthreads();
+            const int c = c0 + tid;
+            if (tid < WINDOW && c < a.n_classes) {
+                double sum = 0.0;
+                for (int g = 0; g < GROUPS; ++g) sum += s_sum[g][tid];
                 a.totals_f64[img * a.n_classes + c] = sum;
                 if (sum < best) {
                     best = sum;
                     bc = c;
                 }
             }
+            __syncthreads();
         }
         s_bv[tid] = best;
         s_bc[tid] = bc;
         __syncthreads();
-        for (int off = 128; off > 0; off >>= 1) {
+        for (int off = 256; off > 0; off >>= 1) {
             if (tid < off) {
                 const double ov = s_bv[tid + off];
                 const int oc = s_bc[tid + off];
@@ -336,7 +350,7 @@ hipError_t launch_fp8_qprep(const BatchDesc *bd, int64_t q_cap, uint4 *q8, int32
 
 hipError_t launch_cand_merge(const RerankArgs &a, int64_t q_cap, hipStream_t s)
 {
-    k_cand_merge<<<grid_for(q_cap, 256, 16384), 256, 0, s>>>(a);
+    k_cand_merge<<<grid_for(q_cap, 4, 65536), 256, 0, s>>>(a);
     return hipGetLastError();
 }
 
@@ -345,7 +359,10 @@ hipError_t launch_rerank(const RerankArgs &a, int64_t q_cap, int64_t img_cap, hi
     k_rerank<<<grid_for(q_cap, 4, 65536), 256, 0, s>>>(a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    k_img_reduce<<<grid_for(img_cap, 1, 16384), 256, 0, s>>>(a);
+    if (a.k <= 16)
+        k_img_reduce<16><<<grid_for(img_cap, 1, 16384), 512, 0, s>>>(a);
+    else
+        k_img_reduce<32><<<grid_for(img_cap, 1, 16384), 512, 0, s>>>(a);
     return hipGetLastError();
 }
 
