@@ -149,6 +149,12 @@ int lnbnn_index_free(lnbnn_index *ix);
 int lnbnn_index_info(const lnbnn_index *ix, int64_t *n_refs, int32_t *n_classes,
                      uint32_t *mode_mask, int64_t *device_bytes);
 
+/* The index's own stream (a hipStream_t), on which calls with stream = NULL
+ * run: an allocator that reuses a device buffer of such a call for work on
+ * other streams must order the reuse after it.  The stream stays valid after
+ * the index is freed.  Errors: EINVAL (NULL argument). */
+int lnbnn_index_stream(const lnbnn_index *ix, void **stream);
+
 /*
  * Classify a batch of query images (Algorithm 2 for every image).
  *

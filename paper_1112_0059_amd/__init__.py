@@ -96,6 +96,7 @@ def load():
                                ctypes.POINTER(P)], ctypes.c_int),
         "lnbnn_index_free": ([P], ctypes.c_int),
         "lnbnn_index_info": ([P, P, P, P, P], ctypes.c_int),
+        "lnbnn_index_stream": ([P, ctypes.POINTER(P)], ctypes.c_int),
         "lnbnn_classify": ([P, P, ctypes.c_int, P, i32, i32, ctypes.c_int, u32, P, P, P, P, P],
                            ctypes.c_int),
         "lnbnn_last_timing": ([P, ctypes.POINTER(lnbnn_timing)], ctypes.c_int),
@@ -142,8 +143,8 @@ def _ptr(x):
     if x is None:
         return None
     if _is_torch(x):
-        return ctypes.c_void_p(x.data_ptr())
-    return x.ctypes.data_as(ctypes.c_void_p)
+        return x.data_ptr()
+    return x.__array_interface__["data"][0]
 
 
 def _stream(x, stream):
@@ -155,12 +156,37 @@ def _stream(x, stream):
     return None
 
 
+def _hold(ix, stream, tensors):
+    """A call whose stream is NULL (torch's default stream) runs on the index's
+    own stream: torch must not hand its device buffers to other work before
+    that stream is done with them."""
+    if stream is not None and stream.value:
+        return
+    import torch
+    if ix.torch_stream is None:
+        s = ctypes.c_void_p()
+        _check(load().lnbnn_index_stream(ix.handle, ctypes.byref(s)))
+        ix.torch_stream = torch.cuda.ExternalStream(s.value, device=tensors[0].device)
+    for t in tensors:
+        if t is not None and _is_torch(t) and t.is_cuda:
+            t.record_stream(ix.torch_stream)
+
+
+_DTYPES = {}      # dtype objects seen -> element type code
+
+
 def _dtype_code(x) -> int:
+    code = _DTYPES.get(x.dtype)
+    if code is not None:
+        return code
     s = str(x.dtype)
     if s.endswith("uint8"):
-        return LNBNN_U8
-    if s.endswith("float32"):
-        return LNBNN_F32
+        code = LNBNN_U8
+    elif s.endswith("float32"):
+        code = LNBNN_F32
+    if code is not None:
+        _DTYPES[x.dtype] = code
+        return code
     raise TypeError(f"descriptors must be uint8 or float32, got {x.dtype}")
 
 
@@ -179,6 +205,7 @@ class Index:
         self.n_classes = n_classes
         self.dtype = dtype
         self.dim = dim
+        self.torch_stream = None      # the index's own stream, for torch's allocator
 
     def free(self):
         if self.handle:
@@ -265,9 +292,12 @@ def lnbnn_classify(ix: Index, queries, img_offsets, k: int, mode: int, flags: in
                if want_totals else None)
         ni = np.empty((n_q, kp), np.int32) if want_neighbours else None
         nd = np.empty((n_q, kp), np.float32) if want_neighbours else None
+    s = _stream(queries, stream)
     _check(load().lnbnn_classify(ix.handle, _ptr(queries), _dtype_code(queries), _ptr(offsets),
                                  n_img, int(k), int(mode), int(flags), _ptr(cls), _ptr(tot),
-                                 _ptr(ni), _ptr(nd), _stream(queries, stream)))
+                                 _ptr(ni), _ptr(nd), s))
+    if dev:
+        _hold(ix, s, (queries, cls, tot, ni, nd))
     return cls, tot, ni, nd
 
 
@@ -284,10 +314,12 @@ def lnbnn_classify_noalloc(ix: Index, queries_dev, img_offsets, k: int, mode: in
     optional), enqueued on torch's current stream (or `stream`)."""
     offsets = np.ascontiguousarray(img_offsets, dtype=np.int64)
     _check_width(ix, queries_dev)
+    s = _stream(queries_dev, stream)
     _check(load().lnbnn_classify_noalloc(
         ix.handle, _ptr(queries_dev), _dtype_code(queries_dev), _ptr(offsets), offsets.shape[0] - 1,
         int(k), int(mode), _ptr(out["class"]), _ptr(out.get("totals")), _ptr(out.get("nbr_idx")),
-        _ptr(out.get("nbr_dist")), _ptr(out.get("status")), _stream(queries_dev, stream)))
+        _ptr(out.get("nbr_dist")), _ptr(out.get("status")), s))
+    _hold(ix, s, (queries_dev, *out.values()))
     return out
 
 

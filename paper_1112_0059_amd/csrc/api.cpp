@@ -80,6 +80,31 @@ static int64_t env_budget()
     return (int64_t)(v * mul);
 }
 
+static std::mutex g_stream_mu;
+static std::map<int, std::vector<hipStream_t>> g_streams;   // device -> streams no index holds
+
+int stream_acquire(int device, hipStream_t *out)
+{
+    {
+        std::lock_guard<std::mutex> lock(g_stream_mu);
+        auto &v = g_streams[device];
+        if (!v.empty()) {
+            *out = v.back();
+            v.pop_back();
+            return LNBNN_OK;
+        }
+    }
+    // a blocking stream stays ordered after work on the NULL stream
+    LN_HIP(hipStreamCreate(out));
+    return LNBNN_OK;
+}
+
+void stream_release(int device, hipStream_t s)
+{
+    std::lock_guard<std::mutex> lock(g_stream_mu);
+    g_streams[device].push_back(s);
+}
+
 static hipError_t dmalloc(void **p, size_t bytes)
 {
     if (fault_injected("alloc")) return hipErrorOutOfMemory;
@@ -112,7 +137,7 @@ int index_fmt(const lnbnn_index *ix, int mode)
 Workspace::~Workspace()
 {
     void *ps[] = {q, offsets, bd, part_d, part_i, totals, totals_f64, cls, nbr_idx, nbr_dist,
-                  q8, qsc, cand, upd_cls, upd_delta, status};
+                  q8, qsc, cand, upd_cls, upd_delta};
     for (void *p : ps)
         if (p) (void)hipFree(p);
     if (h_status) (void)hipHostFree(h_status);
@@ -171,34 +196,36 @@ int32_t wait_spin_limit()
     return (int32_t)std::max(0L, std::min(v, (long)(1 << 30)));
 }
 
-int status_begin(Workspace &ws, hipStream_t s)
+int status_check(Workspace &ws)
 {
-    if (ws.status_dirty) {
-        LN_HIP(launch_set_i32(ws.status, 0, s));
-        ws.status_dirty = false;
-    }
-    return LNBNN_OK;
-}
-
-int status_end(Workspace &ws, hipStream_t s)
-{
-    LN_HIP(hipMemcpyAsync(ws.h_status, ws.status, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    return LNBNN_OK;
-}
-
-int status_check(Workspace &ws, hipStream_t s)
-{
-    const int32_t st = *ws.h_status;
-    if (!(st & kStatusWaitGaveUp)) return LNBNN_OK;
-    // the word accumulates until a failure is reported; clear it now
-    LN_HIP(launch_set_i32(ws.status, 0, s));
-    LN_HIP(hipStreamSynchronize(s));
-    *ws.h_status = 0;
+    if (*(volatile int32_t *)ws.h_status != kStatusWaitGaveUp) return LNBNN_OK;
+    // the word holds a failure until it is reported
+    *(volatile int32_t *)ws.h_status = 0;
     return set_err(LNBNN_EDEVICE,
                    "the distance kernel gave up a bounded wait for an LDS stage (results of the call are invalid)");
 }
 
-void drop_graphs(std::map<std::string, GraphEntry> &graphs)
+int begin_batch(const lnbnn_index *ix, int mode, const BatchDesc &bd, const int64_t *off, BatchDesc *dst,
+                int64_t *dst_off, int32_t *status, hipStream_t s)
+{
+    BeginArgs a;
+    a.bd = bd;
+    a.dst = dst;
+    a.dst_off = dst_off;
+    a.n_off = bd.n_img + 1;
+    a.n_zero = is_fp8_mode(mode) || mode == LNBNN_NBNN_I8 ? 0 : bd.n_img * ix->n_classes;
+    a.status = status;
+    if (a.n_off <= kBeginOffsets) {
+        std::copy(off, off + a.n_off, a.off);
+    } else {
+        LN_HIP(hipMemcpyAsync(dst_off, off, (size_t)a.n_off * 8, hipMemcpyHostToDevice, s));
+        a.n_off = 0;
+    }
+    LN_HIP(launch_begin(a, s));
+    return LNBNN_OK;
+}
+
+void drop_graphs(std::map<GraphKey, GraphEntry> &graphs)
 {
     for (auto &kv : graphs)
         if (kv.second.exec) (void)hipGraphExecDestroy(kv.second.exec);
@@ -207,6 +234,37 @@ void drop_graphs(std::map<std::string, GraphEntry> &graphs)
 
 static void drop_graphs(lnbnn_index *ix) { drop_graphs(ix->graphs); }
 
+// Marks the end of a call's use of the index's workspace on stream s.
+static hipError_t ws_mark(lnbnn_index *ix, hipStream_t s)
+{
+    if (s == ix->own_stream) {
+        ix->ws_use = lnbnn_index::WsUse::own;
+        return hipSuccess;
+    }
+    ix->ws_use = lnbnn_index::WsUse::event;
+    return hipEventRecord(ix->ws_free, s);
+}
+
+// Orders stream s after the last use of the index's workspace.
+static int ws_order(lnbnn_index *ix, hipStream_t s)
+{
+    if (ix->ws_use == lnbnn_index::WsUse::none) return LNBNN_OK;
+    if (ix->ws_use == lnbnn_index::WsUse::own) {
+        if (s == ix->own_stream) return LNBNN_OK;
+        LN_HIP(hipEventRecord(ix->ws_free, ix->own_stream));
+    }
+    LN_HIP(hipStreamWaitEvent(s, ix->ws_free, 0));
+    return LNBNN_OK;
+}
+
+// Waits for the last use of the index's workspace.
+static int ws_sync(lnbnn_index *ix)
+{
+    if (ix->ws_use == lnbnn_index::WsUse::own) LN_HIP(hipStreamSynchronize(ix->own_stream));
+    if (ix->ws_use == lnbnn_index::WsUse::event) LN_HIP(hipEventSynchronize(ix->ws_free));
+    return LNBNN_OK;
+}
+
 // Wait for the work that may still use a workspace before its buffers are
 // replaced: the index's own workspace is last used by the work before the
 // ws_free event; a serving slot's grows only when the slot is created, with
@@ -214,8 +272,7 @@ static void drop_graphs(lnbnn_index *ix) { drop_graphs(ix->graphs); }
 // capturing a graph on a serving stream, and that call is refused then.)
 static int quiesce_ws(lnbnn_index *ix, const Workspace &ws)
 {
-    if (&ws == &ix->ws && ix->ws_used) LN_HIP(hipEventSynchronize(ix->ws_free));
-    return LNBNN_OK;
+    return &ws == &ix->ws ? ws_sync(ix) : LNBNN_OK;
 }
 
 int ensure_ws(lnbnn_index *ix, Workspace &ws, int64_t q_cap, int64_t img_cap, int64_t part, int64_t nbr,
@@ -256,10 +313,9 @@ int ensure_ws(lnbnn_index *ix, Workspace &ws, int64_t q_cap, int64_t img_cap, in
         ws.qbytes_cap = qbytes;
     }
     if (!ws.status) {
-        if ((rc = grow(ix, (void **)&ws.status, 1, 4))) return rc;
         LN_HIP(hipHostMalloc((void **)&ws.h_status, sizeof(int32_t), hipHostMallocDefault));
         *ws.h_status = 0;
-        ws.status_dirty = true;
+        LN_HIP(hipHostGetDevicePointer((void **)&ws.status, ws.h_status, 0));
     }
     ws.q_cap = std::max(ws.q_cap, q_cap);
     return LNBNN_OK;
@@ -313,7 +369,7 @@ static bool variant_serves(int v, int mode, int fmt, int kp)
     return !(variant(v).pl && mode == LNBNN_FP8_RERANK_2K);
 }
 
-static int default_variant(int mode, int fmt, int kp, bool over)
+static int default_variant(int mode, int fmt, int kp, bool over, int64_t n_tiles)
 {
     // Shared lists of tiles wherever the rule allows them.  16x16 blocks (64
     // queries per wave on four query tiles) beat 32x32 pair lists at every batch
@@ -331,6 +387,10 @@ static int default_variant(int mode, int fmt, int kp, bool over)
     // most of its time: one query tile per wave (no spills) beats two, 24.2 ms
     // against 30.1 for 48,000 descriptors over 2.27M references, k = 10
     if (mode == LNBNN_FP8_RERANK_2K) return b <= 40 ? 11 : 0;
+    // an FP8 index of no more tiles than the list holds: every tile would be
+    // recomputed for every query, so short lists of rows are the better ones
+    // (600 references, 64,000 descriptors, k = 5: 379 us against 516)
+    if (b <= 20 && n_tiles <= kp) return 0;
     // 44-64 entries (k = 11..16): one wave per SIMD, 77 ms against 253 on
     // per-half lists for 18,000 descriptors over 15.36M references, k = 16;
     // beyond k = 16 the rule itself is that of per-half lists
@@ -350,12 +410,12 @@ int make_plan(lnbnn_index *ix, int mode, int k, int64_t q_cap, int64_t n_q, int 
         auto it = ix->pinned.find({mode, kpb});
         if (it != ix->pinned.end() && q_cap >= it->second.min_q) tu = it->second.t;
     }
-    const int v = tu.variant >= 0 ? tu.variant : default_variant(mode, fmt, kp, over);
+    const int64_t n_tiles = ix->rows[fmt] / kTileRows;
+    const int v = tu.variant >= 0 ? tu.variant : default_variant(mode, fmt, kp, over, n_tiles);
     if (!variant_serves(v, mode, fmt, kp))
         return set_err(LNBNN_EINVAL, "variant %d cannot serve mode %d with k + 1 = %d", v, mode, kp);
     const Variant var = variant(v);
     const int64_t qb = (int64_t)var.waves * var.qt * var.nt;
-    const int64_t n_tiles = ix->rows[fmt] / kTileRows;
     const int bpc = blocks_per_cu(ix, v, fmt, kpb);
     int64_t resident = (int64_t)ix->cu_count * bpc;
     if (tu.max_workgroups > 0) resident = std::min<int64_t>(resident, tu.max_workgroups);
@@ -482,8 +542,9 @@ int64_t work_elems(const lnbnn_index *ix, const Plan &p, int64_t q_cap)
     // grid, at most 8 rounds of (block, slice) items or one piece more than
     // blocks and workgroups, and at most max_lists per block
     const int64_t n_qb = std::max<int64_t>(1, (q_cap + p.block - 1) / p.block);
+    if (p.max_lists <= 1) return std::max<int64_t>(q_cap, 1) * p.kpb;
     const int64_t rem = std::min<int64_t>(n_qb, p.grid);
-    return (n_qb + std::min<int64_t>(8 * (int64_t)p.grid, rem * p.max_lists)) * p.block * p.kpb;
+    return (n_qb / p.grid * p.grid + std::min<int64_t>(8 * (int64_t)p.grid, rem * p.max_lists)) * p.block * p.kpb;
 }
 
 int enqueue_batch(lnbnn_index *ix, const Plan &p, const BatchIO &io, hipStream_t s, hipEvent_t *kev)
@@ -503,8 +564,6 @@ int enqueue_batch(lnbnn_index *ix, const Plan &p, const BatchIO &io, hipStream_t
         LN_HIP(launch_fp8_qprep(io.bd, io.q_cap, io.q8, io.qsc, s));
     else if (nbnn)
         LN_HIP(launch_fill_i32(io.part_i, 0x7fffffff, io.q_cap, io.q_cap, ix->n_classes, io.bd, s));
-    else
-        LN_HIP(launch_fill_u64(io.totals, io.img_cap * ix->n_classes, io.bd, ix->n_classes, s));
     DistArgs a{};
     a.q = fp8 ? static_cast<const void *>(io.q8) : nullptr;
     a.q_scale = io.qsc;
@@ -554,7 +613,6 @@ int enqueue_batch(lnbnn_index *ix, const Plan &p, const BatchIO &io, hipStream_t
         r.cand = io.cand;
         r.upd_cls = io.upd_cls;
         r.upd_delta = io.upd_delta;
-        r.totals_f64 = io.totals_f64;
         r.status = w->status;
         if (p.pl)
             LN_HIP(launch_refine_fp8(t, r, io.q_cap, s));
@@ -568,9 +626,8 @@ int enqueue_batch(lnbnn_index *ix, const Plan &p, const BatchIO &io, hipStream_t
         n.cls_min = io.part_i;
         n.q_cap = io.q_cap;
         n.n_classes = ix->n_classes;
-        n.totals = io.totals;
         LN_HIP(launch_nbnn_totals(n, io.img_cap, s));
-        LN_HIP(launch_argmin(io.totals, io.bd, io.img_cap, ix->n_classes, s));
+        LN_HIP(launch_argmin(io.bd, io.img_cap, ix->n_classes, s));
     } else {
         FinishArgs f{};
         f.q_shift = p.fmt == FMT_I8 || p.fmt == FMT_I8L ? 128 : 0;
@@ -588,13 +645,12 @@ int enqueue_batch(lnbnn_index *ix, const Plan &p, const BatchIO &io, hipStream_t
         f.q_cap = io.q_cap;
         f.part_d = io.part_d;
         f.part_i = io.part_i;
-        f.totals = io.totals;
         f.status = w->status;
         if (p.pl)
             LN_HIP(launch_refine(p.fmt, t, f, io.q_cap, s));
         else
             LN_HIP(launch_finish(f, io.q_cap, s));
-        LN_HIP(launch_argmin(io.totals, io.bd, io.img_cap, ix->n_classes, s));
+        LN_HIP(launch_argmin(io.bd, io.img_cap, ix->n_classes, s));
     }
     return LNBNN_OK;
 }
@@ -632,6 +688,14 @@ static int free_index_buffers(lnbnn_index *ix)
     for (void *p : ix->retired) (void)hipFree(p);
     ix->retired.clear();
     return LNBNN_OK;
+}
+
+static void free_index_handles(lnbnn_index *ix)
+{
+    for (auto &e : ix->tev)
+        if (e) (void)hipEventDestroy(e);
+    if (ix->ws_free) (void)hipEventDestroy(ix->ws_free);
+    if (ix->own_stream) stream_release(ix->device, ix->own_stream);
 }
 
 // The class-sorted INT8 copy of the index for the original NBNN rule
@@ -777,21 +841,26 @@ extern "C" int lnbnn_build_index(const void *refs, int dtype, int64_t n_refs, in
     ix->modes = mode_mask;
     ix->ws.device = dev;
     LN_HIP(hipDeviceGetAttribute(&ix->cu_count, hipDeviceAttributeMultiprocessorCount, dev));
-    // a blocking stream stays ordered after work on the NULL stream
-    LN_HIP(hipStreamCreate(&ix->own_stream));
-    for (auto &e : ix->tev) LN_HIP(hipEventCreate(&e));
-    LN_HIP(hipEventCreateWithFlags(&ix->ws_free, hipEventDisableTiming));
+    int rc = stream_acquire(dev, &ix->own_stream);
+    if (rc) return rc;
     hipStream_t s = stream ? (hipStream_t)stream : ix->own_stream;
     lnbnn_index *ixp = ix.get();
-
     auto fail = [&](int rc) {
         (void)hipStreamSynchronize(s);
         free_index_buffers(ix.get());
+        free_index_handles(ix.get());
         return rc;
     };
+    for (auto &e : ix->tev) {
+        const hipError_t err = hipEventCreate(&e);
+        if (err != hipSuccess) return fail(hip_err(err, "hipEventCreate"));
+    }
+    {
+        const hipError_t err = hipEventCreateWithFlags(&ix->ws_free, hipEventDisableTiming);
+        if (err != hipSuccess) return fail(hip_err(err, "hipEventCreate"));
+    }
 
     // labels: device copy (and validation when they came as device memory)
-    int rc;
     if ((rc = grow(ixp, (void **)&ix->labels, n_refs, 4))) return fail(rc);
     std::vector<int32_t> hl;           // host copy of device labels
     if (dev_in) {
@@ -901,17 +970,20 @@ extern "C" int lnbnn_index_free(lnbnn_index *ix)
     if (server_pending(ix)) return set_err(LNBNN_EBUSY, "index has pending tickets");
     server_stop(ix);                       // joins the serving threads after their streams drain
     (void)hipSetDevice(ix->device);
-    // the index's own work: classify calls (up to the ws_free event) and
-    // its stream
-    if (ix->ws_used) (void)hipEventSynchronize(ix->ws_free);
+    // the index's own work: the last classify call and its stream
+    (void)ws_sync(ix);
     if (ix->own_stream) (void)hipStreamSynchronize(ix->own_stream);
     drop_graphs(ix);
     free_index_buffers(ix);
-    for (auto &e : ix->tev)
-        if (e) (void)hipEventDestroy(e);
-    if (ix->ws_free) (void)hipEventDestroy(ix->ws_free);
-    if (ix->own_stream) (void)hipStreamDestroy(ix->own_stream);
+    free_index_handles(ix);
     delete ix;
+    return LNBNN_OK;
+}
+
+extern "C" int lnbnn_index_stream(const lnbnn_index *ix, void **stream)
+{
+    if (!ix || !stream) return set_err(LNBNN_EINVAL, "NULL argument");
+    *stream = ix->own_stream;
     return LNBNN_OK;
 }
 
@@ -959,27 +1031,22 @@ int lnbnn::validate_classify(const lnbnn_index *ix, const void *queries, int dty
     return LNBNN_OK;
 }
 
-std::string lnbnn::graph_key(const Plan &p, const BatchIO &io)
+GraphKey lnbnn::graph_key(const Plan &p, const BatchIO &io)
 {
-    // the plan, the capacities, the workspace buffers and the stage-wait
-    // bound (all kernel arguments frozen into the graph); the caller's
-    // queries and outputs travel in the batch descriptor
-    std::ostringstream o;
-    o << wait_spin_limit() << '/' << p.variant << '/' << p.fmt << '/' << p.kpb << '/' << p.n_lists << '/' << p.chunk_tiles << '/'
-      << p.grid << '/' << io.q_cap << '/' << io.img_cap << '/' << io.k << '/' << io.mode << '/' << io.offsets << '/'
-      << io.bd << '/' << io.totals << '/' << io.totals_f64 << '/' << io.part_d << '/' << io.part_i << '/' << io.q8
-      << '/' << io.cand;
-    return o.str();
+    auto at = [](const void *x) { return (int64_t)(uintptr_t)x; };
+    return GraphKey{wait_spin_limit(), p.variant, p.fmt * 1000 + p.kpb, p.n_lists, p.chunk_tiles, p.grid, io.q_cap,
+                    io.img_cap, io.k, io.mode, at(io.offsets), at(io.bd), at(io.part_d), at(io.part_i), at(io.q8),
+                    at(io.cand)};
 }
 
 // Replay (capturing on first use) the launch sequence of a batch.  The
 // caller has made sure that no earlier replay of these graphs is still in
 // flight when an entry is evicted (the workspace's work is ordered on one
 // fence, and eviction waits for it).
-int lnbnn::launch_graph(std::map<std::string, GraphEntry> &graphs, uint64_t &clock, lnbnn_index *ix, const Plan &p,
+int lnbnn::launch_graph(std::map<GraphKey, GraphEntry> &graphs, uint64_t &clock, lnbnn_index *ix, const Plan &p,
                         const BatchIO &io, hipStream_t s)
 {
-    const std::string key = graph_key(p, io);
+    const GraphKey key = graph_key(p, io);
     auto it = graphs.find(key);
     if (it == graphs.end()) {
         if (graphs.size() >= kMaxGraphs) {
@@ -1016,8 +1083,8 @@ int lnbnn::launch_graph(std::map<std::string, GraphEntry> &graphs, uint64_t &clo
 // that image alone (no graph).  With `kev`, the distance-kernel time of every
 // launch is summed.
 static int classify_per_image(lnbnn_index *ix, const void *dq, const int64_t *off, int32_t n_images,
-                              int32_t k, int mode, int32_t *cls, int32_t *nbr_idx, float *nbr_dist, hipStream_t s,
-                              hipEvent_t *kev)
+                              int32_t k, int mode, int32_t *cls, void *totals, int32_t *nbr_idx, float *nbr_dist,
+                              hipStream_t s, hipEvent_t *kev)
 {
     Workspace &ws = ix->ws;
     const int kp = k + 1;
@@ -1038,11 +1105,14 @@ static int classify_per_image(lnbnn_index *ix, const void *dq, const int64_t *of
         bds[m].nbr_idx = nbr_idx ? nbr_idx + off[m] * kp : nullptr;
         bds[m].nbr_dist = nbr_dist ? nbr_dist + off[m] * kp : nullptr;
         bds[m].walk = plans[m].walk;
+        bds[m].totals = static_cast<uint8_t *>(totals) + (int64_t)m * ix->n_classes * 8;
         offs[2 * m] = 0;
         offs[2 * m + 1] = bds[m].n_q;
     }
     LN_HIP(hipMemcpyAsync(ws.bd, bds.data(), n_images * sizeof(BatchDesc), hipMemcpyHostToDevice, s));
     LN_HIP(hipMemcpyAsync(ws.offsets, offs.data(), offs.size() * 8, hipMemcpyHostToDevice, s));
+    if (!is_fp8_mode(mode) && mode != LNBNN_NBNN_I8)
+        LN_HIP(launch_fill_u64(static_cast<unsigned long long *>(totals), (int64_t)n_images * ix->n_classes, s));
     double kms = 0;
     for (int32_t m = 0; m < n_images; ++m) {
         BatchIO io;
@@ -1052,11 +1122,9 @@ static int classify_per_image(lnbnn_index *ix, const void *dq, const int64_t *of
         io.img_cap = 1;
         io.k = k;
         io.mode = mode;
-        io.totals = ws.totals + (int64_t)m * ix->n_classes;
         io.ws = &ws;
         io.part_d = ws.part_d;
         io.part_i = ws.part_i;
-        io.totals_f64 = ws.totals_f64 ? ws.totals_f64 + (int64_t)m * ix->n_classes : nullptr;
         io.q8 = ws.q8;
         io.qsc = ws.qsc;
         io.cand = ws.cand;
@@ -1128,7 +1196,7 @@ extern "C" int lnbnn_classify(lnbnn_index *ix, const void *queries, int dtype, c
     Workspace &ws = ix->ws;
 
     // the shared workspace may still be read by a call on another stream
-    if (ix->ws_used) LN_HIP(hipStreamWaitEvent(s, ix->ws_free, 0));
+    if ((rc = ws_order(ix, s))) return rc;
     // from here on, every exit (errors included) marks the end of this
     // call's use of the workspace on `s`
     struct WsFence {
@@ -1137,9 +1205,7 @@ extern "C" int lnbnn_classify(lnbnn_index *ix, const void *queries, int dtype, c
         bool armed;
         ~WsFence()
         {
-            if (!armed) return;
-            (void)hipEventRecord(ix->ws_free, s);
-            ix->ws_used = true;
+            if (armed) (void)ws_mark(ix, s);
         }
     } fence{ix, s, true};
     const void *dq = queries;
@@ -1150,17 +1216,18 @@ extern "C" int lnbnn_classify(lnbnn_index *ix, const void *queries, int dtype, c
     int32_t *d_cls = dev ? out_class : ws.cls;
     int32_t *d_nbr_i = want_nbr ? (dev ? out_nbr_idx : ws.nbr_idx) : nullptr;
     float *d_nbr_d = want_nbr ? (dev ? out_nbr_dist : ws.nbr_dist) : nullptr;
+    // totals go straight to an aligned device buffer of the caller's
+    void *ws_tot = fp8 ? (void *)ws.totals_f64 : (void *)ws.totals;
+    void *d_tot = dev && out_totals && (uintptr_t)out_totals % 8 == 0 ? out_totals : ws_tot;
 
     hipEvent_t *kev = timed ? ix->tev : nullptr;
     if (timed) LN_HIP(hipEventRecord(ix->tev[2], s));
-    if ((rc = status_begin(ws, s))) return rc;
     if (per_image) {
-        rc = classify_per_image(ix, dq, img_offsets, n_images, k, mode, d_cls, d_nbr_i, d_nbr_d, s, kev);
+        rc = classify_per_image(ix, dq, img_offsets, n_images, k, mode, d_cls, d_tot, d_nbr_i, d_nbr_d, s, kev);
         if (rc) return rc;
     } else {
-        BatchDesc hb{n_q, n_images, dq, d_cls, d_nbr_i, d_nbr_d, plan.walk};
-        LN_HIP(hipMemcpyAsync(ws.bd, &hb, sizeof hb, hipMemcpyHostToDevice, s));
-        LN_HIP(hipMemcpyAsync(ws.offsets, img_offsets, (size_t)(n_images + 1) * 8, hipMemcpyHostToDevice, s));
+        const BatchDesc hb{n_q, n_images, dq, d_cls, d_nbr_i, d_nbr_d, d_tot, plan.walk};
+        if ((rc = begin_batch(ix, mode, hb, img_offsets, ws.bd, ws.offsets, nullptr, s))) return rc;
         BatchIO io;
         io.offsets = ws.offsets;
         io.bd = ws.bd;
@@ -1168,11 +1235,9 @@ extern "C" int lnbnn_classify(lnbnn_index *ix, const void *queries, int dtype, c
         io.img_cap = img_cap;
         io.k = k;
         io.mode = mode;
-        io.totals = ws.totals;
         io.ws = &ws;
         io.part_d = ws.part_d;
         io.part_i = ws.part_i;
-        io.totals_f64 = ws.totals_f64;
         io.q8 = ws.q8;
         io.qsc = ws.qsc;
         io.cand = ws.cand;
@@ -1181,18 +1246,17 @@ extern "C" int lnbnn_classify(lnbnn_index *ix, const void *queries, int dtype, c
         if (direct) {
             if ((rc = enqueue_batch(ix, plan, io, s, kev))) return rc;
         } else {
-            if (ix->graphs.size() >= kMaxGraphs && !ix->graphs.count(graph_key(plan, io)) && ix->ws_used)
-                LN_HIP(hipEventSynchronize(ix->ws_free));   // an eviction: no replay in flight
+            if (ix->graphs.size() >= kMaxGraphs && !ix->graphs.count(graph_key(plan, io)) && (rc = ws_sync(ix)))
+                return rc;                                  // an eviction: no replay in flight
             if ((rc = launch_graph(ix->graphs, ix->graph_clock, ix, plan, io, s))) return rc;
         }
     }
-    if ((rc = status_end(ws, s))) return rc;
     if (timed) LN_HIP(hipEventRecord(ix->tev[3], s));
 
     // outputs
-    if (out_totals)
-        LN_HIP(hipMemcpyAsync(out_totals, fp8 ? (const void *)ws.totals_f64 : (const void *)ws.totals,
-                              (size_t)(n_images * nc * 8), dev ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s));
+    if (out_totals && d_tot != out_totals)
+        LN_HIP(hipMemcpyAsync(out_totals, ws_tot, (size_t)(n_images * nc * 8),
+                              dev ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s));
     if (!dev) {
         LN_HIP(hipMemcpyAsync(out_class, ws.cls, (size_t)n_images * 4, hipMemcpyDeviceToHost, s));
         if (want_nbr) {
@@ -1201,8 +1265,7 @@ extern "C" int lnbnn_classify(lnbnn_index *ix, const void *queries, int dtype, c
         }
     }
     fence.armed = false;
-    LN_HIP(hipEventRecord(ix->ws_free, s));
-    ix->ws_used = true;
+    LN_HIP(ws_mark(ix, s));
     if (!dev) LN_HIP(hipStreamSynchronize(s));
     if (timed) {
         LN_HIP(hipEventSynchronize(ix->tev[3]));
@@ -1220,7 +1283,7 @@ extern "C" int lnbnn_classify(lnbnn_index *ix, const void *queries, int dtype, c
     }
     // a completed sequence (host pointers, or a timed call) reports a
     // bounded wait that gave up
-    if (!dev || timed) return status_check(ws, s);
+    if (!dev || timed) return status_check(ws);
     return LNBNN_OK;
 }
 
@@ -1229,9 +1292,10 @@ extern "C" int lnbnn_sync_status(lnbnn_index *ix)
     if (!ix) return set_err(LNBNN_EINVAL, "NULL index");
     std::lock_guard<std::mutex> lock(ix->mu);
     LN_HIP(hipSetDevice(ix->device));
-    if (!ix->ws_used || !ix->ws.h_status) return LNBNN_OK;
-    LN_HIP(hipEventSynchronize(ix->ws_free));
-    return status_check(ix->ws, ix->own_stream);
+    if (!ix->ws.h_status) return LNBNN_OK;
+    const int rc = ws_sync(ix);
+    if (rc) return rc;
+    return status_check(ix->ws);
 }
 
 extern "C" int lnbnn_last_timing(const lnbnn_index *ix, lnbnn_timing *out)

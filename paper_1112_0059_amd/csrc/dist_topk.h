@@ -581,6 +581,12 @@ static __device__ __forceinline__ void list_insert_med(float v, int idx, float (
     thr = ld[KP - 1];
 }
 
+// Load through the scalar cache (uniform index).
+static __device__ __forceinline__ uint32_t load_uniform(const uint32_t *p, int i)
+{
+    return ((const __attribute__((address_space(4))) uint32_t *)p)[i];
+}
+
 // Insert every key of one tile that beats the list's current KP-th key;
 // gt is the gate threshold that goes with the list's new KP-th key.
 template <class Op, int KP>
@@ -1382,7 +1388,7 @@ void k_dist_topk(DistArgs a)
             }
             auto nbnn_flush = [&]() {
                 if constexpr (Op::kNbnn) {
-                    if (__builtin_isnan(ld[0][KP - 1]) && lane == 0) atomicOr(a.status, kStatusWaitGaveUp);
+                    if (__builtin_isnan(ld[0][KP - 1]) && lane == 0) *a.status = kStatusWaitGaveUp;
 #pragma unroll
                     for (int nt = 0; nt < NT; ++nt) {
                         int key = mk[nt];

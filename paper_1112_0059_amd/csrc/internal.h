@@ -44,6 +44,7 @@ struct BatchDesc {
     int32_t *cls;       // [n_img] argmin class per image
     int32_t *nbr_idx;   // [n_q, k+1] neighbour indices, or null
     float *nbr_dist;    // [n_q, k+1] squared distances, or null
+    void *totals;       // [n_img, n_classes] int64 (exact modes, NBNN) or double (FP8 modes)
     Walk walk;          // how the distance kernel's workgroups split the batch
 };
 
@@ -77,7 +78,7 @@ struct DistArgs {
     // (shared lists) of (key, tile) [slot][queries per block][kp]
     float *part_d;
     int32_t *part_i;
-    int32_t *status;            // bit 0: a bounded stage wait gave up (set by the kernels that
+    int32_t *status;            // a bounded stage wait gave up (set by the kernels that
                                 // read the lists, which carry the mark as a NaN key)
     int32_t spin_limit;         // sleep rounds a stage wait allows before it gives up
     // original NBNN (FMT_I8N): 2 x class + parity of every 32-row tile (the
@@ -101,11 +102,27 @@ struct NbnnArgs {
     const int32_t *cls_min;     // [n_classes][q_cap] minimum key per class and query
     int64_t q_cap;
     int32_t n_classes;
-    unsigned long long *totals; // [n_img, n_classes] int64: sum over the image of the per-class distances
 };
 
-// Bits of the device status word of a launch sequence.
+// Value of a launch sequence's status word once a bounded stage wait gave up.
+// The word may live in pinned host memory, so it is stored, never read or
+// modified, by the kernels that find a mark.
 constexpr int32_t kStatusWaitGaveUp = 1;
+
+// What a batch hands the device, as arguments of one small kernel: its
+// descriptor, the image offsets (where they fit a launch's arguments, else
+// they are copied) and the ranges to clear.
+constexpr int kBeginOffsets = 440;
+struct BeginArgs {
+    BatchDesc bd;
+    BatchDesc *dst;
+    int64_t *dst_off;
+    int64_t n_off;              // offsets in off[] (0: copied otherwise)
+    int64_t n_zero;             // totals to clear
+    int32_t *status;            // cleared if not null
+    int64_t off[kBeginOffsets];
+};
+static_assert(sizeof(BeginArgs) <= 4096, "kernel arguments");
 
 // Result of the FP8 modes: exact re-rank of the candidates and per-image sums.
 struct RerankArgs {
@@ -125,7 +142,6 @@ struct RerankArgs {
     int32_t *cand;              // [q_cap, n_cand]
     int32_t *upd_cls;           // [q_cap, k]: class of the update of rank j, -1 if none
     double *upd_delta;          // [q_cap, k]
-    double *totals_f64;         // [n_img, n_classes]
     int32_t *status;            // set when a list carries a stage-wait mark
 };
 
@@ -146,7 +162,6 @@ struct FinishArgs {
     int64_t q_cap;
     const float *part_d;
     const int32_t *part_i;
-    unsigned long long *totals; // [n_img, n_classes] int64 (two's complement)
     int32_t *status;            // set when a list carries a stage-wait mark
 };
 
@@ -231,12 +246,11 @@ hipError_t launch_dist_topk(int variant, int fmt, int kp, const DistArgs &a, int
                             hipStream_t s);
 int dist_topk_blocks_per_cu(int variant, int fmt, int kp);
 
-hipError_t launch_fill_u64(unsigned long long *p, int64_t n_elems_cap, const BatchDesc *bd,
-                           int32_t n_classes, hipStream_t s);
+hipError_t launch_begin(const BeginArgs &a, hipStream_t s);
+// totals [0, n) = 0 (direct: the pointer, not a batch descriptor)
+hipError_t launch_fill_u64(unsigned long long *p, int64_t n, hipStream_t s);
 hipError_t launch_finish(const FinishArgs &a, int64_t q_cap, hipStream_t s);
-hipError_t launch_argmin(const unsigned long long *totals, const BatchDesc *bd, int64_t img_cap,
-                         int32_t n_classes, hipStream_t s);
-hipError_t launch_set_i32(int32_t *p, int32_t v, hipStream_t s);
+hipError_t launch_argmin(const BatchDesc *bd, int64_t img_cap, int32_t n_classes, hipStream_t s);
 // per reference row: parity of ||r - 128||^2 (u8 rows, dim a multiple of 16)
 hipError_t launch_row_parity(const uint8_t *refs, int64_t n_refs, int dim, uint8_t *out, hipStream_t s);
 hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, int64_t stride, int64_t rows, const BatchDesc *bd,

@@ -213,6 +213,7 @@ __global__ __launch_bounds__(256) void k_finish(FinishArgs a)
 {
     const int64_t n_q = a.bd->n_q;
     const int64_t n_img = a.bd->n_img;
+    unsigned long long *totals = static_cast<unsigned long long *>(a.bd->totals);
     const int kp = a.k + 1;
     for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < n_q;
          q += (int64_t)gridDim.x * blockDim.x) {
@@ -223,7 +224,7 @@ __global__ __launch_bounds__(256) void k_finish(FinishArgs a)
             const float last = a.part_d[((int64_t)l * a.q_cap + q) * a.kp_stride + a.kp_stride - 1];
             marked = marked || __builtin_isnan(last);
         }
-        if (marked) atomicOr(a.status, kStatusWaitGaveUp);
+        if (marked) *a.status = kStatusWaitGaveUp;
         float dd[kMaxKP];
         int ii[kMaxKP];
         for (int p = 0; p < kp; ++p) {
@@ -272,7 +273,7 @@ __global__ __launch_bounds__(256) void k_finish(FinishArgs a)
             for (int jj = 0; jj < j; ++jj) first = first && (lab[jj] != c);
             if (first) {
                 const long long delta = (long long)((int)dd[j] - db);
-                atomicAdd(a.totals + img * a.n_classes + c, (unsigned long long)delta);
+                atomicAdd(totals + img * a.n_classes + c, (unsigned long long)delta);
             }
         }
         int32_t *nbr_idx = a.bd->nbr_idx;
@@ -289,14 +290,14 @@ __global__ __launch_bounds__(256) void k_finish(FinishArgs a)
 // ---------------------------------------------------------------------------
 // K3: argmin over classes, lowest class on ties.  One wave per image.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_argmin(const unsigned long long *__restrict__ totals,
-                                                const BatchDesc *bd, int32_t n_classes)
+__global__ __launch_bounds__(256) void k_argmin(const BatchDesc *bd, int32_t n_classes)
 {
+    const long long *totals = static_cast<const long long *>(bd->totals);
     int32_t *out_class = bd->cls;
     const int lane = threadIdx.x & 63;
     const int64_t n_img = bd->n_img;
     for (int64_t img = blockIdx.x * 4 + (threadIdx.x >> 6); img < n_img; img += (int64_t)gridDim.x * 4) {
-        const long long *t = reinterpret_cast<const long long *>(totals) + img * n_classes;
+        const long long *t = totals + img * n_classes;
         long long best = 0x7fffffffffffffffLL;
         int bc = 0x7fffffff;
         for (int c = lane; c < n_classes; c += 64) {
@@ -318,11 +319,6 @@ __global__ __launch_bounds__(256) void k_argmin(const unsigned long long *__rest
     }
 }
 
-__global__ void k_set_i32(int32_t *p, int32_t v)
-{
-    if (threadIdx.x == 0) *p = v;
-}
-
 // [rows][stride] array: entries [r][0, bd->n_q) set to v.
 __global__ void k_fill_i32(int32_t *p, int32_t v, int64_t stride, int64_t rows, const BatchDesc *bd)
 {
@@ -336,50 +332,69 @@ __global__ void k_fill_i32(int32_t *p, int32_t v, int64_t stride, int64_t rows, 
 // Original NBNN totals (Algorithm 1): totals[img][C] = sum over the image's
 // descriptors d of ||d - NN_C(d)||^2.  cls_min holds the smallest INT8 key
 // of every (class, query); the squared distance is that key plus
-// ||q - 128||^2.  One workgroup per image: each wave takes every 4th class
-// and sums its keys over the image's queries (lanes over queries, 64-bit
-// sums, exact); the norms are summed once per image.
+// ||q - 128||^2.  A workgroup takes 32 classes of an image: each wave every 4th
+// of them, lanes over the image's queries (64-bit sums, exact), four loads in
+// flight; the norms are summed by each workgroup again, which reads 128 bytes
+// per query next to the classes' 128.  One workgroup per image left 8 images on
+// 8 CUs.
 // ---------------------------------------------------------------------------
+constexpr int kTotalsClasses = 32;
+
 __global__ __launch_bounds__(256) void k_nbnn_totals(NbnnArgs a)
 {
     __shared__ long long s_nrm[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t n_img = a.bd->n_img;
     const uint8_t *qb = static_cast<const uint8_t *>(a.bd->q);
-    for (int64_t img = blockIdx.x; img < n_img; img += gridDim.x) {
+    unsigned long long *totals = static_cast<unsigned long long *>(a.bd->totals);
+    const int groups = (a.n_classes + kTotalsClasses - 1) / kTotalsClasses;
+    for (int64_t u = blockIdx.x; u < n_img * groups; u += gridDim.x) {
+        const int64_t img = u / groups;
+        const int c0 = (int)(u - img * groups) * kTotalsClasses, c1 = min(c0 + kTotalsClasses, a.n_classes);
         const int64_t q0 = a.offsets[img], q1 = a.offsets[img + 1];
         long long nrm = 0;
-        for (int64_t q = q0 + tid; q < q1; q += 256) {
-            const uint4 *qr = reinterpret_cast<const uint4 *>(qb + q * kDim);
-            for (int c = 0; c < kDim / 16; ++c) {
-                const uint4 v = qr[c];
-                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-                for (int i = 0; i < 4; ++i)
-                    for (int b = 0; b < 4; ++b) {
-                        const int32_t x = (int32_t)((w[i] >> (8 * b)) & 0xffu) - 128;
-                        nrm += x * x;
-                    }
-            }
+        // eight lanes per query, one 16-byte chunk each
+        for (int64_t i = q0 * 8 + tid; i < q1 * 8; i += 256) {
+            const uint4 v = reinterpret_cast<const uint4 *>(qb)[i];
+            const uint32_t w[4] = {v.x ^ 0x80808080u, v.y ^ 0x80808080u, v.z ^ 0x80808080u, v.w ^ 0x80808080u};
+            int32_t sq = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) sq = __builtin_amdgcn_sdot4((int)w[j], (int)w[j], sq, false);
+            nrm += sq;
         }
         for (int off = 32; off > 0; off >>= 1) nrm += __shfl_xor(nrm, off);
         if (lane == 0) s_nrm[wave] = nrm;
         __syncthreads();
         nrm = s_nrm[0] + s_nrm[1] + s_nrm[2] + s_nrm[3];
-        for (int c = wave; c < a.n_classes; c += 4) {
+        for (int c = c0 + wave; c < c1; c += 4) {
             const int32_t *m = a.cls_min + (int64_t)c * a.q_cap;
             long long sum = 0;
-            for (int64_t q = q0 + lane; q < q1; q += 64) sum += m[q];
+            for (int64_t q = q0 + lane; q < q1; q += 256) {
+                int32_t x[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) x[j] = q + 64 * j < q1 ? m[q + 64 * j] : 0;
+                sum += (long long)x[0] + x[1] + x[2] + x[3];
+            }
             for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
-            if (lane == 0) a.totals[img * a.n_classes + c] = (unsigned long long)(sum + nrm);
+            if (lane == 0) totals[img * a.n_classes + c] = (unsigned long long)(sum + nrm);
         }
         __syncthreads();
     }
 }
 
-__global__ void k_fill_u64(unsigned long long *p, const BatchDesc *bd, int32_t n_classes, int64_t cap)
+__global__ __launch_bounds__(256) void k_begin(BeginArgs a)
 {
-    int64_t n = bd->n_img * (int64_t)n_classes;
-    if (n > cap) n = cap;
+    if (blockIdx.x == 0) {
+        if (threadIdx.x == 0) *a.dst = a.bd;
+        if (threadIdx.x == 0 && a.status) *a.status = 0;
+        for (int64_t i = threadIdx.x; i < a.n_off; i += 256) a.dst_off[i] = a.off[i];
+    }
+    unsigned long long *t = static_cast<unsigned long long *>(a.bd.totals);
+    for (int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x; i < a.n_zero; i += (int64_t)gridDim.x * 256) t[i] = 0ull;
+}
+
+__global__ void k_fill_u64(unsigned long long *p, int64_t n)
+{
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         p[i] = 0ull;
 }
@@ -581,10 +596,15 @@ hipError_t launch_parity_perm(const uint8_t *par, int64_t n_refs, const int32_t 
     return hipGetLastError();
 }
 
-hipError_t launch_fill_u64(unsigned long long *p, int64_t cap, const BatchDesc *bd, int32_t n_classes,
-                           hipStream_t s)
+hipError_t launch_begin(const BeginArgs &a, hipStream_t s)
 {
-    k_fill_u64<<<grid_for(cap, 256, 4096), 256, 0, s>>>(p, bd, n_classes, cap);
+    k_begin<<<grid_for(a.n_zero, 256, 1024), 256, 0, s>>>(a);
+    return hipGetLastError();
+}
+
+hipError_t launch_fill_u64(unsigned long long *p, int64_t n, hipStream_t s)
+{
+    k_fill_u64<<<grid_for(n, 256, 4096), 256, 0, s>>>(p, n);
     return hipGetLastError();
 }
 
@@ -594,10 +614,9 @@ hipError_t launch_finish(const FinishArgs &a, int64_t q_cap, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_argmin(const unsigned long long *totals, const BatchDesc *bd, int64_t img_cap,
-                         int32_t n_classes, hipStream_t s)
+hipError_t launch_argmin(const BatchDesc *bd, int64_t img_cap, int32_t n_classes, hipStream_t s)
 {
-    k_argmin<<<grid_for(img_cap, 4, 16384), 256, 0, s>>>(totals, bd, n_classes);
+    k_argmin<<<grid_for(img_cap, 4, 16384), 256, 0, s>>>(bd, n_classes);
     return hipGetLastError();
 }
 
@@ -611,21 +630,14 @@ hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, int64_t stride, int
 
 hipError_t launch_nbnn_totals(const NbnnArgs &a, int64_t img_cap, hipStream_t s)
 {
-    k_nbnn_totals<<<grid_for(img_cap, 1, 16384), 256, 0, s>>>(a);
+    const int64_t groups = (a.n_classes + kTotalsClasses - 1) / kTotalsClasses;
+    k_nbnn_totals<<<grid_for(img_cap * groups, 1, 16384), 256, 0, s>>>(a);
     return hipGetLastError();
 }
 
-// A one-word store as a kernel (a fill node, not a memset node, when the
-// sequence is captured in a graph).
 hipError_t launch_row_parity(const uint8_t *refs, int64_t n_refs, int dim, uint8_t *out, hipStream_t s)
 {
     k_row_parity<<<grid_for(n_refs * 16, 256, 65536), 256, 0, s>>>(refs, n_refs, dim, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_set_i32(int32_t *p, int32_t v, hipStream_t s)
-{
-    k_set_i32<<<1, 64, 0, s>>>(p, v);
     return hipGetLastError();
 }
 

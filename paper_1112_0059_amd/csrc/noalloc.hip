@@ -90,6 +90,7 @@ extern "C" int lnbnn_classify_noalloc(lnbnn_index *ix, const void *queries_dev, 
     // measure, then carve
     Workspace ws;   // a view of the scratch array: owns nothing
     BatchIO io;
+    void *d_tot = nullptr;
     for (int pass = 0; pass < 2; ++pass) {
         Carve c{pass ? base : nullptr};
         BatchDesc *bd = c.take<BatchDesc>(1);
@@ -138,8 +139,7 @@ extern "C" int lnbnn_classify_noalloc(lnbnn_index *ix, const void *queries_dev, 
         io.img_cap = n_images;
         io.k = k;
         io.mode = mode;
-        io.totals = totals;
-        io.totals_f64 = totals_f64;
+        d_tot = fp8 ? (void *)totals_f64 : (void *)totals;
         io.part_d = part_d;
         io.part_i = part_i;
         io.q8 = q8;
@@ -149,14 +149,9 @@ extern "C" int lnbnn_classify_noalloc(lnbnn_index *ix, const void *queries_dev, 
         io.upd_delta = upd_delta;
     }
     const BatchDesc hb{n_q, n_images, queries_dev, out_class_dev, out_nbr_idx_dev, out_nbr_dist_dev,
-                       plan.walk};
-    int result = LNBNN_OK;
-    hipError_t e = hipMemcpyAsync(const_cast<BatchDesc *>(io.bd), &hb, sizeof hb, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(const_cast<int64_t *>(io.offsets), img_offsets, (size_t)(n_images + 1) * 8,
-                           hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = launch_set_i32(ws.status, 0, s);
-    if (e != hipSuccess) result = hip_err(e, "classify_noalloc setup");
+                       d_tot, plan.walk};
+    int result = begin_batch(ix, mode, hb, img_offsets, const_cast<BatchDesc *>(io.bd),
+                             const_cast<int64_t *>(io.offsets), ws.status, s);
     if (!result) result = enqueue_batch(ix, plan, io, s, nullptr);
     // the view must not free the scratch array
     ws.status = nullptr;

@@ -8,33 +8,141 @@
 //   k_refine<OpFP8>   the same up to the FP8 candidates (the 4k best rows), for
 //                     the exact re-rank in rerank.hip
 //
-// The tiles are recomputed with the instruction and the operand order of the
-// 32x32 distance kernels, so an FP8 key has the same bits there and here; the
-// keys of the exact formats are exact integers anyway.
+// A wave recomputes two tiles per step, one row per lane.  INT8 and 16-bit rows
+// are dotted with the query on the vector units (v_dot4 / v_dot2; the query sits
+// in scalar registers): their keys are exact integers in any order.  An FP8 key
+// must have the bits the 32x32 distance kernels gave it, so it comes from their
+// instruction and operand order, with the query in every column of the block.
 //
-// What bounds it: reading n_need tiles (4-8 KB each) per query, mostly from L2
-// and the infinity cache.  The 63 other columns of each output block are
-// wasted, which costs nothing next to the reads.  Two tiles are computed per
-// step, so that their 64 rows fill the 64 lanes, one row each.
+// What bounds it: reading n_need tiles (4-8 KB each) per query from L2 and the
+// infinity cache, and the instructions of the selection.
 #include "dist_topk.h"
 #include "wave_select.h"
 
 namespace lnbnn {
 
-// One tile's accumulators with the query in every column.
+// The query as the row arithmetic of its format wants it, and one row's key
+// part per lane.
 template <class Op>
-static __device__ __forceinline__ typename Op::acc_t tile_values(const RefineArgs &r, int64_t tile,
-                                                                 const uint4 (&b)[Op::kSteps][Op::kBU], int sb, int lane,
-                                                                 int h)
-{
-    TileRegs<Op> t;
-    tile_load<Op>(r.frag + tile * (Op::kSteps * Op::kAU * 64), reinterpret_cast<const float4 *>(r.seed) + tile * 8,
-                  r.row_scale + (Op::kScaled ? tile * kTileRows : 0), lane, h, t);
-    typename Op::acc_t acc = __builtin_bit_cast(typename Op::acc_t, t.sd);
+struct RowDot;
+
+// INT8: D = seed + sum of s * u in 32-bit integers, u = 127 - q as in load_b.
+template <int S, int FMT>
+struct RowDot<OpI8T<S, FMT>> {
+    using Op = OpI8T<S, FMT>;
+    uint32_t u[8 * S];
+    __device__ __forceinline__ RowDot(const RefineArgs &, const void *q_src, int64_t q, int, int)
+    {
+        const uint32_t *p = reinterpret_cast<const uint32_t *>(static_cast<const uint8_t *>(q_src) + q * Op::kRow);
 #pragma unroll
-    for (int s = 0; s < Op::kSteps; ++s) acc = Op::mma(t.av[s], b[s], acc, t.sa, sb);
-    return acc;
-}
+        for (int i = 0; i < 8 * S; ++i) u[i] = load_uniform(p, i) ^ 0x7f7f7f7fu;
+    }
+    __device__ __forceinline__ int rows(const RefineArgs &r, int ta, int tb, int lane, int *row) const
+    {
+        const int tile = lane < 32 ? ta : tb;
+        *row = tile * kTileRows + (lane & 31);
+        const uint4 *f = r.frag + (int64_t)tile * (S * 64) + (lane & 31);
+        uint4 v[2 * S];
+#pragma unroll
+        for (int c = 0; c < 2 * S; ++c) v[c] = f[(c >> 1) * 64 + 32 * (c & 1)];
+        int d = reinterpret_cast<const int32_t *>(r.seed)[*row];
+#pragma unroll
+        for (int c = 0; c < 2 * S; ++c) {
+            d = __builtin_amdgcn_sdot4((int)v[c].x, (int)u[4 * c + 0], d, false);
+            d = __builtin_amdgcn_sdot4((int)v[c].y, (int)u[4 * c + 1], d, false);
+            d = __builtin_amdgcn_sdot4((int)v[c].z, (int)u[4 * c + 2], d, false);
+            d = __builtin_amdgcn_sdot4((int)v[c].w, (int)u[4 * c + 3], d, false);
+        }
+        return d;
+    }
+};
+
+// 16-bit formats: d' = seed + sum of r * (-2 q) in FP32, exact integers.
+template <class O>
+struct RowDot16 {
+    uint32_t u[64];                 // pairs of -2 q in the operand format
+    __device__ __forceinline__ RowDot16(const RefineArgs &, const void *q_src, int64_t q, int, int)
+    {
+        const uint32_t *p = reinterpret_cast<const uint32_t *>(static_cast<const uint8_t *>(q_src) + q * kDim);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const uint4 w = O::cvt8(make_uint2(load_uniform(p, 2 * i), load_uniform(p, 2 * i + 1)), -2.0f);
+            const uint32_t x[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) u[4 * i + j] = __builtin_amdgcn_readfirstlane(x[j]);
+        }
+    }
+    static __device__ __forceinline__ float dot2(uint32_t x, uint32_t y, float c)
+    {
+        if constexpr (O::kFmt == FMT_F16) {
+            typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+            return __builtin_amdgcn_fdot2(__builtin_bit_cast(h2, x), __builtin_bit_cast(h2, y), c, false);
+        } else {
+            typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+            return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(b2, x), __builtin_bit_cast(b2, y), c, false);
+        }
+    }
+    __device__ __forceinline__ float rows(const RefineArgs &r, int ta, int tb, int lane, int *row) const
+    {
+        const int tile = lane < 32 ? ta : tb;
+        *row = tile * kTileRows + (lane & 31);
+        const uint4 *f = r.frag + (int64_t)tile * (8 * 64) + (lane & 31);
+        float d = r.seed[*row];
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            uint4 v[8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) v[c] = f[(4 * half + (c >> 1)) * 64 + 32 * (c & 1)];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                d = dot2(v[c].x, u[4 * (8 * half + c) + 0], d);
+                d = dot2(v[c].y, u[4 * (8 * half + c) + 1], d);
+                d = dot2(v[c].z, u[4 * (8 * half + c) + 2], d);
+                d = dot2(v[c].w, u[4 * (8 * half + c) + 3], d);
+            }
+        }
+        return d;
+    }
+};
+template <> struct RowDot<OpF16> : RowDot16<OpF16> { using RowDot16<OpF16>::RowDot16; };
+template <> struct RowDot<OpBF16> : RowDot16<OpBF16> { using RowDot16<OpBF16>::RowDot16; };
+
+// FP8: the block instruction of the distance kernels.
+template <>
+struct RowDot<OpFP8> {
+    using Op = OpFP8;
+    uint4 b[Op::kSteps][Op::kBU];
+    int sb;
+    __device__ __forceinline__ RowDot(const RefineArgs &r, const void *q_src, int64_t q, int lane, int)
+    {
+        Op::load_b(q_src, r.q_scale, q, true, lane >> 5, b, sb);
+    }
+    __device__ __forceinline__ f32x16 block(const RefineArgs &r, int64_t tile, int lane) const
+    {
+        TileRegs<Op> t;
+        tile_load<Op>(r.frag + tile * (Op::kSteps * Op::kAU * 64), reinterpret_cast<const float4 *>(r.seed) + tile * 8,
+                      r.row_scale + tile * kTileRows, lane, lane >> 5, t);
+        f32x16 acc = t.sd;
+#pragma unroll
+        for (int s = 0; s < Op::kSteps; ++s) acc = Op::mma(t.av[s], b[s], acc, t.sa, sb);
+        return acc;
+    }
+    __device__ __forceinline__ float rows(const RefineArgs &r, int ta, int tb, int lane, int *row) const
+    {
+        const f32x16 va = block(r, ta, lane), vb = block(r, tb, lane);
+        // lane c + 16 j + 32 h takes register c of tile j
+        const int c = lane & 15;
+        const bool second = lane & 16;
+        float v = va[0];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const float x = second ? vb[i] : va[i];
+            v = c == i ? x : v;
+        }
+        *row = (second ? tb : ta) * kTileRows + 8 * (c >> 2) + 4 * (lane >> 5) + (c & 3);
+        return v;
+    }
+};
 
 // The query's partial lists: slots slot0 .. slot0 + n_lists - 1 (see the walk
 // of k_dist_topk: whole blocks have one, a remaining block one per slice or
@@ -75,9 +183,8 @@ static __device__ __forceinline__ int64_t image_of(const int64_t *offsets, int64
 template <class Op, int CAP>
 static __device__ __forceinline__ void best_rows(const RefineArgs &r, const float *part_d, const int32_t *part_i, int kp,
                                                  const Walk &walk, int64_t q, const void *q_src, WaveSelect<CAP> &sel,
-                                                 int *tiles, int32_t *status, int lane)
+                                                 int *tiles, float *keys, int32_t *status, int lane)
 {
-    const int h = lane >> 5;
     int64_t slot0;
     const int nl = query_slots(r.map, walk, q, &slot0);
     const int64_t ql = q % r.map.block;
@@ -87,7 +194,7 @@ static __device__ __forceinline__ void best_rows(const RefineArgs &r, const floa
     float tau = __builtin_inff();
     bool marked = false;            // a list's last key is NaN: its stage wait gave up
     for (int l = lane; l < nl; l += 64) marked |= __builtin_isnan(part_d[((slot0 + l) * r.map.block + ql) * kp + kp - 1]);
-    if (__builtin_amdgcn_ballot_w64(marked) != 0 && lane == 0) atomicOr(status, kStatusWaitGaveUp);
+    if (__builtin_amdgcn_ballot_w64(marked) != 0 && lane == 0) *status = kStatusWaitGaveUp;
     if (nl == 1) {
         const int64_t base = (slot0 * r.map.block + ql) * kp;
         const bool in = lane < r.n_need;
@@ -106,89 +213,133 @@ static __device__ __forceinline__ void best_rows(const RefineArgs &r, const floa
                 const int l = l0 + lane;
                 const int64_t o = ((slot0 + min(l, nl - 1)) * r.map.block + ql) * kp + p;
                 const int t = part_i[o];
-                more |= sel.add(part_d[o], t, l < nl && t >= 0, lane);
+                more |= sel.add(pair_of(part_d[o], t), l < nl && t >= 0, lane);
             }
             if (!more) break;
+            if (p == 0 && sel.n >= sel.need) sel.cut(lane);   // a bound for the other ranks
         }
         sel.cut(lane);
         n_tiles = sel.n;
-        if (lane < n_tiles) tiles[lane] = (int)sel.buf[lane].y;
-        if (n_tiles == r.n_need) tau = __builtin_bit_cast(float, sel.buf[n_tiles - 1].x);
+        if (lane < n_tiles) tiles[lane] = pair_index(sel.buf[lane]);
+        if (n_tiles == r.n_need) tau = pair_key(sel.buf[n_tiles - 1]);
         wave_lds_fence();
     }
     // their rows: n_need tiles hold a row of key <= tau each, so if no more rows
     // than that are needed, no row above tau is
-    sel = WaveSelect<CAP>(sel.buf, need_rows,
-                          n_tiles == r.n_need && need_rows <= r.n_need && !__builtin_isnan(tau) ? tau : __builtin_inff());
-    uint4 b[Op::kSteps][Op::kBU];
-    int sb;
-    Op::load_b(q_src, r.q_scale, q, true, h, b, sb);
-    for (int t = 0; t < n_tiles; t += 2) {
+    const bool bounded = n_tiles == r.n_need && need_rows <= r.n_need && !__builtin_isnan(tau);
+    sel = WaveSelect<CAP>(sel.buf, need_rows, bounded ? pair_of(tau, 0x7fffffff) : ~0ull);
+    const RowDot<Op> dot(r, q_src, q, lane, 0);
+    // the 64 rows of tiles t and t + 1, one per lane; +inf where there is none
+    auto rows = [&](int t, int *row) -> float {
         const int ta = __builtin_amdgcn_readfirstlane(tiles[t]);
         const int tb = __builtin_amdgcn_readfirstlane(tiles[min(t + 1, n_tiles - 1)]);
-        const typename Op::acc_t va = tile_values<Op>(r, ta, b, sb, lane, h);
-        const typename Op::acc_t vb = tile_values<Op>(r, tb, b, sb, lane, h);
-        // lane c + 16 j + 32 h takes register c of tile j
-        const int c = lane & 15;
-        const bool second = lane & 16;
-        typename Op::gate_t v = va[0];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const typename Op::gate_t x = second ? vb[i] : va[i];
-            v = c == i ? x : v;
-        }
-        const int tile = second ? tb : ta;
-        const int row = tile * kTileRows + 8 * (c >> 2) + 4 * h + (c & 3);
+        const typename Op::gate_t v = dot.rows(r, ta, tb, lane, row);
+        const bool second = Op::kScaled ? lane & 16 : lane & 32;
+        const int par = Op::kParity && (second ? tb : ta) >= r.odd_tile0;
         const bool real = Op::kParity ? v < (typename Op::gate_t)(1 << 29) : (float)v < __builtin_inff();
-        sel.add(Op::tile_key(v, Op::kParity && tile >= r.odd_tile0), row, real && (!second || t + 1 < n_tiles), lane);
+        return real && (!second || t + 1 < n_tiles) ? Op::tile_key(v, par) : __builtin_inff();
+    };
+    if (!bounded && n_tiles > 4 && need_rows <= 48) {
+        // A small index (fewer tiles than needed) gives no bound, and then every
+        // row would go through the buffer.  The need-th smallest of the 64
+        // lanes' smallest keys bounds the rows' (64 groups of rows, each with a
+        // row no larger).
+        float low = __builtin_inff();
+        for (int t = 0; t < n_tiles; t += 2) {
+            int row;
+            const float key = rows(t, &row);
+            keys[t * 32 + lane] = key;
+            low = __builtin_fminf(low, key);
+        }
+        sel.add(pair_of(low, lane), low < __builtin_inff(), lane);
+        sel.cut(lane);
+        sel = WaveSelect<CAP>(sel.buf, need_rows, sel.bound == ~0ull ? ~0ull : pair_of(pair_key(sel.bound), 0x7fffffff));
+        wave_lds_fence();
+        for (int t = 0; t < n_tiles; t += 2) {
+            const float key = keys[t * 32 + lane];
+            const bool second = Op::kScaled ? lane & 16 : lane & 32;
+            const int in = Op::kScaled ? 8 * ((lane & 15) >> 2) + 4 * (lane >> 5) + (lane & 3) : lane & 31;
+            sel.add(pair_of(key, tiles[min(t + (second ? 1 : 0), n_tiles - 1)] * kTileRows + in), key < __builtin_inff(), lane);
+        }
+    } else {
+        for (int t = 0; t < n_tiles; t += 2) {
+            int row;
+            const float key = rows(t, &row);
+            sel.add(pair_of(key, row), key < __builtin_inff(), lane);
+        }
     }
     sel.cut(lane);
 }
 
-// Exact formats: neighbours, background distance and class updates of one query
-// per wave.  Exact integers are added with 64-bit atomics, so totals do not
-// depend on the order of the atomics.
+// Exact formats: neighbours, background distance and class updates, one query
+// at a time per wave.  Exact integers are added, so totals do not depend on the
+// order of the additions.
+//
+// Neighbouring queries belong to the same image, so with one atomic per update
+// they wait for each other at the same few totals: 144,000 descriptors of two
+// classes took 1.15 ms, 0.82 ms with the queries dealt from distant images.  So
+// where a wave has several queries (n_run consecutive ones) and the classes fit
+// its LDS table, it sums an image's updates there and adds the sums when the
+// image ends.
+constexpr int kTableClasses = 256;
+
 template <class Op>
 __global__ __launch_bounds__(256) void k_refine(RefineArgs r, FinishArgs a)
 {
     constexpr int CAP = 128;        // kMaxKP + 64 or more
-    __shared__ uint2 s_sel[4][CAP];
+    __shared__ uint64_t s_sel[4][WaveSelect<CAP>::kSize];
     __shared__ int s_tiles[4][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    __shared__ float s_keys[4][34 * kTileRows];
+    __shared__ long long s_table[4][kTableClasses];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t n_q = a.bd->n_q, n_img = a.bd->n_img;
     const Walk walk = a.bd->walk;
     const int kp = a.k + 1;
+    unsigned long long *totals = static_cast<unsigned long long *>(a.bd->totals);
     int32_t *nbr_idx = a.bd->nbr_idx;
     float *nbr_dist = a.bd->nbr_dist;
-    // Neighbouring queries belong to the same image: with few classes their
-    // atomics all go to the same totals and wait for each other, so workgroups
-    // take groups of four queries from `spread` distant parts of the batch in
-    // turn (two classes, 144,000 descriptors: 1.15 -> 0.82 ms).  With many
-    // classes the totals are many, and neighbours, which share tiles, are better
-    // kept together (256 classes, 288,000 descriptors: 1.96 ms, spread 2.59 ms).
-    const int64_t spread = max(1, 64 / a.n_classes);
-    const int64_t part = ((n_q + 3) / 4 + spread - 1) / spread;
-    for (int64_t u = blockIdx.x; u < part * spread; u += gridDim.x) {
-        const int64_t q = ((u % spread) * part + u / spread) * 4 + __builtin_amdgcn_readfirstlane(wave);
-        if (q >= n_q) continue;
-        WaveSelect<CAP> sel(s_sel[wave], kp, __builtin_inff());
-        best_rows<Op, CAP>(r, a.part_d, a.part_i, a.kp_stride, walk, q, a.bd->q, sel, s_tiles[wave], a.status, lane);
+    const int64_t n_waves = (int64_t)gridDim.x * 4;
+    const int64_t n_run = (n_q + n_waves - 1) / n_waves;
+    const bool table = n_run > 1 && a.n_classes <= kTableClasses;
+    long long *tab = s_table[wave];
+    if (table)
+        for (int c = lane; c < a.n_classes; c += 64) tab[c] = 0;
+    int64_t img = -1, img_end = 0;  // image of the last query, and the query it ends before
+    auto flush = [&]() {
+        wave_lds_fence();
+        for (int c = lane; c < a.n_classes; c += 64) {
+            const long long v = tab[c];
+            if (v != 0) atomicAdd(totals + img * a.n_classes + c, (unsigned long long)v);
+            tab[c] = 0;
+        }
+        wave_lds_fence();
+    };
+    const int64_t q0 = ((int64_t)blockIdx.x * 4 + wave) * n_run, q1 = min(q0 + n_run, n_q);
+    for (int64_t q = q0; q < q1; ++q) {
+        WaveSelect<CAP> sel(s_sel[wave], kp, ~0ull);
+        best_rows<Op, CAP>(r, a.part_d, a.part_i, a.kp_stride, walk, q, a.bd->q, sel, s_tiles[wave], s_keys[wave], a.status, lane);
         // rank `lane` of the list; fewer than k + 1 rows only after a stage wait gave up
         const bool have = lane < sel.n && lane < kp;
-        const uint2 e = sel.buf[have ? lane : 0];
-        const float key = __builtin_bit_cast(float, e.x);
+        const uint64_t e = sel.buf[have ? lane : 0];
+        const float key = pair_key(e);
         int idx = -1;
-        if (have) idx = a.perm ? a.perm[e.y] : (int)e.y;
+        if (have) idx = a.perm ? a.perm[pair_index(e)] : pair_index(e);
         const int lab = lane < a.k && idx >= 0 ? a.labels[idx] : -1;
         const int db = __shfl((int)key, a.k);
-        bool first = lab >= 0;
+        bool first = lab >= 0 && sel.n == kp;
         for (int j = 0; j < a.k; ++j) {
             const int before = __builtin_amdgcn_readlane(lab, j);
             if (j < lane && before == lab) first = false;
         }
-        const int64_t img = image_of(a.offsets, n_img, q, lane);
-        if (first && sel.n == kp)
-            atomicAdd(a.totals + img * a.n_classes + lab, (unsigned long long)(long long)((int)key - db));
+        if (q >= img_end) {
+            if (table && img >= 0) flush();
+            img = image_of(a.offsets, n_img, q, lane);
+            img_end = a.offsets[img + 1];
+        }
+        const long long delta = (int)key - db;
+        // the updates of one query are of different classes
+        if (first && table) tab[lab] += delta;
+        if (first && !table) atomicAdd(totals + img * a.n_classes + lab, (unsigned long long)delta);
         if (nbr_idx) {
             // ||q - shift||^2 turns the key back into the squared distance
             uint32_t qq = 0;
@@ -207,28 +358,32 @@ __global__ __launch_bounds__(256) void k_refine(RefineArgs r, FinishArgs a)
         }
         wave_lds_fence();
     }
+    if (table && img >= 0) flush();
 }
 
 // FP8: the n_cand best rows by (key, row), one query per wave.
 __global__ __launch_bounds__(256) void k_refine_fp8(RefineArgs r, RerankArgs a)
 {
     constexpr int CAP = 192;        // 4 * 32 candidates + 64
-    __shared__ uint2 s_sel[4][CAP];
+    __shared__ uint64_t s_sel[4][WaveSelect<CAP>::kSize];
     __shared__ int s_tiles[4][64];
+    __shared__ float s_keys[4][48 * kTileRows];     // lists of up to 48 tiles (k <= 12) take the bounded pass
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t n_q = a.bd->n_q;
     const Walk walk = a.bd->walk;
     for (int64_t q = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(wave); q < n_q; q += (int64_t)gridDim.x * 4) {
-        WaveSelect<CAP> sel(s_sel[wave], a.n_cand, __builtin_inff());
-        best_rows<OpFP8, CAP>(r, a.part_d, a.part_i, a.kp_stride, walk, q, r.q, sel, s_tiles[wave], a.status, lane);
-        for (int j = lane; j < a.n_cand; j += 64) a.cand[q * a.n_cand + j] = j < sel.n ? (int)sel.buf[j].y : -1;
+        WaveSelect<CAP> sel(s_sel[wave], a.n_cand, ~0ull);
+        best_rows<OpFP8, CAP>(r, a.part_d, a.part_i, a.kp_stride, walk, q, r.q, sel, s_tiles[wave], s_keys[wave], a.status, lane);
+        for (int j = lane; j < a.n_cand; j += 64) a.cand[q * a.n_cand + j] = j < sel.n ? pair_index(sel.buf[j]) : -1;
         wave_lds_fence();
     }
 }
 
 hipError_t launch_refine(int fmt, const RefineArgs &r, const FinishArgs &a, int64_t q_cap, hipStream_t s)
 {
-    const int grid = grid_for(q_cap, 4, 65536);
+    // one query per wave up to 2,048 (nothing gains on the shortest path
+    // there), then at least four, on at most 2,048 workgroups (8 per CU)
+    const int grid = grid_for(q_cap, q_cap <= 2048 ? 4 : 16, 2048);
     switch (fmt) {
     case FMT_F16: k_refine<OpF16><<<grid, 256, 0, s>>>(r, a); break;
     case FMT_BF16: k_refine<OpBF16><<<grid, 256, 0, s>>>(r, a); break;

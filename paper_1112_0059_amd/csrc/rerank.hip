@@ -135,7 +135,7 @@ __global__ void k_fp8_qprep(const BatchDesc *bd, uint4 *__restrict__ q8, int32_t
 __global__ __launch_bounds__(256) void k_cand_merge(RerankArgs a)
 {
     constexpr int CAP = 192;        // 4 * 32 candidates + 64
-    __shared__ uint2 s_sel[4][CAP];
+    __shared__ uint64_t s_sel[4][WaveSelect<CAP>::kSize];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t n_q = a.bd->n_q;
     for (int64_t q = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(wave); q < n_q; q += (int64_t)gridDim.x * 4) {
@@ -143,16 +143,21 @@ __global__ __launch_bounds__(256) void k_cand_merge(RerankArgs a)
         const bool in = lane < a.n_lists;
         // a list's last key is NaN: its stage wait gave up
         const bool marked = in && __builtin_isnan(a.part_d[base + a.kp_stride - 1]);
-        if (__builtin_amdgcn_ballot_w64(marked) != 0 && lane == 0) atomicOr(a.status, kStatusWaitGaveUp);
-        WaveSelect<CAP> sel(s_sel[wave], a.n_cand, __builtin_inff());
+        if (__builtin_amdgcn_ballot_w64(marked) != 0 && lane == 0) *a.status = kStatusWaitGaveUp;
+        WaveSelect<CAP> sel(s_sel[wave], a.n_cand, ~0ull);
         for (int p = 0; p < a.kp_stride; ++p) {
             const int i = a.part_i[base + p];
-            if (!sel.add(a.part_d[base + p], i, in && i >= 0, lane)) break;
+            if (!sel.add(pair_of(a.part_d[base + p], i), in && i >= 0, lane)) break;
         }
         sel.cut(lane);
-        for (int j = lane; j < a.n_cand; j += 64) a.cand[q * a.n_cand + j] = j < sel.n ? (int)sel.buf[j].y : -1;
+        for (int j = lane; j < a.n_cand; j += 64) a.cand[q * a.n_cand + j] = j < sel.n ? pair_index(sel.buf[j]) : -1;
         wave_lds_fence();
     }
+}
+
+static __device__ __forceinline__ bool pair_less(float d0, int i0, float d1, int i1)
+{
+    return d0 < d1 || (d0 == d1 && (uint32_t)i0 < (uint32_t)i1);
 }
 
 // One wave per query.  Lane j holds candidates j and j + 64 (n_cand <= 128)
@@ -272,6 +277,7 @@ __global__ __launch_bounds__(512) void k_img_reduce(RerankArgs a)
     __shared__ int s_bc[512];
     const int tid = threadIdx.x, group = tid / G, j = tid % G;
     const int64_t n_img = a.bd->n_img;
+    double *totals = static_cast<double *>(a.bd->totals);
     const int k = a.k;
     for (int64_t img = blockIdx.x; img < n_img; img += gridDim.x) {
         const int64_t q0 = a.offsets[img], n = a.offsets[img + 1] - q0;
@@ -304,7 +310,7 @@ __global__ __launch_bounds__(512) void k_img_reduce(RerankArgs a)
             if (tid < WINDOW && c < a.n_classes) {
                 double sum = 0.0;
                 for (int g = 0; g < GROUPS; ++g) sum += s_sum[g][tid];
-                a.totals_f64[img * a.n_classes + c] = sum;
+                totals[img * a.n_classes + c] = sum;
                 if (sum < best) {
                     best = sum;
                     bc = c;

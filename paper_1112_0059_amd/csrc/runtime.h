@@ -1,6 +1,7 @@
 // Host runtime shared by the classify path and the serving loop.
 #pragma once
 
+#include <array>
 #include <atomic>
 #include <condition_variable>
 #include <cstdarg>
@@ -57,12 +58,11 @@ struct Workspace {
     int32_t *cand = nullptr;
     int32_t *upd_cls = nullptr;
     double *upd_delta = nullptr;
-    // status word of the launch sequences run on this workspace (bit
-    // kStatusWaitGaveUp: a bounded stage wait gave up), and its pinned host
-    // copy, written after every sequence
+    // status word of the launch sequences run on this workspace
+    // (kStatusWaitGaveUp: a bounded stage wait gave up): pinned host memory,
+    // and its device address
     int32_t *status = nullptr;
     int32_t *h_status = nullptr;
-    bool status_dirty = false;   // freshly allocated: cleared by the next sequence's stream
     int device = 0;
     ~Workspace();
     int64_t bytes() const;
@@ -93,18 +93,12 @@ constexpr int kSplitLists = 256;
 // Everything a batch launch sequence needs; pointers are device pointers.
 struct BatchIO {
     const Workspace *ws = nullptr;      // owner of the buffers below (capacity checks)
-    const void *q = nullptr;
     const int64_t *offsets = nullptr;
     const BatchDesc *bd = nullptr;
     int64_t q_cap = 0;
     int64_t img_cap = 0;
     int32_t k = 0;
     int mode = 0;
-    int32_t *cls = nullptr;
-    unsigned long long *totals = nullptr;
-    double *totals_f64 = nullptr;
-    int32_t *nbr_idx = nullptr;
-    float *nbr_dist = nullptr;
     float *part_d = nullptr;
     int32_t *part_i = nullptr;
     // FP8 mode
@@ -114,6 +108,12 @@ struct BatchIO {
     int32_t *upd_cls = nullptr;
     double *upd_delta = nullptr;
 };
+
+// What a captured sequence depends on: the plan, the capacities, the
+// workspace buffers and the stage-wait bound (all kernel arguments frozen into
+// it).  The caller's queries and outputs, and the batch's own split, travel in
+// the batch descriptor.
+using GraphKey = std::array<int64_t, 16>;
 
 struct GraphEntry {
     hipGraphExec_t exec = nullptr;
@@ -170,7 +170,7 @@ struct lnbnn_index {
     };
     std::map<std::pair<int, int>, Pin> pinned;
     std::map<std::tuple<int, int, int>, int> occupancy;  // (variant, fmt, kpb) -> blocks/CU
-    std::map<std::string, lnbnn::GraphEntry> graphs;
+    std::map<lnbnn::GraphKey, lnbnn::GraphEntry> graphs;
     uint64_t graph_clock = 0;
     // device buffers replaced by a larger one: kept until the index is
     // freed, since work in flight (or a graph being captured elsewhere) may
@@ -180,8 +180,12 @@ struct lnbnn_index {
     lnbnn_timing last_timing{};
     bool has_timing = false;
     hipEvent_t tev[4] = {nullptr, nullptr, nullptr, nullptr};
-    hipEvent_t ws_free = nullptr;   // recorded after the last use of `ws`
-    bool ws_used = false;
+    // Last use of `ws`: on the index's own stream (which outlives it and runs
+    // its work in order, so calls that stay on it need no event), or on a
+    // caller's, marked by the event.
+    enum class WsUse { none, own, event };
+    WsUse ws_use = WsUse::none;
+    hipEvent_t ws_free = nullptr;
 
     lnbnn::Server *server = nullptr;   // owned; created by the first submit, deleted by server_stop
     std::mutex server_mu;
@@ -204,18 +208,20 @@ int make_plan(lnbnn_index *ix, int mode, int k, int64_t q_cap, int64_t n_q, int 
 // q_cap queries planned alike needs.
 int64_t batch_elems(const lnbnn_index *ix, const Plan &p, int64_t q_cap);
 int64_t work_elems(const lnbnn_index *ix, const Plan &p, int64_t q_cap);
-// Enqueue fill + distance kernel + finish + argmin for one batch (the data
+// Hand a batch to the device: its descriptor and offsets into `dst` / `dst_off`
+// and, for the exact modes, its totals cleared.  Precedes enqueue_batch (or the
+// replay of its captured sequence) on the stream.
+int begin_batch(const lnbnn_index *ix, int mode, const BatchDesc &bd, const int64_t *off, BatchDesc *dst,
+                int64_t *dst_off, int32_t *status, hipStream_t s);
+// Enqueue distance kernel + finish + argmin for one batch (the data
 // pointers come from the batch descriptor io.bd).  When `kev` is not null,
 // events 0/1 bracket the distance kernel.
 int enqueue_batch(lnbnn_index *ix, const Plan &p, const BatchIO &io, hipStream_t s, hipEvent_t *kev);
 // Bounded-wait spin limit for the distance kernel (LNBNN_WAIT_SPINS).
 int32_t wait_spin_limit();
-// Status word handling around a launch sequence on workspace `ws`.
-int status_begin(Workspace &ws, hipStream_t s);
-int status_end(Workspace &ws, hipStream_t s);
-// After the sequence has completed: LNBNN_EDEVICE (and the word cleared) if
-// a bounded wait gave up.
-int status_check(Workspace &ws, hipStream_t s);
+// After the workspace's sequences have completed: LNBNN_EDEVICE (and the
+// status word cleared) if a bounded wait gave up.
+int status_check(Workspace &ws);
 // Capacity bucket: the next power of two >= max(n, lo).
 int64_t cap_bucket(int64_t n, int64_t lo);
 int ensure_ws(lnbnn_index *ix, Workspace &ws, int64_t q_cap, int64_t img_cap, int64_t part,
@@ -225,10 +231,17 @@ int fp8_candidates(int k);
 int dist_list_len(int mode, int k);
 int64_t row_bytes(int dtype, int dim);
 
-int launch_graph(std::map<std::string, GraphEntry> &graphs, uint64_t &clock, lnbnn_index *ix, const Plan &p,
+int launch_graph(std::map<GraphKey, GraphEntry> &graphs, uint64_t &clock, lnbnn_index *ix, const Plan &p,
                  const BatchIO &io, hipStream_t s);
-void drop_graphs(std::map<std::string, GraphEntry> &graphs);
-std::string graph_key(const Plan &p, const BatchIO &io);
+void drop_graphs(std::map<GraphKey, GraphEntry> &graphs);
+GraphKey graph_key(const Plan &p, const BatchIO &io);
+
+// Streams of the indexes, kept when an index is freed and given to the next one
+// on the device: as many as indexes ever lived at once.  They are never
+// destroyed, because a caller's allocator may still order a buffer's reuse
+// after the stream an index wrote it on.
+int stream_acquire(int device, hipStream_t *out);
+void stream_release(int device, hipStream_t s);
 
 void server_stop(lnbnn_index *ix);
 bool server_pending(lnbnn_index *ix);

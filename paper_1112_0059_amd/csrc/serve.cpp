@@ -56,7 +56,6 @@ struct Slot {
     Workspace ws;
     uint8_t *h_q = nullptr;        // pinned staging
     int64_t *h_off = nullptr;
-    BatchDesc *h_bd = nullptr;
     int32_t *h_cls = nullptr;
     uint8_t *h_tot = nullptr;
     std::vector<Request *> batch;
@@ -64,7 +63,7 @@ struct Slot {
     int status = LNBNN_OK;
     std::string error;
     bool busy = false;
-    std::map<std::string, GraphEntry> graphs;
+    std::map<GraphKey, GraphEntry> graphs;
     uint64_t graph_clock = 0;
 };
 
@@ -118,6 +117,14 @@ static int64_t slot_bytes(lnbnn_index *ix, int64_t cap, int64_t img_cap)
     return b;
 }
 
+// Partial lists per query of the shared-list plans: as many as keep a slot's
+// lists (whole blocks of up to 1,024 queries) within kMaxLists per descriptor of
+// its capacity, which slot_bytes counts.
+static int slot_lists(int64_t cap)
+{
+    return (int)std::max<int64_t>(1, kMaxLists * cap / ((cap + 1023) / 1024 * 1024));
+}
+
 static int setup_slot(Server *sv, Slot *sl)
 {
     lnbnn_index *ix = sv->ix;
@@ -134,7 +141,7 @@ static int setup_slot(Server *sv, Slot *sl)
         for (int k = 1; k <= kmax; ++k) {
             for (int64_t q = 1024; ; q = std::min(cap, q * 2)) {
                 Plan p;
-                if (make_plan(ix, mode, k, std::min(q, cap), std::min(q, cap), kMaxLists, &p) == LNBNN_OK)
+                if (make_plan(ix, mode, k, std::min(q, cap), std::min(q, cap), slot_lists(cap), &p) == LNBNN_OK)
                     part = std::max(part, work_elems(ix, p, cap));
                 if (q >= cap) break;
             }
@@ -146,7 +153,6 @@ static int setup_slot(Server *sv, Slot *sl)
     if (fp8 && (rc = ensure_fp8_ws(ix, sl->ws, cap, fp8_candidates(kmax), kmax))) return rc;
     LN_HIP(hipHostMalloc((void **)&sl->h_q, std::max<int64_t>(1, cap * rb), hipHostMallocDefault));
     LN_HIP(hipHostMalloc((void **)&sl->h_off, (img + 1) * 8, hipHostMallocDefault));
-    LN_HIP(hipHostMalloc((void **)&sl->h_bd, sizeof(BatchDesc), hipHostMallocDefault));
     LN_HIP(hipHostMalloc((void **)&sl->h_cls, img * 4, hipHostMallocDefault));
     LN_HIP(hipHostMalloc((void **)&sl->h_tot, img * (int64_t)ix->n_classes * 8, hipHostMallocDefault));
     return LNBNN_OK;
@@ -157,7 +163,6 @@ static void free_slot(Slot *sl)
     drop_graphs(sl->graphs);
     if (sl->h_q) (void)hipHostFree(sl->h_q);
     if (sl->h_off) (void)hipHostFree(sl->h_off);
-    if (sl->h_bd) (void)hipHostFree(sl->h_bd);
     if (sl->h_cls) (void)hipHostFree(sl->h_cls);
     if (sl->h_tot) (void)hipHostFree(sl->h_tot);
     if (sl->done) (void)hipEventDestroy(sl->done);
@@ -183,17 +188,18 @@ static int launch_slot(Server *sv, Slot *sl)
     const int64_t n_img = (int64_t)sl->batch.size();
     Workspace &ws = sl->ws;
     LN_HIP(hipMemcpyAsync(ws.q, sl->h_q, (size_t)std::max<int64_t>(rb, n_q * rb), hipMemcpyHostToDevice, sl->stream));
-    LN_HIP(hipMemcpyAsync(ws.offsets, sl->h_off, (size_t)(n_img + 1) * 8, hipMemcpyHostToDevice, sl->stream));
     // planned for the batch's own size within its power-of-two bucket, so
     // small batches get a split that still fills the GPU
     int64_t bucket = 1024;
     while (bucket < n_q) bucket *= 2;
     bucket = std::min(bucket, sv->max_batch_desc);
     Plan plan;
-    int rc = make_plan(ix, mode, k, std::max<int64_t>(1, bucket), n_q, kMaxLists, &plan);
+    int rc = make_plan(ix, mode, k, std::max<int64_t>(1, bucket), n_q, slot_lists(sv->max_batch_desc), &plan);
     if (rc) return rc;
-    *sl->h_bd = BatchDesc{n_q, n_img, ws.q, ws.cls, nullptr, nullptr, plan.walk};
-    LN_HIP(hipMemcpyAsync(ws.bd, sl->h_bd, sizeof(BatchDesc), hipMemcpyHostToDevice, sl->stream));
+    // each batch starts from a clear status word (checked by the completer)
+    *ws.h_status = 0;
+    const BatchDesc bd{n_q, n_img, ws.q, ws.cls, nullptr, nullptr, fp8 ? (void *)ws.totals_f64 : (void *)ws.totals, plan.walk};
+    if ((rc = begin_batch(ix, mode, bd, sl->h_off, ws.bd, ws.offsets, nullptr, sl->stream))) return rc;
     BatchIO io;
     io.offsets = ws.offsets;
     io.bd = ws.bd;
@@ -201,8 +207,6 @@ static int launch_slot(Server *sv, Slot *sl)
     io.img_cap = sv->max_images;
     io.k = k;
     io.mode = mode;
-    io.totals = ws.totals;
-    io.totals_f64 = ws.totals_f64;
     io.ws = &ws;
     io.part_d = ws.part_d;
     io.part_i = ws.part_i;
@@ -216,11 +220,7 @@ static int launch_slot(Server *sv, Slot *sl)
     plan.q_cap = sv->max_batch_desc;
     if (work_elems(ix, plan, plan.q_cap) > ws.part_cap)
         return set_err(LNBNN_EINVAL, "launch tuning changed after the serving loop sized its buffers");
-    // each batch starts from a clear status word (checked by the completer)
-    LN_HIP(launch_set_i32(ws.status, 0, sl->stream));
-    ws.status_dirty = false;
     if ((rc = launch_graph(sl->graphs, sl->graph_clock, ix, plan, io, sl->stream))) return rc;
-    if ((rc = status_end(ws, sl->stream))) return rc;
     LN_HIP(hipMemcpyAsync(sl->h_cls, ws.cls, (size_t)n_img * 4, hipMemcpyDeviceToHost, sl->stream));
     LN_HIP(hipMemcpyAsync(sl->h_tot, fp8 ? (const void *)ws.totals_f64 : (const void *)ws.totals,
                           (size_t)(n_img * ix->n_classes * 8), hipMemcpyDeviceToHost, sl->stream));
@@ -305,7 +305,7 @@ static void completer(Server *sv)
             if (e != hipSuccess) {
                 status = LNBNN_EDEVICE;
                 error = std::string("batch failed: ") + hipGetErrorString(e);
-            } else if (*sl->ws.h_status & kStatusWaitGaveUp) {
+            } else if (*(volatile int32_t *)sl->ws.h_status == kStatusWaitGaveUp) {
                 status = LNBNN_EDEVICE;
                 error = "batch failed: the distance kernel gave up a bounded wait for an LDS stage";
             }
