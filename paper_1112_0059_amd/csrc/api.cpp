@@ -369,7 +369,7 @@ static bool variant_serves(int v, int mode, int fmt, int kp)
     return !(variant(v).pl && mode == LNBNN_FP8_RERANK_2K);
 }
 
-static int default_variant(int mode, int fmt, int kp, bool over, int64_t n_tiles)
+static int default_variant(int mode, int fmt, int kp, bool over, int64_t n_tiles, int64_t n_q, int cu_count)
 {
     // Shared lists of tiles wherever the rule allows them.  16x16 blocks (64
     // queries per wave on four query tiles) beat 32x32 pair lists at every batch
@@ -378,8 +378,21 @@ static int default_variant(int mode, int fmt, int kp, bool over, int64_t n_tiles
     // 11.3, the two-class sweep 2.83 against 3.01; FP16, k = 20, 20.3 against
     // 22.0; original NBNN 11.6 against 12.4.  FP8 keeps the 32x32 form, whose keys
     // the re-rank's candidates are defined by.
-    if (fmt == FMT_I8) return 25;
-    if (fmt == FMT_I8N) return 15;
+    if (fmt == FMT_I8 || fmt == FMT_I8N) {
+        // Two query halves per wave (blocks of 1,024 queries) read a tile from
+        // LDS once for twice the queries: 128 images against 15.36M references
+        // 388 ms against 424, 32 against 2.27M 9.9 against 10.5, original NBNN
+        // 9.4 against 10.4.  Not where the larger blocks pad more than that
+        // gains (one image of 2,251: 4.68 ms against 4.08), nor, with lists
+        // (two starts per lane), where a block's pieces are short: 48,000
+        // descriptors against 1.2M references (6,900 tiles a piece) 5.9 ms
+        // either way, against 0.6M 3.3 against 3.2.
+        const int64_t b512 = (n_q + 511) / 512, b1024 = (n_q + 1023) / 1024;
+        const int64_t piece = b1024 < cu_count ? n_tiles * b1024 / cu_count : n_tiles;
+        const bool halves = b1024 * 200 <= b512 * 106 && variant_supports(28, fmt, kp);
+        if (fmt == FMT_I8N) return halves ? 28 : 15;
+        return halves && piece >= 8192 ? 28 : 25;
+    }
     if (fmt == FMT_I8L) return 19;
     if (fmt == FMT_F16 || fmt == FMT_BF16) return 26;
     const int b = kp_bucket(kp, fmt);
@@ -411,7 +424,7 @@ int make_plan(lnbnn_index *ix, int mode, int k, int64_t q_cap, int64_t n_q, int 
         if (it != ix->pinned.end() && q_cap >= it->second.min_q) tu = it->second.t;
     }
     const int64_t n_tiles = ix->rows[fmt] / kTileRows;
-    const int v = tu.variant >= 0 ? tu.variant : default_variant(mode, fmt, kp, over, n_tiles);
+    const int v = tu.variant >= 0 ? tu.variant : default_variant(mode, fmt, kp, over, n_tiles, n_q, ix->cu_count);
     if (!variant_serves(v, mode, fmt, kp))
         return set_err(LNBNN_EINVAL, "variant %d cannot serve mode %d with k + 1 = %d", v, mode, kp);
     const Variant var = variant(v);
@@ -541,10 +554,14 @@ int64_t work_elems(const lnbnn_index *ix, const Plan &p, int64_t q_cap)
     // whole blocks have one list per query; the remaining ones, fewer than a
     // grid, at most 8 rounds of (block, slice) items or one piece more than
     // blocks and workgroups, and at most max_lists per block
-    const int64_t n_qb = std::max<int64_t>(1, (q_cap + p.block - 1) / p.block);
     if (p.max_lists <= 1) return std::max<int64_t>(q_cap, 1) * p.kpb;
-    const int64_t rem = std::min<int64_t>(n_qb, p.grid);
-    return (n_qb / p.grid * p.grid + std::min<int64_t>(8 * (int64_t)p.grid, rem * p.max_lists)) * p.block * p.kpb;
+    auto lists = [&](int64_t block) {
+        const int64_t n_qb = std::max<int64_t>(1, (q_cap + block - 1) / block);
+        const int64_t rem = std::min<int64_t>(n_qb, p.grid);
+        return (n_qb / p.grid * p.grid + std::min<int64_t>(8 * (int64_t)p.grid, rem * p.max_lists)) * block;
+    };
+    // INT8 batches of other sizes may take the shape with larger blocks
+    return std::max(lists(p.block), p.fmt == FMT_I8 ? lists(1024) : 0) * p.kpb;
 }
 
 int enqueue_batch(lnbnn_index *ix, const Plan &p, const BatchIO &io, hipStream_t s, hipEvent_t *kev)

@@ -632,6 +632,7 @@ constexpr int lists_per_lane() { return PL ? 1 : NT; }
 // fills after about 50 appends, so a merge (4 KP-step insertions) costs each
 // append a fraction of an insertion, and 8 waves' buffers are 16 KB, which the
 // deepest stage shapes leave free.
+// (Two query halves per wave keep two buffers per lane, of two entries.)
 constexpr int kBufEntries = 4;
 
 // min of x across lanes l, l + 32 for y's tile and x's: after the swap lanes
@@ -667,18 +668,20 @@ static __device__ __forceinline__ typename Op::gate_t owned_min(const AccArr<Op,
 
 // A lane's append buffer in LDS: entry j at byte 512 j from its base, so a
 // wave's appends of equal fill are consecutive.
+template <int N>
 struct TileBuf {
+    static constexpr int kEntries = N;
     uint2 *base;
     int cnt;
 };
 
 // Merge the wave's append buffers into its register lists.
-template <class Op, int KP>
-static __device__ __forceinline__ void buf_merge(TileBuf &buf, float &thr, typename Op::gate_t &gt, float (&ld)[KP],
+template <class Op, int KP, class Buf>
+static __device__ __forceinline__ void buf_merge(Buf &buf, float &thr, typename Op::gate_t &gt, float (&ld)[KP],
                                                  int (&li)[KP])
 {
 #pragma unroll 1
-    for (int j = 0; j < kBufEntries; ++j) {
+    for (int j = 0; j < Buf::kEntries; ++j) {
         const uint2 e = buf.base[j * 64];
         const float v = __builtin_bit_cast(float, e.x);
         const bool take = j < buf.cnt && v < thr;
@@ -710,10 +713,10 @@ static __device__ __forceinline__ void gate_any(const typename Op::acc_t (&acc)[
 
 // Insertions for the tiles whose gate passed (rare).  pos: the tile (shared
 // lists) or the lane's first row.
-template <class Op, int KP, int NT, bool PL>
+template <class Op, int KP, int NT, bool PL, class Buf>
 static __device__ __forceinline__ void gate_insert(AccArr<Op, NT> &acc, const bool (&any)[NT], typename Op::gate_t m,
                                                    float (&thr)[lists_per_lane<PL, NT>()],
-                                                   typename Op::gate_t (&gt)[lists_per_lane<PL, NT>()], TileBuf &buf,
+                                                   typename Op::gate_t (&gt)[lists_per_lane<PL, NT>()], Buf &buf,
                                                    float (&ld)[lists_per_lane<PL, NT>()][KP],
                                                    int (&li)[lists_per_lane<PL, NT>()][KP], int pos, int odd_tile0)
 {
@@ -725,7 +728,7 @@ static __device__ __forceinline__ void gate_insert(AccArr<Op, NT> &acc, const bo
                 buf.base[buf.cnt * 64] = make_uint2(__builtin_bit_cast(uint32_t, key), (uint32_t)pos);
                 buf.cnt += 1;
             }
-            if (__builtin_amdgcn_ballot_w64(buf.cnt == kBufEntries) != 0)
+            if (__builtin_amdgcn_ballot_w64(buf.cnt == Buf::kEntries) != 0)
                 buf_merge<Op, KP>(buf, thr[0], gt[0], ld[0], li[0]);
         }
     } else {
@@ -758,11 +761,11 @@ static __device__ __forceinline__ void nbnn_tile_min(const AccArr<Op, NT> &acc, 
 // Gate + insert for the NT query tiles of one reference tile.  All gates
 // are computed before any branch so they can overlap the next MFMA chain.
 // (Original NBNN: the running minimum keys instead.)
-template <class Op, int KP, int NT, bool PL>
+template <class Op, int KP, int NT, bool PL, class Buf>
 static __device__ __forceinline__ void tiles_select(AccArr<Op, NT> &acc,
                                                     float (&thr)[lists_per_lane<PL, NT>()],
                                                     typename Op::gate_t (&gt)[lists_per_lane<PL, NT>()],
-                                                    typename Op::gate_t (&mk)[NT], TileBuf &buf,
+                                                    typename Op::gate_t (&mk)[NT], Buf &buf,
                                                     float (&ld)[lists_per_lane<PL, NT>()][KP],
                                                     int (&li)[lists_per_lane<PL, NT>()][KP], int pos, int odd_tile0,
                                                     int nb_par = 0)
@@ -1022,12 +1025,12 @@ static __device__ __forceinline__ void pin_acc(const AccArr<Op, NT> &acc)
 // gate of the previous tile (acc_old), scheduled as one block: all LDS reads
 // of the new tile first, then MFMAs interleaved with the gate's vector ops.
 // Insertions for the previous tile (rare) follow after the block.
-template <class Op, int KP, int NT, bool PL, int NL = lists_per_lane<PL, NT>()>
+template <class Op, int KP, int NT, bool PL, class Buf, int NL = lists_per_lane<PL, NT>()>
 static __device__ __forceinline__ void pipe_step(AccArr<Op, NT> &acc_new, AccArr<Op, NT> &acc_old,
                                                  const uint4 (&bq)[NT][Op::kSteps][Op::kBU], const int (&sb)[NT],
                                                  const uint4 *frag, const float4 *seed, const int32_t *rsc, int lane,
                                                  int h, float (&thr)[NL], typename Op::gate_t (&gt)[NL],
-                                                 typename Op::gate_t (&mk)[NT], TileBuf &buf, float (&ld)[NL][KP],
+                                                 typename Op::gate_t (&mk)[NT], Buf &buf, float (&ld)[NL][KP],
                                                  int (&li)[NL][KP], int pos_old, int odd_tile0, int nb_par = 0)
 {
     using acc_t = typename Op::acc_t;
@@ -1126,12 +1129,12 @@ static __device__ __forceinline__ void tile_load(const uint4 *frag, const float4
 // One pipeline step on a tile already in registers: its MFMA chain (into
 // acc_new) interleaved with the gate of the previous tile (acc_old); the
 // next tile's LDS loads, issued just before by the caller, lead the block.
-template <class Op, int KP, int NT, bool PL, int NL = lists_per_lane<PL, NT>()>
+template <class Op, int KP, int NT, bool PL, bool READS, class Buf, int NL = lists_per_lane<PL, NT>()>
 static __device__ __forceinline__ void pipe_step_regs(AccArr<Op, NT> &acc_new, AccArr<Op, NT> &acc_old,
                                                       const uint4 (&bq)[NT][Op::kSteps][Op::kBU],
                                                       const int (&sb)[NT], const TileRegs<Op> &cur,
                                                       float (&thr)[NL], typename Op::gate_t (&gt)[NL],
-                                                      typename Op::gate_t (&mk)[NT], TileBuf &buf, float (&ld)[NL][KP],
+                                                      typename Op::gate_t (&mk)[NT], Buf &buf, float (&ld)[NL][KP],
                                                       int (&li)[NL][KP], int pos_old, int odd_tile0, int nb_par = 0)
 {
     using acc_t = typename Op::acc_t;
@@ -1154,10 +1157,11 @@ static __device__ __forceinline__ void pipe_step_regs(AccArr<Op, NT> &acc_new, A
     // chains have completed when the gate's first vector op issues.
     constexpr int NM = S * NT * Op::kMfma;        // MFMAs of the step
     constexpr int LEAD = LNBNN_GATE_LEAD < NM ? LNBNN_GATE_LEAD : NM;
-    constexpr int NREAD = S * Op::kAU + Op::kAccN / 4 + (Op::kScaled ? 32 / Op::kQT : 0);   // next tile's LDS loads
+    // the next tile's LDS loads, issued before this step (READS)
+    constexpr int NREAD = READS ? S * Op::kAU + Op::kAccN / 4 + (Op::kScaled ? 32 / Op::kQT : 0) : 0;
 #if LNBNN_READS_AFTER_LEAD
     __builtin_amdgcn_sched_group_barrier(0x008, LEAD, 0);
-    __builtin_amdgcn_sched_group_barrier(0x100, NREAD, 0);
+    if constexpr (READS) __builtin_amdgcn_sched_group_barrier(0x100, NREAD, 0);
 #else
     __builtin_amdgcn_sched_group_barrier(0x100, NREAD, 0);
     __builtin_amdgcn_sched_group_barrier(0x008, LEAD, 0);
@@ -1176,7 +1180,7 @@ static __device__ __forceinline__ void pipe_step_regs(AccArr<Op, NT> &acc_new, A
 template <int KP, int NL>
 constexpr int waves_per_simd() { return (KP > 40 || (NL == 2 && KP > 20)) ? 1 : 2; }
 
-template <class Op, int KP, int NT, int MT, int W, int NB, bool PL = false, int PFM = 0>
+template <class Op, int KP, int NT, int MT, int W, int NB, bool PL = false, int PFM = 0, int QH = 1>
 __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W),
                           amdgpu_waves_per_eu(waves_per_simd<KP, lists_per_lane<PL, NT>()>(),
                                               waves_per_simd<KP, lists_per_lane<PL, NT>()>())))
@@ -1186,7 +1190,11 @@ void k_dist_topk(DistArgs a)
     constexpr int AU = Op::kAU;
     constexpr int TILE_U4 = S * AU * 64;          // uint4 per 32-row tile
     constexpr int STAGE_U4 = MT * TILE_U4;
-    constexpr int QW = Op::kQT * NT;              // queries per wave
+    // QH = 2: two halves of NT query tiles per wave.  A tile's fragments are read
+    // from LDS once for both: the MFMAs of one half are issued with the gate
+    // of the other, where QH = 1 pairs a tile's MFMAs with the gate of the tile
+    // before.
+    constexpr int QW = Op::kQT * NT * QH;         // queries per wave
     constexpr int NL = lists_per_lane<PL, NT>();  // lists per lane
     static_assert(!PL || NT == Op::kGroups, "shared lists: one query tile per lane group");
     constexpr int QB = W * QW;                    // queries per workgroup
@@ -1209,6 +1217,8 @@ void k_dist_topk(DistArgs a)
     static_assert(MT % 2 == 0, "tiles are processed in pairs");
     static_assert(!Op::kNbnn || kPrefetch, "per-class minima are built on the 8-bit tile paths");
     static_assert(NB >= 2 && (PD - 1) * LPS < 64, "prefetch depth");
+    static_assert(QH == 1 || (QH == 2 && kCounters && (PL || Op::kNbnn)), "two query halves: prefetched tiles, one list per query");
+    constexpr int kBuf = kBufEntries / QH;
     __shared__ uint4 s_frag[NB][STAGE_U4];
     __shared__ float4 s_seed[NB][MT * 8];
     __shared__ int32_t s_rsc[NB][RSC];
@@ -1216,7 +1226,7 @@ void k_dist_topk(DistArgs a)
     // [NB, 2NB): waves done reading it (counts accumulate over the item)
     __shared__ uint32_t s_cnt[2 * NB];
     constexpr bool kTileLists = PL && !Op::kNbnn;       // lists of tiles, filled through append buffers
-    __shared__ uint2 s_buf[kTileLists ? W * kBufEntries * 64 : 1];
+    __shared__ uint2 s_buf[kTileLists ? W * QH * kBuf * 64 : 1];
     auto cnt_signal = [&](int i) {
         asm volatile("" ::: "memory");
         if ((threadIdx.x & 63) == 0)
@@ -1241,7 +1251,9 @@ void k_dist_topk(DistArgs a)
     const int64_t n_q = a.bd->n_q;
     const void *q_src = a.q ? a.q : a.bd->q;
     const int64_t n_qb = (n_q + QB - 1) / QB;
-    TileBuf tbuf{s_buf + (kTileLists ? wave * kBufEntries * 64 + lane : 0), 0};
+    TileBuf<kBuf> tbuf[QH];
+#pragma unroll
+    for (int qh = 0; qh < QH; ++qh) tbuf[qh] = {s_buf + (kTileLists ? (wave * QH + qh) * kBuf * 64 + lane : 0), 0};
 
     // Walk.  Every item is a query block and a range of reference tiles.
     //
@@ -1325,43 +1337,48 @@ void k_dist_topk(DistArgs a)
             }
             const int n_t = (int)(t1 - t0);                // multiple of 8, so of MT
 
-            uint4 bq[NT][S][Op::kBU];
-            int sb[NT];
-            int64_t qi[NT];
+            uint4 bq[QH][NT][S][Op::kBU];
+            int sb[QH][NT];
+            int64_t qi[QH][NT];
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                qi[nt] = (int64_t)qb * QB + wave * QW + nt * Op::kQT + col;
-                Op::load_b(q_src, a.q_scale, qi[nt], qi[nt] < n_q, h, bq[nt], sb[nt]);
-            }
+            for (int qh = 0; qh < QH; ++qh)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    qi[qh][nt] = (int64_t)qb * QB + wave * QW + (qh * NT + nt) * Op::kQT + col;
+                    Op::load_b(q_src, a.q_scale, qi[qh][nt], qi[qh][nt] < n_q, h, bq[qh][nt], sb[qh][nt]);
+                }
 
-            // the query of list l, and its partial list's offset
-            auto list_query = [&](int l) -> int64_t {
-                return PL ? (int64_t)qb * QB + wave * QW + h * Op::kQT + col : qi[l];
+            // the query of list l of half qh, and its partial list's offset
+            auto list_query = [&](int qh, int l) -> int64_t {
+                return PL ? (int64_t)qb * QB + wave * QW + (qh * NT + h) * Op::kQT + col : qi[qh][l];
             };
-            auto list_base = [&](int l) -> int64_t {
-                return PL ? ((int64_t)slot * QB + wave * QW + h * Op::kQT + col) * KP
-                          : ((int64_t)(slot * Op::kGroups + h) * a.q_cap + qi[l]) * KP;
+            auto list_base = [&](int qh, int l) -> int64_t {
+                return PL ? ((int64_t)slot * QB + wave * QW + (qh * NT + h) * Op::kQT + col) * KP
+                          : ((int64_t)(slot * Op::kGroups + h) * a.q_cap + qi[qh][l]) * KP;
             };
-            float ld[NL][KP];
-            int li[NL][KP];
-            float thr[NL];
-            typename Op::gate_t gt[NL];
+            float ld[QH][NL][KP];
+            int li[QH][NL][KP];
+            float thr[QH][NL];
+            typename Op::gate_t gt[QH][NL];
             // original NBNN: each query tile's running minimum key (the
             // lane's share of the rows)
-            typename Op::gate_t mk[NT];
+            typename Op::gate_t mk[QH][NT];
 #pragma unroll
-            for (int l = 0; l < NL; ++l) {
-                const int64_t base = list_base(l);
-                const bool load = !Op::kNbnn && resume && list_query(l) < n_q;
+            for (int qh = 0; qh < QH; ++qh) {
 #pragma unroll
-                for (int p = 0; p < KP; ++p) {
-                    ld[l][p] = load ? a.part_d[base + p] : __builtin_inff();
-                    li[l][p] = load ? a.part_i[base + p] : -1;
+                for (int l = 0; l < NL; ++l) {
+                    const int64_t base = list_base(qh, l);
+                    const bool load = !Op::kNbnn && resume && list_query(qh, l) < n_q;
+#pragma unroll
+                    for (int p = 0; p < KP; ++p) {
+                        ld[qh][l][p] = load ? a.part_d[base + p] : __builtin_inff();
+                        li[qh][l][p] = load ? a.part_i[base + p] : -1;
+                    }
+                    thr[qh][l] = ld[qh][l][KP - 1];
+                    gt[qh][l] = Op::gate_thr(thr[qh][l]);
                 }
-                thr[l] = ld[l][KP - 1];
-                gt[l] = Op::gate_thr(thr[l]);
+                tbuf[qh].cnt = 0;
             }
-            tbuf.cnt = 0;
             // A wave whose stage wait gave up marks its first list with a NaN
             // key in the last slot: its threshold turns NaN, so nothing more
             // is inserted, and the kernels that read the lists (merge, FP8
@@ -1370,8 +1387,8 @@ void k_dist_topk(DistArgs a)
             // anyway: a flag of its own made the hot loop spill.
             auto mark_if = [&](bool gave_up) {
                 const float nan = __builtin_nanf("");
-                ld[0][KP - 1] = gave_up ? nan : ld[0][KP - 1];
-                thr[0] = gave_up ? nan : thr[0];
+                ld[0][0][KP - 1] = gave_up ? nan : ld[0][0][KP - 1];
+                thr[0][0] = gave_up ? nan : thr[0][0];
             };
             // Original NBNN: the class (and parity) of the running minima, and
             // their flush into the per-class minima: the lanes of a query
@@ -1384,20 +1401,24 @@ void k_dist_topk(DistArgs a)
                 cur_cls = enc0 >> 1;
                 p_cur = p_prev = enc0 & 1;
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt) mk[nt] = 0x7fffffff;
+                for (int qh = 0; qh < QH; ++qh)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) mk[qh][nt] = 0x7fffffff;
             }
             auto nbnn_flush = [&]() {
                 if constexpr (Op::kNbnn) {
-                    if (__builtin_isnan(ld[0][KP - 1]) && lane == 0) *a.status = kStatusWaitGaveUp;
+                    if (__builtin_isnan(ld[0][0][KP - 1]) && lane == 0) *a.status = kStatusWaitGaveUp;
 #pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) {
-                        int key = mk[nt];
+                    for (int qh = 0; qh < QH; ++qh)
 #pragma unroll
-                        for (int o = Op::kQT; o < 64; o <<= 1) key = min(key, __shfl_xor(key, o));
-                        if (h == 0 && qi[nt] < n_q && key < (1 << 29))
-                            atomicMin(a.cls_min + (int64_t)cur_cls * a.q_cap + qi[nt], key);
-                        mk[nt] = 0x7fffffff;
-                    }
+                        for (int nt = 0; nt < NT; ++nt) {
+                            int key = mk[qh][nt];
+#pragma unroll
+                            for (int o = Op::kQT; o < 64; o <<= 1) key = min(key, __shfl_xor(key, o));
+                            if (h == 0 && qi[qh][nt] < n_q && key < (1 << 29))
+                                atomicMin(a.cls_min + (int64_t)cur_cls * a.q_cap + qi[qh][nt], key);
+                            mk[qh][nt] = 0x7fffffff;
+                        }
                 }
             };
             // The queries and lists are in registers before any stage copy
@@ -1497,12 +1518,17 @@ void k_dist_topk(DistArgs a)
                                           tr[(m + 1) % 2]);
                         }
                         const int nb_par = m == 0 ? p_prev : p_cur;
-                        if constexpr (m % 2 == 0)
-                            pipe_step_regs<Op, KP, NT, PL>(acc0, acc1, bq, sb, tr[0], thr, gt, mk, tbuf, ld, li,
-                                                           pos_prev, a.odd_tile0, nb_par);
+                        constexpr int LH = QH - 1;        // the half the tile before ended with
+                        if constexpr (QH > 1)
+                            pipe_step_regs<Op, KP, NT, PL, true>(acc0, acc1, bq[0], sb[0], tr[m % 2], thr[LH], gt[LH],
+                                                                 mk[LH], tbuf[LH], ld[LH], li[LH], pos_prev, a.odd_tile0,
+                                                                 nb_par);
+                        else if constexpr (m % 2 == 0)
+                            pipe_step_regs<Op, KP, NT, PL, true>(acc0, acc1, bq[0], sb[0], tr[0], thr[0], gt[0], mk[0],
+                                                                 tbuf[0], ld[0], li[0], pos_prev, a.odd_tile0, nb_par);
                         else
-                            pipe_step_regs<Op, KP, NT, PL>(acc1, acc0, bq, sb, tr[1], thr, gt, mk, tbuf, ld, li,
-                                                           pos_prev, a.odd_tile0, nb_par);
+                            pipe_step_regs<Op, KP, NT, PL, true>(acc1, acc0, bq[0], sb[0], tr[1], thr[0], gt[0], mk[0],
+                                                                 tbuf[0], ld[0], li[0], pos_prev, a.odd_tile0, nb_par);
                         // the step of a stage's first tile gated the previous
                         // stage's last tile: a new class starts after it
                         if constexpr (Op::kNbnn && m == 0) {
@@ -1511,6 +1537,10 @@ void k_dist_topk(DistArgs a)
                                 cur_cls = st_cls;
                             }
                         }
+                        if constexpr (QH == 2)
+                            pipe_step_regs<Op, KP, NT, PL, false>(acc1, acc0, bq[LH], sb[LH], tr[m % 2], thr[0], gt[0],
+                                                                  mk[0], tbuf[0], ld[0], li[0], pos_t, a.odd_tile0,
+                                                                  p_cur);
                         pos_prev = pos_t;
                     });
                 }
@@ -1557,10 +1587,10 @@ void k_dist_topk(DistArgs a)
                         }
                         const int nb_par = m == 0 ? p_prev : p_cur;
                         if constexpr (m % 2 == 0)
-                            pipe_step_regs<Op, KP, NT, PL>(acc0, acc1, bq, sb, tr[0], thr, gt, mk, tbuf, ld, li,
+                            pipe_step_regs<Op, KP, NT, PL, true>(acc0, acc1, bq[0], sb[0], tr[0], thr[0], gt[0], mk[0], tbuf[0], ld[0], li[0],
                                                            pos_prev, a.odd_tile0, nb_par);
                         else
-                            pipe_step_regs<Op, KP, NT, PL>(acc1, acc0, bq, sb, tr[1], thr, gt, mk, tbuf, ld, li,
+                            pipe_step_regs<Op, KP, NT, PL, true>(acc1, acc0, bq[0], sb[0], tr[1], thr[0], gt[0], mk[0], tbuf[0], ld[0], li[0],
                                                            pos_prev, a.odd_tile0, nb_par);
                         if constexpr (Op::kNbnn && m == 0) {
                             if (st_cls != cur_cls) {
@@ -1585,13 +1615,13 @@ void k_dist_topk(DistArgs a)
 #pragma unroll
                 for (int m = 0; m < MT; m += 2) {
                     const int pos_t = pos_of(st * MT + m);
-                    pipe_step<Op, KP, NT, PL>(acc0, acc1, bq, sb, s_frag[buf] + m * TILE_U4, s_seed[buf] + m * 8,
-                                              s_rsc[buf] + (Op::kScaled ? m * kTileRows : 0), lane, h, thr, gt, mk,
-                                              tbuf, ld, li, pos_prev, a.odd_tile0);
-                    pipe_step<Op, KP, NT, PL>(acc1, acc0, bq, sb, s_frag[buf] + (m + 1) * TILE_U4,
+                    pipe_step<Op, KP, NT, PL>(acc0, acc1, bq[0], sb[0], s_frag[buf] + m * TILE_U4, s_seed[buf] + m * 8,
+                                              s_rsc[buf] + (Op::kScaled ? m * kTileRows : 0), lane, h, thr[0], gt[0], mk[0],
+                                              tbuf[0], ld[0], li[0], pos_prev, a.odd_tile0);
+                    pipe_step<Op, KP, NT, PL>(acc1, acc0, bq[0], sb[0], s_frag[buf] + (m + 1) * TILE_U4,
                                               s_seed[buf] + (m + 1) * 8,
-                                              s_rsc[buf] + (Op::kScaled ? (m + 1) * kTileRows : 0), lane, h, thr,
-                                              gt, mk, tbuf, ld, li, pos_t, a.odd_tile0);
+                                              s_rsc[buf] + (Op::kScaled ? (m + 1) * kTileRows : 0), lane, h, thr[0],
+                                              gt[0], mk[0], tbuf[0], ld[0], li[0], pos_t, a.odd_tile0);
                     pos_prev = pos_t + kPosStep;
                 }
                 // Stage st + 1 has landed (this wave's part); after the barrier
@@ -1606,21 +1636,24 @@ void k_dist_topk(DistArgs a)
             }
             wait_vmcnt<0>();                    // drain the loads past the end of the chunk
             __syncthreads();
-            tiles_select<Op, KP, NT, PL>(acc1, thr, gt, mk, tbuf, ld, li, pos_prev, a.odd_tile0, p_cur);
+            tiles_select<Op, KP, NT, PL>(acc1, thr[QH - 1], gt[QH - 1], mk[QH - 1], tbuf[QH - 1], ld[QH - 1], li[QH - 1],
+                                         pos_prev, a.odd_tile0, p_cur);
             if constexpr (Op::kNbnn) {
                 nbnn_flush();
                 continue;
             }
-            if constexpr (kTileLists) buf_merge<Op, KP>(tbuf, thr[0], gt[0], ld[0], li[0]);
-
 #pragma unroll
-            for (int l = 0; l < NL; ++l) {
-                if (list_query(l) < n_q) {
-                    const int64_t base = list_base(l);
+            for (int qh = 0; qh < QH; ++qh) {
+                if constexpr (kTileLists) buf_merge<Op, KP>(tbuf[qh], thr[qh][0], gt[qh][0], ld[qh][0], li[qh][0]);
 #pragma unroll
-                    for (int p = 0; p < KP; ++p) {
-                        a.part_d[base + p] = ld[l][p];
-                        a.part_i[base + p] = li[l][p];
+                for (int l = 0; l < NL; ++l) {
+                    if (list_query(qh, l) < n_q) {
+                        const int64_t base = list_base(qh, l);
+#pragma unroll
+                        for (int p = 0; p < KP; ++p) {
+                            a.part_d[base + p] = ld[qh][l][p];
+                            a.part_i[base + p] = li[qh][l][p];
+                        }
                     }
                 }
             }
@@ -1628,10 +1661,10 @@ void k_dist_topk(DistArgs a)
     }
 }
 
-template <class Op, int KP, int NT, int MT, int W, int NB, bool PL = false, int PFM = 0>
+template <class Op, int KP, int NT, int MT, int W, int NB, bool PL = false, int PFM = 0, int QH = 1>
 static void *kernel_ptr()
 {
-    return reinterpret_cast<void *>(&k_dist_topk<Op, KP, NT, MT, W, NB, PL, PFM>);
+    return reinterpret_cast<void *>(&k_dist_topk<Op, KP, NT, MT, W, NB, PL, PFM, QH>);
 }
 
 template <class Op, int KP>
@@ -1693,10 +1726,15 @@ static void *pick_variant(int v)
         if constexpr (!std::is_void<Q16>::value && !Op::kNbnn && KP <= 33) {
             if constexpr (Op::kSteps * Op::kAU == 4) {
                 if (v == 25) return kernel_ptr<Q16, KP, 4, 8, 8, 4, true>();
+                // two halves of four query tiles: INT8 lists up to 11
+                if constexpr (Op::kFmt == FMT_I8 && KP <= 11)
+                    if (v == 28) return kernel_ptr<Q16, KP, 4, 8, 8, 4, true, 0, 2>();
             } else {
                 if (v == 26) return kernel_ptr<Q16, KP, 4, 4, 8, 4, true>();
             }
         }
+        if constexpr (Op::kNbnn)
+            if (v == 28) return kernel_ptr<Q16, KP, 4, 8, 8, 4, true, 0, 2>();
         // the FP8 top-4k candidate lists on 16x16 blocks (40 entries at
         // k = 10), with and without the next-tile prefetch
         if constexpr (Op::kFmt == FMT_FP8 && KP > 33 && KP <= 40)
