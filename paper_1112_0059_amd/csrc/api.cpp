@@ -105,10 +105,69 @@ void stream_release(int device, hipStream_t s)
     g_streams[device].push_back(s);
 }
 
+struct KeptBlock {
+    int device;
+    void *p;
+    size_t bytes;
+};
+static std::mutex g_kept_mu;
+static std::vector<KeptBlock> g_kept;                       // oldest first
+static size_t g_kept_bytes = 0;
+static std::unordered_map<void *, KeptBlock> g_given;       // buffers in use
+
+static void drop_kept_locked(size_t down_to)
+{
+    size_t n = 0;
+    while (n < g_kept.size() && g_kept_bytes > down_to) {
+        (void)hipFree(g_kept[n].p);
+        g_kept_bytes -= g_kept[n++].bytes;
+    }
+    g_kept.erase(g_kept.begin(), g_kept.begin() + n);
+}
+
 static hipError_t dmalloc(void **p, size_t bytes)
 {
     if (fault_injected("alloc")) return hipErrorOutOfMemory;
-    return hipMalloc(p, bytes);
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    std::lock_guard<std::mutex> lock(g_kept_mu);
+    // the smallest kept block that fits and wastes at most a quarter
+    size_t best = g_kept.size();
+    for (size_t i = 0; i < g_kept.size(); ++i)
+        if (g_kept[i].device == dev && g_kept[i].bytes >= bytes && g_kept[i].bytes <= bytes + bytes / 4 + 4096 &&
+            (best == g_kept.size() || g_kept[i].bytes < g_kept[best].bytes))
+            best = i;
+    if (best < g_kept.size()) {
+        *p = g_kept[best].p;
+        g_kept_bytes -= g_kept[best].bytes;
+        g_given[*p] = g_kept[best];
+        g_kept.erase(g_kept.begin() + best);
+        return hipSuccess;
+    }
+    e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory && !g_kept.empty()) {
+        (void)hipGetLastError();
+        drop_kept_locked(0);
+        e = hipMalloc(p, bytes);
+    }
+    if (e == hipSuccess) g_given[*p] = KeptBlock{dev, *p, bytes};
+    return e;
+}
+
+void dfree(void *p)
+{
+    if (!p) return;
+    std::lock_guard<std::mutex> lock(g_kept_mu);
+    auto it = g_given.find(p);
+    if (it == g_given.end()) {
+        (void)hipFree(p);
+        return;
+    }
+    g_kept.push_back(it->second);
+    g_kept_bytes += it->second.bytes;
+    g_given.erase(it);
+    drop_kept_locked(kKeptBytes);
 }
 
 int64_t row_bytes(int dtype, int dim) { return dtype == LNBNN_U8 ? dim : (int64_t)dim * 4; }
@@ -139,7 +198,7 @@ Workspace::~Workspace()
     void *ps[] = {q, offsets, bd, part_d, part_i, totals, totals_f64, cls, nbr_idx, nbr_dist,
                   q8, qsc, cand, upd_cls, upd_delta};
     for (void *p : ps)
-        if (p) (void)hipFree(p);
+        dfree(p);
     if (h_status) (void)hipHostFree(h_status);
 }
 
@@ -410,6 +469,14 @@ static int default_variant(int mode, int fmt, int kp, bool over, int64_t n_tiles
     return b <= 40 ? 16 : !over ? 18 : 0;
 }
 
+// Most rounds of (block, slice) items worth trying for `rem` blocks: few blocks
+// fill a grid almost evenly in one (13 blocks: 19 slices, 247 of 256), and each
+// further round only adds lists.
+static int64_t cut_rounds(int64_t rem, int64_t grid)
+{
+    return std::max<int64_t>(1, std::min<int64_t>(8, (16 * rem + grid - 1) / grid));
+}
+
 int make_plan(lnbnn_index *ix, int mode, int k, int64_t q_cap, int64_t n_q, int max_lists, Plan *out)
 {
     const int kp = dist_list_len(mode, k);
@@ -460,7 +527,7 @@ int make_plan(lnbnn_index *ix, int mode, int k, int64_t q_cap, int64_t n_q, int 
         int64_t slices = rem > 0 ? 1 : 0, tiles = n_tiles, pieces = rem;
         if (rem > 0 && max_lists > 1) {
             double best = (double)n_tiles;
-            for (int64_t rounds = 1; rounds <= 8; ++rounds) {
+            for (int64_t rounds = 1; rounds <= cut_rounds(rem, grid); ++rounds) {
                 const int64_t t = up8((n_tiles + rounds * grid / rem - 1) / (rounds * grid / rem));
                 const int64_t n = (n_tiles + t - 1) / t;
                 const double cost = (double)((rem * n + grid - 1) / grid) * ((double)t + kStart);
@@ -552,13 +619,14 @@ int64_t work_elems(const lnbnn_index *ix, const Plan &p, int64_t q_cap)
 {
     if (!p.pl || p.fmt == FMT_I8N) return batch_elems(ix, p, q_cap);
     // whole blocks have one list per query; the remaining ones, fewer than a
-    // grid, at most 8 rounds of (block, slice) items or one piece more than
-    // blocks and workgroups, and at most max_lists per block
+    // grid, at most cut_rounds rounds of (block, slice) items or one piece per
+    // block and workgroup, and at most max_lists per block
     if (p.max_lists <= 1) return std::max<int64_t>(q_cap, 1) * p.kpb;
     auto lists = [&](int64_t block) {
         const int64_t n_qb = std::max<int64_t>(1, (q_cap + block - 1) / block);
         const int64_t rem = std::min<int64_t>(n_qb, p.grid);
-        return (n_qb / p.grid * p.grid + std::min<int64_t>(8 * (int64_t)p.grid, rem * p.max_lists)) * block;
+        const int64_t pieces = std::max<int64_t>(cut_rounds(rem, p.grid) * p.grid, rem + p.grid);
+        return (n_qb / p.grid * p.grid + std::min<int64_t>(pieces, rem * p.max_lists)) * block;
     };
     // INT8 batches of other sizes may take the shape with larger blocks
     return std::max(lists(p.block), p.fmt == FMT_I8 ? lists(1024) : 0) * p.kpb;
@@ -680,29 +748,29 @@ int enqueue_batch(lnbnn_index *ix, const Plan &p, const BatchIO &io, hipStream_t
 static int free_index_buffers(lnbnn_index *ix)
 {
     for (int f = 0; f < kNumFmt; ++f) {
-        if (ix->frag[f]) (void)hipFree(ix->frag[f]);
+        if (ix->frag[f]) dfree(ix->frag[f]);
         ix->frag[f] = nullptr;
     }
     // seeds of the two exact 16-bit formats share one buffer
-    if (ix->seed[FMT_F16]) (void)hipFree(ix->seed[FMT_F16]);
-    else if (ix->seed[FMT_BF16]) (void)hipFree(ix->seed[FMT_BF16]);
-    if (ix->seed[FMT_FP8]) (void)hipFree(ix->seed[FMT_FP8]);
-    if (ix->seed[FMT_I8]) (void)hipFree(ix->seed[FMT_I8]);
-    if (ix->seed[FMT_I8L]) (void)hipFree(ix->seed[FMT_I8L]);
-    if (ix->seed[FMT_I8N]) (void)hipFree(ix->seed[FMT_I8N]);
+    if (ix->seed[FMT_F16]) dfree(ix->seed[FMT_F16]);
+    else if (ix->seed[FMT_BF16]) dfree(ix->seed[FMT_BF16]);
+    if (ix->seed[FMT_FP8]) dfree(ix->seed[FMT_FP8]);
+    if (ix->seed[FMT_I8]) dfree(ix->seed[FMT_I8]);
+    if (ix->seed[FMT_I8L]) dfree(ix->seed[FMT_I8L]);
+    if (ix->seed[FMT_I8N]) dfree(ix->seed[FMT_I8N]);
     for (int f = 0; f < kNumFmt; ++f) ix->seed[f] = nullptr;
-    if (ix->perm) (void)hipFree(ix->perm);
+    if (ix->perm) dfree(ix->perm);
     ix->perm = nullptr;
-    if (ix->tile_class) (void)hipFree(ix->tile_class);
+    if (ix->tile_class) dfree(ix->tile_class);
     ix->tile_class = nullptr;
-    if (ix->labels) (void)hipFree(ix->labels);
-    if (ix->ref_f32) (void)hipFree(ix->ref_f32);
-    if (ix->row_scale) (void)hipFree(ix->row_scale);
+    if (ix->labels) dfree(ix->labels);
+    if (ix->ref_f32) dfree(ix->ref_f32);
+    if (ix->row_scale) dfree(ix->row_scale);
     ix->labels = nullptr;
     ix->ref_f32 = nullptr;
     ix->row_scale = nullptr;
     std::lock_guard<std::mutex> lock(ix->retired_mu);
-    for (void *p : ix->retired) (void)hipFree(p);
+    for (void *p : ix->retired) dfree(p);
     ix->retired.clear();
     return LNBNN_OK;
 }
@@ -784,32 +852,30 @@ static int build_nbnn_layout(lnbnn_index *ix, const uint8_t *d_refs, const int32
 static int build_i8(lnbnn_index *ix, const uint8_t *d_refs, int fmt, hipStream_t s, int64_t *bytes)
 {
     const int64_t n = ix->n_refs, n_blocks = (n + 255) / 256;
-    uint8_t *d_par = nullptr;            // parity of every reference, then the blocks' odd counts
-    const int64_t cnt_at = (n + 3) / 4 * 4;
-    LN_HIP(hipMallocAsync((void **)&d_par, cnt_at + (n_blocks + 1) * 4, s));
-    int32_t *block_odd = reinterpret_cast<int32_t *>(d_par + cnt_at);
+    auto up = [](int64_t r) { return (r + kPadRows - 1) / kPadRows * kPadRows; };
+    const int64_t most = up(n) + kPadRows;           // rows, however the parities fall
+    int32_t *iseed = nullptr;
+    int rc = grow(ix, (void **)&ix->frag[fmt], most * ix->dim, 1);
+    if (!rc) rc = grow(ix, (void **)&iseed, most, 4);
+    if (!rc) ix->seed[fmt] = reinterpret_cast<float *>(iseed);
+    if (!rc) rc = grow(ix, (void **)&ix->perm, most, 4);
+    if (rc) return rc;
+    // the parity of every reference and the blocks' odd counts sit in the seeds'
+    // buffer until the rows are packed: n + n / 64 of its 4 n bytes
+    uint8_t *d_par = reinterpret_cast<uint8_t *>(iseed);
+    int32_t *block_odd = iseed + (n + 3) / 4;
     int32_t n_odd = 0;
     hipError_t e = launch_row_parity(d_refs, n, ix->dim, d_par, s);
     if (e == hipSuccess) e = launch_parity_count(d_par, n, block_odd, s);
     if (e == hipSuccess) e = hipMemcpyAsync(&n_odd, block_odd + n_blocks, 4, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
-    auto up = [](int64_t r) { return (r + kPadRows - 1) / kPadRows * kPadRows; };
     const int64_t even_pad = up(n - n_odd), n_pad = even_pad + up(n_odd);
-    int32_t *iseed = nullptr;
-    int rc = e == hipSuccess ? LNBNN_OK : hip_err(e, "row parity");
-    if (!rc) rc = grow(ix, (void **)&ix->frag[fmt], n_pad * ix->dim, 1);
-    if (!rc) rc = grow(ix, (void **)&iseed, n_pad, 4);
-    if (!rc) ix->seed[fmt] = reinterpret_cast<float *>(iseed);
-    if (!rc) rc = grow(ix, (void **)&ix->perm, n_pad, 4);
-    if (!rc) {
-        e = launch_parity_perm(d_par, n, block_odd, even_pad, n_pad, ix->perm, s);
-        if (e == hipSuccess) e = launch_pack_i8(d_refs, n_pad, ix->dim, ix->frag[fmt], iseed, s, ix->perm);
-        if (e != hipSuccess) rc = hip_err(e, "pack i8");
-    }
-    (void)hipFreeAsync(d_par, s);
+    if (e == hipSuccess) e = launch_parity_perm(d_par, n, block_odd, even_pad, n_pad, ix->perm, s);
+    if (e == hipSuccess) e = launch_pack_i8(d_refs, n_pad, ix->dim, ix->frag[fmt], iseed, s, ix->perm);
+    if (e != hipSuccess) rc = hip_err(e, "pack i8");
     ix->rows[fmt] = n_pad;
     ix->odd_tile0 = (int32_t)(even_pad / kTileRows);
-    *bytes += n_pad * (ix->dim + 8);
+    *bytes += most * (ix->dim + 8);
     return rc;
 }
 
@@ -877,19 +943,25 @@ extern "C" int lnbnn_build_index(const void *refs, int dtype, int64_t n_refs, in
         if (err != hipSuccess) return fail(hip_err(err, "hipEventCreate"));
     }
 
-    // labels: device copy (and validation when they came as device memory)
-    if ((rc = grow(ixp, (void **)&ix->labels, n_refs, 4))) return fail(rc);
-    std::vector<int32_t> hl;           // host copy of device labels
+    // labels: device copy (and validation when they came as device memory: on
+    // the device, 2.3M labels read back and checked here took 2 ms)
+    if ((rc = grow(ixp, (void **)&ix->labels, n_refs + 1, 4))) return fail(rc);
+    std::vector<int32_t> hl;           // host copy of device labels (the class-sorted layout)
     if (dev_in) {
-        hl.resize(n_refs);
-        hipError_t e = hipMemcpy(hl.data(), labels, n_refs * 4, hipMemcpyDeviceToHost);
-        if (e != hipSuccess) return fail(hip_err(e, "hipMemcpy(labels)"));
-        for (int64_t j = 0; j < n_refs; ++j)
-            if (hl[j] < 0 || hl[j] >= n_classes)
-                return fail(set_err(LNBNN_EINVAL, "label[%lld] = %d outside [0, %d)", (long long)j, hl[j],
-                                    n_classes));
-        e = hipMemcpyAsync(ix->labels, labels, n_refs * 4, hipMemcpyDeviceToDevice, s);
+        hipError_t e = hipMemcpyAsync(ix->labels, labels, n_refs * 4, hipMemcpyDeviceToDevice, s);
         if (e != hipSuccess) return fail(hip_err(e, "hipMemcpyAsync(labels)"));
+        int32_t bad = 0, value = 0;    // first label out of range (n_refs: none), in the spare last element
+        e = launch_check_labels(ix->labels, n_refs, n_classes, ix->labels + n_refs, s);
+        if (e == hipSuccess) e = hipMemcpyAsync(&bad, ix->labels + n_refs, 4, hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (e == hipSuccess && bad < n_refs) e = hipMemcpy(&value, ix->labels + bad, 4, hipMemcpyDeviceToHost);
+        if (e == hipSuccess && (mode_mask & LNBNN_MODE_BIT(LNBNN_NBNN_I8)) && bad >= n_refs) {
+            hl.resize(n_refs);
+            e = hipMemcpy(hl.data(), ix->labels, n_refs * 4, hipMemcpyDeviceToHost);
+        }
+        if (e != hipSuccess) return fail(hip_err(e, "label check"));
+        if (bad < n_refs)
+            return fail(set_err(LNBNN_EINVAL, "label[%lld] = %d outside [0, %d)", (long long)bad, value, n_classes));
     } else {
         hipError_t e = hipMemcpyAsync(ix->labels, labels, n_refs * 4, hipMemcpyHostToDevice, s);
         if (e != hipSuccess) return fail(hip_err(e, "hipMemcpyAsync(labels)"));
@@ -919,8 +991,11 @@ extern "C" int lnbnn_build_index(const void *refs, int dtype, int64_t n_refs, in
     }
     float *seed = nullptr;
     int64_t bytes = n_refs * 4 + (dtype == LNBNN_F32 ? rbytes : 0);
-    rc = grow(ixp, (void **)&seed, ix->n_pad, 4);
-    if (!rc) bytes += ix->n_pad * 4;
+    // seeds of the 16-bit or the FP8 copy (the INT8 copies have their own)
+    if (dtype == LNBNN_F32 || (mode_mask & (LNBNN_MODE_BIT(LNBNN_EXACT_F16) | LNBNN_MODE_BIT(LNBNN_EXACT_BF16)))) {
+        rc = grow(ixp, (void **)&seed, ix->n_pad, 4);
+        if (!rc) bytes += ix->n_pad * 4;
+    }
     bool seeded = false;
     if (dtype == LNBNN_F32) {
         if (!rc) rc = grow(ixp, (void **)&ix->row_scale, ix->n_pad, 4);
@@ -961,14 +1036,10 @@ extern "C" int lnbnn_build_index(const void *refs, int dtype, int64_t n_refs, in
     if (staged) (void)hipFreeAsync(staged, s);
     hipError_t e = hipStreamSynchronize(s);
     if (rc) {
-        if (seed && !seeded) (void)hipFree(seed);
+        if (seed && !seeded) dfree(seed);
         return fail(rc);
     }
     if (e != hipSuccess) return fail(hip_err(e, "build_index sync"));
-    if (seed && !seeded) {   // no mode used the shared seed buffer
-        (void)hipFree(seed);
-        bytes -= ix->n_pad * 4;
-    }
     ix->device_bytes = bytes;
     size_t free_b = 0, total_b = 0;
     LN_HIP(hipMemGetInfo(&free_b, &total_b));

@@ -251,6 +251,8 @@ hipError_t launch_begin(const BeginArgs &a, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, hipStream_t s);
 hipError_t launch_finish(const FinishArgs &a, int64_t q_cap, hipStream_t s);
 hipError_t launch_argmin(const BatchDesc *bd, int64_t img_cap, int32_t n_classes, hipStream_t s);
+// first_bad = the first index of labels [0, n) outside [0, n_classes), or n
+hipError_t launch_check_labels(const int32_t *labels, int64_t n, int32_t n_classes, int32_t *first_bad, hipStream_t s);
 // per reference row: parity of ||r - 128||^2 (u8 rows, dim a multiple of 16)
 hipError_t launch_row_parity(const uint8_t *refs, int64_t n_refs, int dim, uint8_t *out, hipStream_t s);
 hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, int64_t stride, int64_t rows, const BatchDesc *bd,

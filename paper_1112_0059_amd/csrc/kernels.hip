@@ -95,6 +95,17 @@ __global__ __launch_bounds__(256) void k_row_parity(const uint8_t *__restrict__ 
     }
 }
 
+__global__ __launch_bounds__(256) void k_check_labels(const int32_t *__restrict__ labels, int32_t n, int32_t n_classes,
+                                                      int32_t *__restrict__ first_bad)
+{
+    int bad = n;
+    for (int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+        if (labels[i] < 0 || labels[i] >= n_classes) bad = min(bad, (int)i);
+    if (bad < n) atomicMin(first_bad, bad);
+}
+
+__global__ void k_set_i32(int32_t *p, int32_t v) { *p = v; }
+
 // Odd rows of each 256-row block.
 __global__ __launch_bounds__(256) void k_parity_blocks(const uint8_t *__restrict__ par, int64_t n_refs,
                                                        int32_t *__restrict__ block_odd)
@@ -577,6 +588,15 @@ hipError_t launch_pack_i8(const uint8_t *refs, int64_t n_pad, int dim, uint4 *fr
         k_pack_i8<OpI8L, 16><<<grid_for(n_pad * 16, 256, 65536), 256, 0, s>>>(refs, n_pad, frag, seed, perm);
     else
         return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+hipError_t launch_check_labels(const int32_t *labels, int64_t n, int32_t n_classes, int32_t *first_bad, hipStream_t s)
+{
+    k_set_i32<<<1, 1, 0, s>>>(first_bad, (int32_t)n);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    k_check_labels<<<grid_for(n, 1024, 4096), 256, 0, s>>>(labels, (int32_t)n, n_classes, first_bad);
     return hipGetLastError();
 }
 
