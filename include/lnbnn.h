@@ -130,7 +130,8 @@ enum {
  * Memory: the packed references stay resident (N x 256 B per FP16/BF16
  * mode, N x dim B for INT8, N x 128 B FP8 plus N x 512 B FP32 for the
  * re-rank, about N x 132 B for the class-sorted NBNN copy), with FP32 norms
- * (4 B) and int32 labels (4 B) per reference.
+ * (4 B) and int32 labels (4 B) per reference, and for INT8 the packed order
+ * (4 B).
  * Errors: EINVAL (NULL pointer, dim not 128 or 160, 160 with other data or
  * modes than u8 INT8, n_refs < 1 or >= 2^31-256,
  * n_classes < 1, label out of range, empty or data-incompatible mode mask),
@@ -142,7 +143,9 @@ int lnbnn_build_index(const void *refs, int dtype, int64_t n_refs, int32_t dim,
                       uint32_t flags, void *stream, lnbnn_index **out);
 
 /* Release an index and every device buffer it owns.  EBUSY while serving
- * tickets are pending (nothing is freed then).  NULL is accepted. */
+ * tickets are pending (nothing is freed then).  NULL is accepted.  Up to 1 GiB
+ * of released buffers per process stays allocated for the next index (given
+ * back to the device when an allocation fails). */
 int lnbnn_index_free(lnbnn_index *ix);
 
 /* Basic facts of an index (any pointer may be NULL). */
