@@ -114,6 +114,7 @@ static std::mutex g_kept_mu;
 static std::vector<KeptBlock> g_kept;                       // oldest first
 static size_t g_kept_bytes = 0;
 static std::unordered_map<void *, KeptBlock> g_given;       // buffers in use
+static thread_local bool t_keep_frees = true;               // false: this thread's dfree goes to the driver
 
 static void drop_kept_locked(size_t down_to)
 {
@@ -160,7 +161,8 @@ void dfree(void *p)
     if (!p) return;
     std::lock_guard<std::mutex> lock(g_kept_mu);
     auto it = g_given.find(p);
-    if (it == g_given.end()) {
+    if (it == g_given.end() || !t_keep_frees) {
+        if (it != g_given.end()) g_given.erase(it);
         (void)hipFree(p);
         return;
     }
@@ -1061,6 +1063,16 @@ extern "C" int lnbnn_index_free(lnbnn_index *ix)
     // the index's own work: the last classify call and its stream
     (void)ws_sync(ix);
     if (ix->own_stream) (void)hipStreamSynchronize(ix->own_stream);
+    // and calls that leave no mark (lnbnn_classify_noalloc on a caller's
+    // stream): the buffers may go to another index at once.  Where the device
+    // cannot be waited for (a capture elsewhere), they go back to the driver.
+    struct KeepScope {
+        ~KeepScope() { t_keep_frees = true; }
+    } scope;
+    if (hipDeviceSynchronize() != hipSuccess) {
+        (void)hipGetLastError();
+        t_keep_frees = false;
+    }
     drop_graphs(ix);
     free_index_buffers(ix);
     free_index_handles(ix);
