@@ -69,6 +69,29 @@ def test_walks(walk_set, mode, workgroups, n_img):
             _check(got, (wt[:n_img], wc[:n_img], wi[:n], wd[:n]))
 
 
+@pytest.mark.parametrize("mode", [I8, NB])
+@pytest.mark.parametrize("workgroups,chunk,n_img", [(0, 0, 7), (3, 512, 7), (4, 0, 6), (1, 8, 2), (0, 0, 1)])
+def test_query_halves(walk_set, mode, workgroups, chunk, n_img):
+    """Two query halves per wave (blocks of 1,024 queries): slices, runs, whole
+    rounds with parked lists, a last block of a few queries, one query."""
+    R, labels, Q, off, ix, (wt, wc, wi, wd) = walk_set
+    off = off[:n_img + 1]
+    n = int(off[-1])
+    _say(f"halves mode={mode} workgroups={workgroups} chunk={chunk} images={n_img}")
+    L.lnbnn_set_tuning(ix, mode, 10, variant=28, chunk_tiles=chunk, max_workgroups=workgroups)
+    try:
+        got = L.lnbnn_classify(ix, Q[:n], off, 10, mode, flags=L.LNBNN_TIMING, want_neighbours=mode != NB)
+        assert L.lnbnn_last_timing(ix)["tile_variant"] == 28
+    finally:
+        L.lnbnn_set_tuning(ix, mode, 10)
+    if mode == NB:
+        _, _, D = oracle.knn_class_block(Q[:n], R, labels, 9, 1)
+        tot, cls = oracle.nbnn(D, off)
+        assert np.array_equal(got[1], tot) and np.array_equal(got[0], cls)
+    else:
+        _check(got, (wt[:n_img], wc[:n_img], wi[:n], wd[:n]))
+
+
 @pytest.mark.parametrize("mode", [I8, F16, BF16])
 @pytest.mark.parametrize("kind", ["ties", "even", "odd", "one_odd", "loc"])
 def test_ties_and_parities(mode, kind):
