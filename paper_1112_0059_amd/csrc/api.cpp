@@ -458,8 +458,9 @@ static int default_variant(int mode, int fmt, int kp, bool over, int64_t n_tiles
     if (fmt == FMT_F16 || fmt == FMT_BF16) return 26;
     const int b = kp_bucket(kp, fmt);
     // the union-of-halves rule keeps per-half lists of rows, whose insertions are
-    // most of its time: one query tile per wave (no spills) beats two, 24.2 ms
-    // against 30.1 for 48,000 descriptors over 2.27M references, k = 10
+    // most of its time over short slices: one query tile per wave (no spills)
+    // beats two, 24.2 ms against 30.1 for 48,000 descriptors over 2.27M
+    // references, k = 10 (make_plan takes two where the slices are long)
     if (mode == LNBNN_FP8_RERANK_2K) return b <= 40 ? 11 : 0;
     // an FP8 index of no more tiles than the list holds: every tile would be
     // recomputed for every query, so short lists of rows are the better ones
@@ -599,7 +600,27 @@ int make_plan(lnbnn_index *ix, int mode, int k, int64_t q_cap, int64_t n_q, int 
     p.n_lists = (int)S * groups;
     p.walk.n_slices = (int)S;
     p.walk.tiles_per_slice = (int)tps;
-    p.grid = (int)std::max<int64_t>(1, std::min<int64_t>((q_cap + qb - 1) / qb * S, resident_wg));
+    int64_t item_qb = qb, grid_wg = resident_wg;
+    // The union-of-halves rule: two query tiles per wave read a tile once for
+    // twice the queries and win where the lists have settled, over long slices.
+    // Lists of up to 8 (k <= 4): 48,000 descriptors, k = 1, slices of 8,900 tiles
+    // 12.2 ms against 17.1, k = 3 14.9 against 18.8; one image, 15,000 tiles 5.6
+    // against 7.9.  Lists of 20, whose insertions cost more: slices of 60,000
+    // tiles 96 ms against 119, 48,000 tiles 36.5 against 39.6, but 8,900 tiles
+    // 28.6 against 22.7.  And for lists of up to 4 where whole slices of 512
+    // queries fill the chip anyway (45,500 descriptors over 97,000 references:
+    // 1.34 against 1.45).  One tile elsewhere: its items are twice as many (one
+    // image, slices of 2,200 tiles, k = 1: 0.85 against 1.38).  Same slices and
+    // lists either way.
+    const int64_t settled = kpb <= 8 ? 4096 : 24576;
+    if (by512 && (tps >= settled || (kpb <= 4 && n_qb * S >= ix->cu_count))) {
+        p.variant = 8;
+        item_qb = slice_qb;
+        p.block = (int)item_qb;
+        grid_wg = (int64_t)ix->cu_count * blocks_per_cu(ix, p.variant, fmt, kpb);
+        if (tu.max_workgroups > 0) grid_wg = std::min<int64_t>(grid_wg, tu.max_workgroups);
+    }
+    p.grid = (int)std::max<int64_t>(1, std::min<int64_t>((q_cap + item_qb - 1) / item_qb * S, grid_wg));
     // By default an item sweeps its whole slice with its lists in registers;
     // a tuned chunk length makes workgroups that own several items walk the
     // slice chunk by chunk instead (lists saved between chunks), which keeps

@@ -148,3 +148,35 @@ def test_fp8_candidates_do_not_depend_on_the_walk(k):
                 assert np.array_equal(x, y)
     finally:
         ix.free()
+
+
+@pytest.mark.parametrize("n_ref,n_q,workgroups,k,want,other", [
+    (131063, 1300, 1, 1, 8, 11),    # 4,096 tiles in one slice
+    (131063, 1300, 1, 3, 8, 11),
+    (131063, 1300, 1, 5, 11, 8),    # lists of 20
+    (786401, 700, 1, 5, 8, 11),     # 24,576 tiles
+    (130711, 1300, 1, 1, 11, 8),    # 4,085 tiles, fewer items than CUs
+    (64013, 4096, 0, 1, 8, 8),      # 8 blocks of 512 in 32 slices: 256 items
+    (64013, 4096, 0, 2, 8, 8),
+])
+def test_union_of_halves_shapes(n_ref, n_q, workgroups, k, want, other):
+    """Default shape of the union-of-halves FP8 rule: where the slices are the
+    same, so are the lists, and every result is equal to the other shape's."""
+    rng = np.random.default_rng(n_ref + k)
+    R = rng.standard_normal((n_ref, 128), dtype=np.float32)
+    labels = rng.integers(0, 5, size=n_ref).astype(np.int32)
+    Q = rng.standard_normal((n_q, 128), dtype=np.float32)
+    off = np.array([0, 1, 700, n_q], np.int64)
+    mode = L.LNBNN_FP8_RERANK_2K
+    ix = L.lnbnn_build_index(R, labels, 5, L.LNBNN_MODE_BIT(mode))
+    try:
+        res = []
+        for v in (-1, other):
+            _say(f"union refs={n_ref} queries={n_q} workgroups={workgroups} k={k} variant={v}")
+            L.lnbnn_set_tuning(ix, mode, k, variant=v, max_workgroups=workgroups)
+            res.append(L.lnbnn_classify(ix, Q, off, k, mode, flags=L.LNBNN_TIMING, want_neighbours=True))
+            assert L.lnbnn_last_timing(ix)["tile_variant"] == (want if v < 0 else other)
+    finally:
+        ix.free()
+    for a, b in zip(*res):
+        assert np.array_equal(a, b)
