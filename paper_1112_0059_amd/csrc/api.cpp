@@ -723,7 +723,7 @@ int enqueue_batch(lnbnn_index *ix, const Plan &p, const BatchIO &io, hipStream_t
         r.upd_delta = io.upd_delta;
         r.status = w->status;
         if (p.pl)
-            LN_HIP(launch_refine_fp8(t, r, io.q_cap, s));
+            LN_HIP(launch_refine_fp8(variant(p.variant).qt, t, r, io.q_cap, s));
         else
             LN_HIP(launch_cand_merge(r, io.q_cap, s));
         LN_HIP(launch_rerank(r, io.q_cap, io.img_cap, s));

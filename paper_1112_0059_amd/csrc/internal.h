@@ -237,9 +237,10 @@ hipError_t launch_fp8_qprep(const BatchDesc *bd, int64_t q_cap, uint4 *q8, int32
 // merge of the candidate lists into a.cand (one list per lane group)
 hipError_t launch_cand_merge(const RerankArgs &a, int64_t q_cap, hipStream_t s);
 hipError_t launch_rerank(const RerankArgs &a, int64_t q_cap, int64_t img_cap, hipStream_t s);
-// shared lists: the exact formats' whole finish, and the FP8 candidates
+// shared lists: the exact formats' whole finish, and the FP8 candidates (qt: the
+// block shape, and so the arithmetic, of the variant that made the lists)
 hipError_t launch_refine(int fmt, const RefineArgs &r, const FinishArgs &a, int64_t q_cap, hipStream_t s);
-hipError_t launch_refine_fp8(const RefineArgs &r, const RerankArgs &a, int64_t q_cap, hipStream_t s);
+hipError_t launch_refine_fp8(int qt, const RefineArgs &r, const RerankArgs &a, int64_t q_cap, hipStream_t s);
 int grid_for(int64_t n, int block, int cap);
 
 hipError_t launch_dist_topk(int variant, int fmt, int kp, const DistArgs &a, int grid,

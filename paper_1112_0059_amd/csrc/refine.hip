@@ -3,15 +3,15 @@
 //
 //   k_refine<Op>      per query (one wave): merge of the query's partial lists
 //                     of (key, tile), recomputation of the rows of the k + 1
-//                     best tiles on the matrix cores, the k + 1 best rows by
-//                     (key, row), and Algorithm 2's class updates
-//   k_refine<OpFP8>   the same up to the FP8 candidates (the 4k best rows), for
+//                     best tiles, the k + 1 best rows by (key, row), and
+//                     Algorithm 2's class updates
+//   k_refine_fp8<Op>  the same up to the FP8 candidates (the 4k best rows), for
 //                     the exact re-rank in rerank.hip
 //
 // A wave recomputes two tiles per step, one row per lane.  INT8 and 16-bit rows
 // are dotted with the query on the vector units (v_dot4 / v_dot2; the query sits
 // in scalar registers): their keys are exact integers in any order.  An FP8 key
-// must have the bits the 32x32 distance kernels gave it, so it comes from their
+// must have the bits the distance kernel gave it, so it comes from that kernel's
 // instruction and operand order, with the query in every column of the block.
 //
 // What bounds it: reading n_need tiles (4-8 KB each) per query from L2 and the
@@ -22,13 +22,20 @@
 namespace lnbnn {
 
 // The query as the row arithmetic of its format wants it, and one row's key
-// part per lane.
+// part per lane: rows() takes two tiles, lane l row row_in(l) of the first one
+// or, where second(l), of the second.
 template <class Op>
 struct RowDot;
 
+// one row per lane: lanes 0-31 the first tile
+struct RowPerLane {
+    static __device__ __forceinline__ bool second(int lane) { return lane & 32; }
+    static __device__ __forceinline__ int row_in(int lane) { return lane & 31; }
+};
+
 // INT8: D = seed + sum of s * u in 32-bit integers, u = 127 - q as in load_b.
 template <int S, int FMT>
-struct RowDot<OpI8T<S, FMT>> {
+struct RowDot<OpI8T<S, FMT>> : RowPerLane {
     using Op = OpI8T<S, FMT>;
     uint32_t u[8 * S];
     __device__ __forceinline__ RowDot(const RefineArgs &, const void *q_src, int64_t q, int, int)
@@ -39,8 +46,8 @@ struct RowDot<OpI8T<S, FMT>> {
     }
     __device__ __forceinline__ int rows(const RefineArgs &r, int ta, int tb, int lane, int *row) const
     {
-        const int tile = lane < 32 ? ta : tb;
-        *row = tile * kTileRows + (lane & 31);
+        const int tile = second(lane) ? tb : ta;
+        *row = tile * kTileRows + row_in(lane);
         const uint4 *f = r.frag + (int64_t)tile * (S * 64) + (lane & 31);
         uint4 v[2 * S];
 #pragma unroll
@@ -59,7 +66,7 @@ struct RowDot<OpI8T<S, FMT>> {
 
 // 16-bit formats: d' = seed + sum of r * (-2 q) in FP32, exact integers.
 template <class O>
-struct RowDot16 {
+struct RowDot16 : RowPerLane {
     uint32_t u[64];                 // pairs of -2 q in the operand format
     __device__ __forceinline__ RowDot16(const RefineArgs &, const void *q_src, int64_t q, int, int)
     {
@@ -84,8 +91,8 @@ struct RowDot16 {
     }
     __device__ __forceinline__ float rows(const RefineArgs &r, int ta, int tb, int lane, int *row) const
     {
-        const int tile = lane < 32 ? ta : tb;
-        *row = tile * kTileRows + (lane & 31);
+        const int tile = second(lane) ? tb : ta;
+        *row = tile * kTileRows + row_in(lane);
         const uint4 *f = r.frag + (int64_t)tile * (8 * 64) + (lane & 31);
         float d = r.seed[*row];
 #pragma unroll
@@ -107,42 +114,53 @@ struct RowDot16 {
 template <> struct RowDot<OpF16> : RowDot16<OpF16> { using RowDot16<OpF16>::RowDot16; };
 template <> struct RowDot<OpBF16> : RowDot16<OpBF16> { using RowDot16<OpBF16>::RowDot16; };
 
-// FP8: the block instruction of the distance kernels.
-template <>
-struct RowDot<OpFP8> {
-    using Op = OpFP8;
+// FP8: the block instruction of the distance kernel that made the lists, with
+// the query in every column.  The two block shapes sum in different orders
+// (two chained sums of 64 products, or one of 128) and their keys may differ in
+// the last place; a listed key bounds the rows' keys only where both come
+// from one of them.
+template <class Op>
+struct RowDotFP8 {
+    static constexpr int kAcc = Op::kAccN;          // a lane's registers of a tile
     uint4 b[Op::kSteps][Op::kBU];
     int sb;
-    __device__ __forceinline__ RowDot(const RefineArgs &r, const void *q_src, int64_t q, int lane, int)
+    __device__ __forceinline__ RowDotFP8(const RefineArgs &r, const void *q_src, int64_t q, int lane, int)
     {
-        Op::load_b(q_src, r.q_scale, q, true, lane >> 5, b, sb);
+        Op::load_b(q_src, r.q_scale, q, true, lane / Op::kQT, b, sb);
     }
-    __device__ __forceinline__ f32x16 block(const RefineArgs &r, int64_t tile, int lane) const
+    __device__ __forceinline__ typename Op::acc_t block(const RefineArgs &r, int64_t tile, int lane) const
     {
         TileRegs<Op> t;
         tile_load<Op>(r.frag + tile * (Op::kSteps * Op::kAU * 64), reinterpret_cast<const float4 *>(r.seed) + tile * 8,
-                      r.row_scale + tile * kTileRows, lane, lane >> 5, t);
-        f32x16 acc = t.sd;
+                      r.row_scale + tile * kTileRows, lane, lane / Op::kQT, t);
+        typename Op::acc_t acc = t.sd;
 #pragma unroll
         for (int s = 0; s < Op::kSteps; ++s) acc = Op::mma(t.av[s], b[s], acc, t.sa, sb);
         return acc;
     }
+    // lane c + kAcc j + kQT h takes register c of tile j
+    static __device__ __forceinline__ bool second(int lane) { return lane & kAcc; }
+    static __device__ __forceinline__ int row_in(int lane)
+    {
+        const int c = lane & (kAcc - 1);
+        return Op::kRowStride * (c >> 2) + 4 * (lane / Op::kQT) + (c & 3);
+    }
     __device__ __forceinline__ float rows(const RefineArgs &r, int ta, int tb, int lane, int *row) const
     {
-        const f32x16 va = block(r, ta, lane), vb = block(r, tb, lane);
-        // lane c + 16 j + 32 h takes register c of tile j
-        const int c = lane & 15;
-        const bool second = lane & 16;
+        const typename Op::acc_t va = block(r, ta, lane), vb = block(r, tb, lane);
+        const int c = lane & (kAcc - 1);
         float v = va[0];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const float x = second ? vb[i] : va[i];
+        for (int i = 0; i < kAcc; ++i) {
+            const float x = second(lane) ? vb[i] : va[i];
             v = c == i ? x : v;
         }
-        *row = (second ? tb : ta) * kTileRows + 8 * (c >> 2) + 4 * (lane >> 5) + (c & 3);
+        *row = (second(lane) ? tb : ta) * kTileRows + row_in(lane);
         return v;
     }
 };
+template <> struct RowDot<OpFP8> : RowDotFP8<OpFP8> { using RowDotFP8<OpFP8>::RowDotFP8; };
+template <> struct RowDot<OpFP8Q> : RowDotFP8<OpFP8Q> { using RowDotFP8<OpFP8Q>::RowDotFP8; };
 
 // The query's partial lists: slots slot0 .. slot0 + n_lists - 1 (see the walk
 // of k_dist_topk: whole blocks have one, a remaining block one per slice or
@@ -234,7 +252,7 @@ static __device__ __forceinline__ void best_rows(const RefineArgs &r, const floa
         const int ta = __builtin_amdgcn_readfirstlane(tiles[t]);
         const int tb = __builtin_amdgcn_readfirstlane(tiles[min(t + 1, n_tiles - 1)]);
         const typename Op::gate_t v = dot.rows(r, ta, tb, lane, row);
-        const bool second = Op::kScaled ? lane & 16 : lane & 32;
+        const bool second = RowDot<Op>::second(lane);
         const int par = Op::kParity && (second ? tb : ta) >= r.odd_tile0;
         const bool real = Op::kParity ? v < (typename Op::gate_t)(1 << 29) : (float)v < __builtin_inff();
         return real && (!second || t + 1 < n_tiles) ? Op::tile_key(v, par) : __builtin_inff();
@@ -257,9 +275,8 @@ static __device__ __forceinline__ void best_rows(const RefineArgs &r, const floa
         wave_lds_fence();
         for (int t = 0; t < n_tiles; t += 2) {
             const float key = keys[t * 32 + lane];
-            const bool second = Op::kScaled ? lane & 16 : lane & 32;
-            const int in = Op::kScaled ? 8 * ((lane & 15) >> 2) + 4 * (lane >> 5) + (lane & 3) : lane & 31;
-            sel.add(pair_of(key, tiles[min(t + (second ? 1 : 0), n_tiles - 1)] * kTileRows + in), key < __builtin_inff(), lane);
+            const int tile = tiles[min(t + (RowDot<Op>::second(lane) ? 1 : 0), n_tiles - 1)];
+            sel.add(pair_of(key, tile * kTileRows + RowDot<Op>::row_in(lane)), key < __builtin_inff(), lane);
         }
     } else {
         for (int t = 0; t < n_tiles; t += 2) {
@@ -361,7 +378,9 @@ __global__ __launch_bounds__(256) void k_refine(RefineArgs r, FinishArgs a)
     if (table && img >= 0) flush();
 }
 
-// FP8: the n_cand best rows by (key, row), one query per wave.
+// FP8: the n_cand best rows by (key, row), one query per wave.  Op: the block
+// shape of the lists.
+template <class Op>
 __global__ __launch_bounds__(256) void k_refine_fp8(RefineArgs r, RerankArgs a)
 {
     constexpr int CAP = 192;        // 4 * 32 candidates + 64
@@ -373,7 +392,7 @@ __global__ __launch_bounds__(256) void k_refine_fp8(RefineArgs r, RerankArgs a)
     const Walk walk = a.bd->walk;
     for (int64_t q = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(wave); q < n_q; q += (int64_t)gridDim.x * 4) {
         WaveSelect<CAP> sel(s_sel[wave], a.n_cand, ~0ull);
-        best_rows<OpFP8, CAP>(r, a.part_d, a.part_i, a.kp_stride, walk, q, r.q, sel, s_tiles[wave], s_keys[wave], a.status, lane);
+        best_rows<Op, CAP>(r, a.part_d, a.part_i, a.kp_stride, walk, q, r.q, sel, s_tiles[wave], s_keys[wave], a.status, lane);
         for (int j = lane; j < a.n_cand; j += 64) a.cand[q * a.n_cand + j] = j < sel.n ? pair_index(sel.buf[j]) : -1;
         wave_lds_fence();
     }
@@ -394,9 +413,13 @@ hipError_t launch_refine(int fmt, const RefineArgs &r, const FinishArgs &a, int6
     return hipGetLastError();
 }
 
-hipError_t launch_refine_fp8(const RefineArgs &r, const RerankArgs &a, int64_t q_cap, hipStream_t s)
+hipError_t launch_refine_fp8(int qt, const RefineArgs &r, const RerankArgs &a, int64_t q_cap, hipStream_t s)
 {
-    k_refine_fp8<<<grid_for(q_cap, 4, 65536), 256, 0, s>>>(r, a);
+    const int grid = grid_for(q_cap, 4, 65536);
+    if (qt == 16)
+        k_refine_fp8<OpFP8Q><<<grid, 256, 0, s>>>(r, a);
+    else
+        k_refine_fp8<OpFP8><<<grid, 256, 0, s>>>(r, a);
     return hipGetLastError();
 }
 
