@@ -33,16 +33,35 @@ struct RowPerLane {
     static __device__ __forceinline__ int row_in(int lane) { return lane & 31; }
 };
 
+// The N dwords of a query (a wave-uniform address) into scalar registers.  A
+// scalar load drops the two low bits of its address, and a caller's u8 rows may
+// start at any byte: such a query is loaded one dword per lane and read lane by
+// lane.
+template <int N>
+static __device__ __forceinline__ void load_query(const uint8_t *p, int lane, uint32_t (&w)[N])
+{
+    static_assert(N <= 64, "one dword per lane");
+    if (((uintptr_t)p & 3) == 0) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) w[i] = load_uniform(reinterpret_cast<const uint32_t *>(p), i);
+    } else {
+        uint32_t x = 0;
+        if (lane < N) __builtin_memcpy(&x, p + 4 * lane, 4);
+#pragma unroll
+        for (int i = 0; i < N; ++i) w[i] = (uint32_t)__builtin_amdgcn_readlane((int)x, i);
+    }
+}
+
 // INT8: D = seed + sum of s * u in 32-bit integers, u = 127 - q as in load_b.
 template <int S, int FMT>
 struct RowDot<OpI8T<S, FMT>> : RowPerLane {
     using Op = OpI8T<S, FMT>;
     uint32_t u[8 * S];
-    __device__ __forceinline__ RowDot(const RefineArgs &, const void *q_src, int64_t q, int, int)
+    __device__ __forceinline__ RowDot(const RefineArgs &, const void *q_src, int64_t q, int lane)
     {
-        const uint32_t *p = reinterpret_cast<const uint32_t *>(static_cast<const uint8_t *>(q_src) + q * Op::kRow);
+        load_query(static_cast<const uint8_t *>(q_src) + q * Op::kRow, lane, u);
 #pragma unroll
-        for (int i = 0; i < 8 * S; ++i) u[i] = load_uniform(p, i) ^ 0x7f7f7f7fu;
+        for (int i = 0; i < 8 * S; ++i) u[i] ^= 0x7f7f7f7fu;
     }
     __device__ __forceinline__ int rows(const RefineArgs &r, int ta, int tb, int lane, int *row) const
     {
@@ -68,12 +87,13 @@ struct RowDot<OpI8T<S, FMT>> : RowPerLane {
 template <class O>
 struct RowDot16 : RowPerLane {
     uint32_t u[64];                 // pairs of -2 q in the operand format
-    __device__ __forceinline__ RowDot16(const RefineArgs &, const void *q_src, int64_t q, int, int)
+    __device__ __forceinline__ RowDot16(const RefineArgs &, const void *q_src, int64_t q, int lane)
     {
-        const uint32_t *p = reinterpret_cast<const uint32_t *>(static_cast<const uint8_t *>(q_src) + q * kDim);
+        uint32_t raw[32];
+        load_query(static_cast<const uint8_t *>(q_src) + q * kDim, lane, raw);
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            const uint4 w = O::cvt8(make_uint2(load_uniform(p, 2 * i), load_uniform(p, 2 * i + 1)), -2.0f);
+            const uint4 w = O::cvt8(make_uint2(raw[2 * i], raw[2 * i + 1]), -2.0f);
             const uint32_t x[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
             for (int j = 0; j < 4; ++j) u[4 * i + j] = __builtin_amdgcn_readfirstlane(x[j]);
@@ -124,7 +144,7 @@ struct RowDotFP8 {
     static constexpr int kAcc = Op::kAccN;          // a lane's registers of a tile
     uint4 b[Op::kSteps][Op::kBU];
     int sb;
-    __device__ __forceinline__ RowDotFP8(const RefineArgs &r, const void *q_src, int64_t q, int lane, int)
+    __device__ __forceinline__ RowDotFP8(const RefineArgs &r, const void *q_src, int64_t q, int lane)
     {
         Op::load_b(q_src, r.q_scale, q, true, lane / Op::kQT, b, sb);
     }
@@ -246,7 +266,7 @@ static __device__ __forceinline__ void best_rows(const RefineArgs &r, const floa
     // than that are needed, no row above tau is
     const bool bounded = n_tiles == r.n_need && need_rows <= r.n_need && !__builtin_isnan(tau);
     sel = WaveSelect<CAP>(sel.buf, need_rows, bounded ? pair_of(tau, 0x7fffffff) : ~0ull);
-    const RowDot<Op> dot(r, q_src, q, lane, 0);
+    const RowDot<Op> dot(r, q_src, q, lane);
     // the 64 rows of tiles t and t + 1, one per lane; +inf where there is none
     auto rows = [&](int t, int *row) -> float {
         const int ta = __builtin_amdgcn_readfirstlane(tiles[t]);
