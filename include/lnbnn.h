@@ -114,7 +114,8 @@ enum {
  * nearest-neighbour index over the descriptors of all classes; its second:
  * the class lookup Class(p), Sec. 6.1's per-descriptor "accessory data").
  *
- *   refs       [n_refs, dim] LNBNN_U8 (values 0..255) or LNBNN_F32
+ *   refs       [n_refs, dim] LNBNN_U8 (values 0..255) or LNBNN_F32 (a row with a
+ *              NaN or an infinity is no query's neighbour)
  *   dim        LNBNN_DIM, or LNBNN_DIM_LOC with U8 data and mode_mask =
  *              LNBNN_MODE_BIT(LNBNN_EXACT_I8) (queries then carry 160 bytes)
  *   labels     [n_refs] int32 class of every reference, in [0, n_classes)

@@ -35,6 +35,10 @@ static __device__ __forceinline__ uint32_t fp8x2(float a, float b)
     return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(a, b, 0, false) & 0xffffu;
 }
 
+// Seed (squared norm) and E8M0 exponent of every row.  A reference with a NaN or
+// an infinity, or whose squared norm overflows, is packed like a padding row (seed
+// +inf, zero codes), which no key passes: a NaN key would hide the other rows of
+// its tile, whose smallest key it makes NaN.
 __global__ void k_fp8_rowprep(const float *__restrict__ refs, int64_t n_refs, int64_t n_pad,
                               int32_t *__restrict__ rsc, float *__restrict__ seed)
 {
@@ -47,11 +51,13 @@ __global__ void k_fp8_rowprep(const float *__restrict__ refs, int64_t n_refs, in
         }
         const float4 *p = reinterpret_cast<const float4 *>(refs + row * kDim);
         float m = 0.0f;
+        bool finite = true;
         for (int c = 0; c < kDim / 4; ++c) {
             const float4 v = p[c];
             m = fmaxf(m, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
+            finite = finite && isfinite(v.x) && isfinite(v.y) && isfinite(v.z) && isfinite(v.w);
         }
-        const int e = fp8_exponent(m);
+        const int e = finite ? fp8_exponent(m) : 0;
         // ||r~||^2 of the dequantised values r~ = fp8(r * 2^e) * 2^-e
         float s = 0.0f;
         for (int c = 0; c < kDim / 4; ++c) {
@@ -69,14 +75,15 @@ __global__ void k_fp8_rowprep(const float *__restrict__ refs, int64_t n_refs, in
             s = fmaf(r3, r3, s);
         }
         rsc[row] = 127 - e;
-        seed[row] = s;
+        seed[row] = finite && isfinite(s) ? s : __builtin_inff();
     }
 }
 
 // Fragment u = ((tile * 2 + s) * 2 + half) * 64 + lane: 16 codes of row
 // 32*tile + (lane & 31), K elements 64*s + 32*(lane >> 5) + 16*half + 0..15.
 __global__ void k_fp8_pack(const float *__restrict__ refs, int64_t n_refs, int64_t n_frag,
-                           const int32_t *__restrict__ rsc, uint4 *__restrict__ frag)
+                           const int32_t *__restrict__ rsc, const float *__restrict__ seed,
+                           uint4 *__restrict__ frag)
 {
     for (int64_t u = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; u < n_frag;
          u += (int64_t)gridDim.x * blockDim.x) {
@@ -86,7 +93,7 @@ __global__ void k_fp8_pack(const float *__restrict__ refs, int64_t n_refs, int64
         const int64_t tile = u >> 8;
         const int64_t row = tile * kTileRows + (lane & 31);
         uint4 out = make_uint4(0u, 0u, 0u, 0u);
-        if (row < n_refs) {
+        if (row < n_refs && seed[row] < __builtin_inff()) {
             const int e = 127 - rsc[row];
             const float4 *p = reinterpret_cast<const float4 *>(refs + row * kDim + 64 * s + 32 * (lane >> 5) + 16 * half);
             uint32_t w[4];
@@ -344,7 +351,7 @@ hipError_t launch_fp8_index(const float *refs, int64_t n_refs, int64_t n_pad, ui
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int64_t n_frag = (n_pad / kTileRows) * 4 * 64;
-    k_fp8_pack<<<grid_for(n_frag, 256, 65536), 256, 0, s>>>(refs, n_refs, n_frag, rsc, frag);
+    k_fp8_pack<<<grid_for(n_frag, 256, 65536), 256, 0, s>>>(refs, n_refs, n_frag, rsc, seed, frag);
     return hipGetLastError();
 }
 
