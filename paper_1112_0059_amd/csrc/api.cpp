@@ -430,7 +430,9 @@ static bool variant_serves(int v, int mode, int fmt, int kp)
     return !(variant(v).pl && mode == LNBNN_FP8_RERANK_2K);
 }
 
-static int default_variant(int mode, int fmt, int kp, bool over, int64_t n_tiles, int64_t n_q, int cu_count)
+// max_lists = 1: the caller's buffers hold one list per query and no more.
+static int default_variant(int mode, int fmt, int kp, bool over, int64_t n_tiles, int64_t n_q, int max_lists,
+                           int cu_count)
 {
     // Shared lists of tiles wherever the rule allows them.  16x16 blocks (64
     // queries per wave on four query tiles) beat 32x32 pair lists at every batch
@@ -464,8 +466,9 @@ static int default_variant(int mode, int fmt, int kp, bool over, int64_t n_tiles
     if (mode == LNBNN_FP8_RERANK_2K) return b <= 40 ? 11 : 0;
     // an FP8 index of no more tiles than the list holds: every tile would be
     // recomputed for every query, so short lists of rows are the better ones
-    // (600 references, 64,000 descriptors, k = 5: 379 us against 516)
-    if (b <= 20 && n_tiles <= kp) return 0;
+    // (600 references, 64,000 descriptors, k = 5: 379 us against 516) where
+    // two lists per query fit
+    if (b <= 20 && n_tiles <= kp && max_lists > 1) return 0;
     // 44-64 entries (k = 11..16): one wave per SIMD, 77 ms against 253 on
     // per-half lists for 18,000 descriptors over 15.36M references, k = 16;
     // beyond k = 16 the rule itself is that of per-half lists
@@ -494,7 +497,8 @@ int make_plan(lnbnn_index *ix, int mode, int k, int64_t q_cap, int64_t n_q, int 
         if (it != ix->pinned.end() && q_cap >= it->second.min_q) tu = it->second.t;
     }
     const int64_t n_tiles = ix->rows[fmt] / kTileRows;
-    const int v = tu.variant >= 0 ? tu.variant : default_variant(mode, fmt, kp, over, n_tiles, n_q, ix->cu_count);
+    const int v = tu.variant >= 0 ? tu.variant
+                                  : default_variant(mode, fmt, kp, over, n_tiles, n_q, max_lists, ix->cu_count);
     if (!variant_serves(v, mode, fmt, kp))
         return set_err(LNBNN_EINVAL, "variant %d cannot serve mode %d with k + 1 = %d", v, mode, kp);
     const Variant var = variant(v);

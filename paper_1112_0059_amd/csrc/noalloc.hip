@@ -111,8 +111,9 @@ extern "C" int lnbnn_classify_noalloc(lnbnn_index *ix, const void *queries_dev, 
         int32_t *upd_cls = fp8 ? c.take<int32_t>(q_cap * k) : nullptr;
         double *upd_delta = fp8 ? c.take<double>(q_cap * k) : nullptr;
         if (pass == 0) {
-            if (c.used > kScratchBytes && plan.pl && plan.max_lists > 1) {
+            if (c.used > kScratchBytes && plan.max_lists > 1) {
                 // fewer partial lists: at most as many as the other plans, then none but the blocks' own
+                // (and no shape that keeps several per query)
                 if ((rc = make_plan(ix, mode, k, q_cap, n_q, plan.max_lists > kMaxLists ? kMaxLists : 1, &plan)))
                     return rc;
                 part = batch_elems(ix, plan, q_cap);

@@ -201,7 +201,8 @@ int mode_fmt(int mode);
 bool is_fp8_mode(int mode);
 int index_fmt(const lnbnn_index *ix, int mode);   // mode_fmt, with the 160-element INT8 tiles where they apply
 // Plan for a batch of n_q queries in buffers of q_cap.  max_lists: most
-// partial lists per query of a shared-list plan (1: no block is split).
+// partial lists per query of a shared-list plan (1: no block is split, and no
+// default shape keeps several lists per query where one would do).
 int make_plan(lnbnn_index *ix, int mode, int k, int64_t q_cap, int64_t n_q, int max_lists, Plan *out);
 // Elements of part_d / part_i the plan's batch needs (the lists, or the
 // original NBNN mode's per-class minima), and the most that any batch of up to
