@@ -453,7 +453,9 @@ static int default_variant(int mode, int fmt, int kp, bool over, int64_t n_tiles
         const int64_t b512 = (n_q + 511) / 512, b1024 = (n_q + 1023) / 1024;
         const int64_t piece = b1024 < cu_count ? n_tiles * b1024 / cu_count : n_tiles;
         const bool halves = b1024 * 200 <= b512 * 106 && variant_supports(28, fmt, kp);
-        if (fmt == FMT_I8N) return halves ? 28 : 15;
+        // (Algorithm 1 on fewer than 64 tiles, too few to cut for idle CUs: 600
+        // references, 64,000 descriptors 74 us with halves, 63 without)
+        if (fmt == FMT_I8N) return halves && n_tiles >= 64 ? 28 : 15;
         return halves && piece >= 8192 ? 28 : 25;
     }
     if (fmt == FMT_I8L) return 19;
@@ -521,23 +523,36 @@ int make_plan(lnbnn_index *ix, int mode, int k, int64_t q_cap, int64_t n_q, int 
         // remaining blocks, cut into slices or equal runs (see k_dist_topk).
         // Every piece costs its tiles and the start of a fresh list, about
         // kStart tiles' time (nearly every tile inserts until 64 k tiles are
-        // seen).  K rounds of (block, slice) items: K x (tiles per slice +
-        // start).  Runs: one piece, or two where a block ends inside, per
+        // seen; the original NBNN has no list, only its queries to load and
+        // its minima to flush: 6,000 references of two classes, 100,000
+        // descriptors 188 us at 128 tiles, 131 at 64, 126 at 32, where batches of
+        // 200,000 lose 4 %).  K rounds of (block, slice) items: K x (tiles per
+        // slice + start).  Runs: one piece, or two where a block ends inside, per
         // workgroup, whatever R is; but each workgroup then reads other tiles
         // at any time, and the L2 and the infinity cache serve nobody twice
         // (kRunCost).  Without a cut a batch just past a multiple of 256 blocks
         // ran one more whole round: 563 blocks of 512 queries over 15.36M
         // references took 526 ms instead of 431 ms.
-        constexpr double kStart = 128, kRunCost = 1.08;
+        const double kStart = fmt == FMT_I8N ? 64 : 128;
+        constexpr double kRunCost = 1.08;
         const int64_t n_qb = std::max<int64_t>(1, (n_q + qb - 1) / qb);
         const int64_t grid = resident, full = n_qb / grid, rem = n_qb % grid;
         int64_t slices = rem > 0 ? 1 : 0, tiles = n_tiles, pieces = rem;
         if (rem > 0 && max_lists > 1) {
-            double best = (double)n_tiles;
+            // Up to an eighth of the grid in blocks: a sweep of few tiles is
+            // nothing but list start, cut or not (each tile inserts, about three
+            // tiles' time), and its latency is all there is: 2,000 descriptors
+            // against 3,000 FP16 references, k = 10, 76 us in slices of 8 of the 96
+            // tiles, 160 in one sweep.  With more blocks the second list of every
+            // query costs more than that gains (INT8, 64,000 descriptors, 2,000
+            // references, k = 10: 191 us whole, 247 in two slices).
+            const bool few = fmt != FMT_I8N && rem * 8 <= grid;
+            auto piece = [&](double t) { return t + (few ? std::min(2 * t, kStart) : kStart); };
+            double best = few ? piece((double)n_tiles) : (double)n_tiles;
             for (int64_t rounds = 1; rounds <= cut_rounds(rem, grid); ++rounds) {
                 const int64_t t = up8((n_tiles + rounds * grid / rem - 1) / (rounds * grid / rem));
                 const int64_t n = (n_tiles + t - 1) / t;
-                const double cost = (double)((rem * n + grid - 1) / grid) * ((double)t + kStart);
+                const double cost = (double)((rem * n + grid - 1) / grid) * piece((double)t);
                 if (n > 1 && n <= max_lists && cost < best) {
                     best = cost;
                     slices = n;
