@@ -430,10 +430,50 @@ static bool variant_serves(int v, int mode, int fmt, int kp)
     return !(variant(v).pl && mode == LNBNN_FP8_RERANK_2K);
 }
 
-// max_lists = 1: the caller's buffers hold one list per query and no more.
-static int default_variant(int mode, int fmt, int kp, bool over, int64_t n_tiles, int64_t n_q, int max_lists,
-                           int cu_count)
+// Variant with per-lane-group lists of rows for an exact search of a small index,
+// or -1 where lists of tiles are faster.  k_refine costs every query about the same
+// (1 ns and more in a large batch at k = 1), while row lists cost it an insertion
+// path that grows with the references seen, and that is latency where a batch does
+// not fill the chip.  So the line lies at a number of references that falls with the
+// list length and rises with the batch.  Rows against tiles, microseconds a call
+// (references x descriptors):
+//   FP16  k = 1:  3,000 x 128,000 196 / 232; 6,000 x 64,000 187 / 225, x 128,000 291 / 290
+//         k = 2:  600 x 30,000 92 / 110, 3,000 169 / 168
+//         k = 5:  1,000 x 64,000 155 / 180, x 30,000 131 / 129; 2,000 x 128,000 305 / 316
+//         k = 10: 1,000 x 64,000 240 / 269; 2,000 x 128,000 496 / 499
+//         k = 15: 1,000 x 128,000 489 / 590; 600 x 64,000 280 / 320
+//   INT8  k = 1:  1,000 x 30,000 65 / 81; 1,000 x 128,000 125 / 143, 3,000 214 / 167
+//         k = 10: 300 x 128,000 205 / 284, 600 276 / 284; 300 x 64,000 148 / 166
+//         k = 15: 300 x 128,000 288 / 300, 600 385 / 355
+// Lists of 21 and 33 stay on tiles (FP16, k = 32, 1,000 x 128,000: 1,106 us, every
+// tile recomputed for every query, against 1,270).
+static int row_list_variant(int fmt, int kp, int b, int64_t n_refs, int64_t n_q)
 {
+    const bool q1 = n_q >= 1000, q20 = n_q >= 20000, q50 = n_q >= 50000, q100 = n_q >= 100000;
+    int64_t most = 0;           // references
+    if (fmt == FMT_F16 || fmt == FMT_BF16) {
+        if (b <= 2) most = q100 ? 4500 : q50 ? 6400 : 3200;
+        else if (kp == 3) most = q50 ? 1500 : q20 ? 3200 : 0;
+        else if (b <= 6) most = q100 ? 2100 : q50 ? 1500 : q20 ? 700 : 0;
+        else if (b <= 11) most = q50 ? 1100 : 0;
+        else if (b <= 16) most = q100 ? 1100 : q50 ? 700 : 0;
+        return n_refs > most ? -1 : b <= 2 && !q100 ? 6 : 2;
+    }
+    if (b <= 2) most = q100 ? 1100 : q1 ? 3200 : 0;
+    else if (b <= 11) most = q100 ? 640 : q50 ? 320 : 0;
+    else if (b <= 16) most = q100 ? 320 : 0;
+    return n_refs > most ? -1 : q100 ? 2 : 11;
+}
+
+// max_lists = 1: the caller's buffers hold one list per query and no more.
+static int default_variant(int mode, int fmt, int kp, bool over, int64_t n_refs, int64_t n_tiles, int64_t n_q,
+                           int max_lists, int cu_count)
+{
+    const int b = kp_bucket(kp, fmt);
+    if (!is_fp8_mode(mode) && fmt != FMT_I8N && max_lists > 1) {
+        const int v = row_list_variant(fmt, kp, b, n_refs, n_q);
+        if (v >= 0) return v;
+    }
     // Shared lists of tiles wherever the rule allows them.  16x16 blocks (64
     // queries per wave on four query tiles) beat 32x32 pair lists at every batch
     // size measured: INT8, one image of 2,251 descriptors against 15.36M
@@ -460,7 +500,6 @@ static int default_variant(int mode, int fmt, int kp, bool over, int64_t n_tiles
     }
     if (fmt == FMT_I8L) return 19;
     if (fmt == FMT_F16 || fmt == FMT_BF16) return 26;
-    const int b = kp_bucket(kp, fmt);
     // the union-of-halves rule keeps per-half lists of rows, whose insertions are
     // most of its time over short slices: one query tile per wave (no spills)
     // beats two, 24.2 ms against 30.1 for 48,000 descriptors over 2.27M
@@ -500,7 +539,8 @@ int make_plan(lnbnn_index *ix, int mode, int k, int64_t q_cap, int64_t n_q, int 
     }
     const int64_t n_tiles = ix->rows[fmt] / kTileRows;
     const int v = tu.variant >= 0 ? tu.variant
-                                  : default_variant(mode, fmt, kp, over, n_tiles, n_q, max_lists, ix->cu_count);
+                                  : default_variant(mode, fmt, kp, over, ix->n_refs, n_tiles, n_q, max_lists,
+                                                    ix->cu_count);
     if (!variant_serves(v, mode, fmt, kp))
         return set_err(LNBNN_EINVAL, "variant %d cannot serve mode %d with k + 1 = %d", v, mode, kp);
     const Variant var = variant(v);
@@ -546,7 +586,9 @@ int make_plan(lnbnn_index *ix, int mode, int k, int64_t q_cap, int64_t n_q, int 
             // tiles, 160 in one sweep.  With more blocks the second list of every
             // query costs more than that gains (INT8, 64,000 descriptors, 2,000
             // references, k = 10: 191 us whole, 247 in two slices).
-            const bool few = fmt != FMT_I8N && rem * 8 <= grid;
+            // 16 tiles are too few to be worth it (INT8, 300 references, 12,000
+            // descriptors, k = 5: 68 us whole, 74 in two).
+            const bool few = fmt != FMT_I8N && rem * 8 <= grid && n_tiles > 16;
             auto piece = [&](double t) { return t + (few ? std::min(2 * t, kStart) : kStart); };
             double best = few ? piece((double)n_tiles) : (double)n_tiles;
             for (int64_t rounds = 1; rounds <= cut_rounds(rem, grid); ++rounds) {

@@ -140,9 +140,13 @@ static int setup_slot(Server *sv, Slot *sl)
         if (!(ix->modes & LNBNN_MODE_BIT(mode))) continue;
         for (int k = 1; k <= kmax; ++k) {
             for (int64_t q = 1024; ; q = std::min(cap, q * 2)) {
-                Plan p;
-                if (make_plan(ix, mode, k, std::min(q, cap), std::min(q, cap), slot_lists(cap), &p) == LNBNN_OK)
-                    part = std::max(part, work_elems(ix, p, cap));
+                // both ends of the bucket: the shape also follows the batch's own size
+                for (int64_t n_q : {std::min(q, cap), q / 2 + 1, int64_t(1)}) {
+                    Plan p;
+                    if (n_q <= std::min(q, cap) &&
+                        make_plan(ix, mode, k, std::min(q, cap), n_q, slot_lists(cap), &p) == LNBNN_OK)
+                        part = std::max(part, work_elems(ix, p, cap));
+                }
                 if (q >= cap) break;
             }
         }
