@@ -592,10 +592,13 @@ int make_plan(lnbnn_index *ix, int mode, int k, int64_t q_cap, int64_t n_q, int 
             auto piece = [&](double t) { return t + (few ? std::min(2 * t, kStart) : kStart); };
             double best = few ? piece((double)n_tiles) : (double)n_tiles;
             for (int64_t rounds = 1; rounds <= cut_rounds(rem, grid); ++rounds) {
-                const int64_t t = up8((n_tiles + rounds * grid / rem - 1) / (rounds * grid / rem));
+                // as many slices as fill the rounds, or as a query may have lists
+                // (three blocks in at most 64 lists each: 192 of 256 workgroups)
+                const int64_t most = std::min<int64_t>(rounds * grid / rem, max_lists);
+                const int64_t t = up8((n_tiles + most - 1) / most);
                 const int64_t n = (n_tiles + t - 1) / t;
                 const double cost = (double)((rem * n + grid - 1) / grid) * piece((double)t);
-                if (n > 1 && n <= max_lists && cost < best) {
+                if (n > 1 && cost < best) {
                     best = cost;
                     slices = n;
                     tiles = t;
