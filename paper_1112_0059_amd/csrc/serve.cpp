@@ -53,6 +53,7 @@ struct Request {
 struct Slot {
     hipStream_t stream = nullptr;
     hipEvent_t done = nullptr;
+    hipEvent_t computed = nullptr; // the batch's kernels have run (its results are still to be copied)
     Workspace ws;
     uint8_t *h_q = nullptr;        // pinned staging
     int64_t *h_off = nullptr;
@@ -81,6 +82,7 @@ struct Server {
     std::unordered_map<uint64_t, Request *> reqs;
     std::deque<Slot *> inflight;
     std::vector<Slot *> slots;
+    Slot *last = nullptr;                 // slot of the last batch launched (scheduler thread)
     std::thread sched, compl_thr;
     uint64_t next_ticket = 1;
     int64_t next_batch = 0;
@@ -132,6 +134,7 @@ static int setup_slot(Server *sv, Slot *sl)
     const int64_t cap = sv->max_batch_desc, img = sv->max_images;
     LN_HIP(hipStreamCreateWithFlags(&sl->stream, hipStreamNonBlocking));
     LN_HIP(hipEventCreateWithFlags(&sl->done, hipEventDisableTiming));
+    LN_HIP(hipEventCreateWithFlags(&sl->computed, hipEventDisableTiming));
     sl->ws.device = ix->device;
     const int kmax = fp8 ? kMaxFp8K : LNBNN_MAX_K;
     // partial lists: the largest layout any (mode, k, batch bucket) plans
@@ -170,8 +173,13 @@ static void free_slot(Slot *sl)
     if (sl->h_cls) (void)hipHostFree(sl->h_cls);
     if (sl->h_tot) (void)hipHostFree(sl->h_tot);
     if (sl->done) (void)hipEventDestroy(sl->done);
+    if (sl->computed) (void)hipEventDestroy(sl->computed);
     if (sl->stream) (void)hipStreamDestroy(sl->stream);
 }
+
+// Descriptors x references from which a batch waits for the kernels of the batch
+// before it (see launch_slot): about 0.2 ms of sweep.
+constexpr int64_t kOrderedWork = int64_t(1) << 31;
 
 // Enqueue one batch on a slot (the slot's requests are in sl->batch).
 static int launch_slot(Server *sv, Slot *sl)
@@ -224,7 +232,16 @@ static int launch_slot(Server *sv, Slot *sl)
     plan.q_cap = sv->max_batch_desc;
     if (work_elems(ix, plan, plan.q_cap) > ws.part_cap)
         return set_err(LNBNN_EINVAL, "launch tuning changed after the serving loop sized its buffers");
+    // A sweep takes all LDS and most registers of every compute unit, so the
+    // short kernels that finish the batch before (k_refine, the FP8 re-rank and
+    // sums) could not start beside it: that batch would be published a whole
+    // sweep late.  So a sweep of any length waits for them; uploads and the batch
+    // descriptor do not.
+    if (sv->last && sv->last != sl && n_q * ix->n_refs >= kOrderedWork)
+        LN_HIP(hipStreamWaitEvent(sl->stream, sv->last->computed, 0));
     if ((rc = launch_graph(sl->graphs, sl->graph_clock, ix, plan, io, sl->stream))) return rc;
+    LN_HIP(hipEventRecord(sl->computed, sl->stream));
+    sv->last = sl;
     LN_HIP(hipMemcpyAsync(sl->h_cls, ws.cls, (size_t)n_img * 4, hipMemcpyDeviceToHost, sl->stream));
     LN_HIP(hipMemcpyAsync(sl->h_tot, fp8 ? (const void *)ws.totals_f64 : (const void *)ws.totals,
                           (size_t)(n_img * ix->n_classes * 8), hipMemcpyDeviceToHost, sl->stream));
