@@ -259,8 +259,8 @@ int lnbnn_last_timing(const lnbnn_index *ix, lnbnn_timing *out);
 
 /*
  * Project autotuner for the batched launch: times every kernel variant that
- * can serve (mode, k) on the given query batch (same arguments as a
- * LNBNN_DEVICE_PTRS classify without outputs), then chunk lengths of the
+ * can serve (mode, k), by its whole launch sequence, on the given query batch
+ * (same arguments as a LNBNN_DEVICE_PTRS classify without outputs), then chunk lengths of the
  * chunk-major walk (lnbnn_tuning.chunk_tiles) for the two fastest, and keeps
  * the fastest setting for this index, keyed by (arch, n_refs, dim, k bucket,
  * mode).  The setting applies to batches of comparable size: those whose

@@ -1603,20 +1603,26 @@ extern "C" int lnbnn_autotune(lnbnn_index *ix, const void *queries_dev, int dtyp
     int32_t *d_cls = nullptr;
     // stream-ordered: freeing it does not synchronise the device
     LN_HIP(hipMallocAsync((void **)&d_cls, std::max<int32_t>(1, n_images) * 4, ts));
-    // distance-kernel time of one (variant, chunk) setting: mean of two runs
-    // after one warm-up run
+    // time of the whole launch sequence with one (variant, chunk) setting: mean of
+    // two runs after one warm-up run.  (Not the distance kernel's alone: shared
+    // lists leave the rows of the best tiles to the kernel after it.)
     auto time_setting = [&](int v, int chunk, double *ms) {
         lnbnn_tuning t{v, chunk, 0};
         int r = lnbnn_set_tuning(ix, mode, k, &t);
-        double tot = 0;
+        double tot = 0, dist = 0;
         for (int rep = 0; rep < 3 && !r; ++rep) {
             r = lnbnn_classify(ix, queries_dev, dtype, img_offsets, n_images, k, mode,
                                LNBNN_DEVICE_PTRS | LNBNN_NO_GRAPH | LNBNN_TIMING, d_cls, nullptr, nullptr, nullptr,
                                stream);
-            if (!r && rep > 0) tot += ix->last_timing.dist_kernel_ms;
+            if (!r && rep > 0) {
+                tot += ix->last_timing.total_ms;
+                dist += ix->last_timing.dist_kernel_ms;
+            }
         }
         *ms = tot / 2;
-        if (!r) log_line("tuner: mode %d, k %d: %s, chunk %d: %.2f ms", mode, k, variant_name(v), chunk, *ms);
+        if (!r)
+            log_line("tuner: mode %d, k %d: %s, chunk %d: %.2f ms, distance kernel %.2f ms", mode, k, variant_name(v),
+                     chunk, *ms, dist / 2);
         return r;
     };
     // every variant with whole-slice sweeps, then chunk lengths (chunk-major
