@@ -715,8 +715,9 @@ int64_t work_elems(const lnbnn_index *ix, const Plan &p, int64_t q_cap)
         const int64_t pieces = std::max<int64_t>(cut_rounds(rem, p.grid) * p.grid, rem + p.grid);
         return (n_qb / p.grid * p.grid + std::min<int64_t>(pieces, rem * p.max_lists)) * block;
     };
-    // INT8 batches of other sizes may take the shape with larger blocks
-    return std::max(lists(p.block), p.fmt == FMT_I8 ? lists(1024) : 0) * p.kpb;
+    // INT8 batches of other sizes may take the shape with larger blocks, where
+    // the list length has it
+    return std::max(lists(p.block), p.fmt == FMT_I8 && variant_supports(28, p.fmt, p.kpb) ? lists(1024) : 0) * p.kpb;
 }
 
 int enqueue_batch(lnbnn_index *ix, const Plan &p, const BatchIO &io, hipStream_t s, hipEvent_t *kev)
