@@ -146,8 +146,13 @@ int lnbnn_build_index(const void *refs, int dtype, int64_t n_refs, int32_t dim,
 /* Release an index and every device buffer it owns.  EBUSY while serving
  * tickets are pending (nothing is freed then).  NULL is accepted.  Up to 1 GiB
  * of released buffers per process stays allocated for the next index (given
- * back to the device when an allocation fails). */
+ * back to the device by lnbnn_trim, and when an allocation of the library fails;
+ * the default serving budget counts them as free memory). */
 int lnbnn_index_free(lnbnn_index *ix);
+
+/* Give the buffers kept from released indexes back to the device, for other
+ * users of its memory.  Always LNBNN_OK. */
+int lnbnn_trim(void);
 
 /* Basic facts of an index (any pointer may be NULL). */
 int lnbnn_index_info(const lnbnn_index *ix, int64_t *n_refs, int32_t *n_classes,

@@ -95,6 +95,7 @@ def load():
         "lnbnn_build_index": ([P, ctypes.c_int, i64, i32, P, i32, u32, i64, u32, P,
                                ctypes.POINTER(P)], ctypes.c_int),
         "lnbnn_index_free": ([P], ctypes.c_int),
+        "lnbnn_trim": ([], ctypes.c_int),
         "lnbnn_index_info": ([P, P, P, P, P], ctypes.c_int),
         "lnbnn_index_stream": ([P, ctypes.POINTER(P)], ctypes.c_int),
         "lnbnn_classify": ([P, P, ctypes.c_int, P, i32, i32, ctypes.c_int, u32, P, P, P, P, P],
@@ -241,6 +242,11 @@ def lnbnn_build_index(refs, labels, n_classes: int, mode_mask: int, hbm_budget_b
 
 def lnbnn_index_free(ix: Index):
     ix.free()
+
+
+def lnbnn_trim():
+    """Give device buffers kept from freed indexes back to the device."""
+    _check(load().lnbnn_trim())
 
 
 def lnbnn_index_info(ix: Index) -> dict:

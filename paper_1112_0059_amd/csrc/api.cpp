@@ -172,6 +172,29 @@ void dfree(void *p)
     drop_kept_locked(kKeptBytes);
 }
 
+// Stream-ordered allocation; the kept buffers make room for it too.
+static hipError_t dmalloc_async(void **p, size_t bytes, hipStream_t s)
+{
+    hipError_t e = hipMallocAsync(p, bytes, s);
+    if (e != hipErrorOutOfMemory) return e;
+    (void)hipGetLastError();
+    {
+        std::lock_guard<std::mutex> lock(g_kept_mu);
+        drop_kept_locked(0);
+    }
+    return hipMallocAsync(p, bytes, s);
+}
+
+// Bytes kept on a device: free for the next index, though the driver counts
+// them as used.
+static size_t kept_bytes(int device)
+{
+    std::lock_guard<std::mutex> lock(g_kept_mu);
+    size_t n = 0;
+    for (const KeptBlock &b : g_kept) n += b.device == device ? b.bytes : 0;
+    return n;
+}
+
 int64_t row_bytes(int dtype, int dim) { return dtype == LNBNN_U8 ? dim : (int64_t)dim * 4; }
 
 int mode_fmt(int mode)
@@ -892,7 +915,7 @@ static int build_nbnn_layout(lnbnn_index *ix, const uint8_t *d_refs, const int32
     std::vector<uint8_t> par(ix->n_refs);
     {
         uint8_t *d_par = nullptr;
-        LN_HIP(hipMallocAsync((void **)&d_par, std::max<int64_t>(1, ix->n_refs), s));
+        LN_HIP(dmalloc_async((void **)&d_par, std::max<int64_t>(1, ix->n_refs), s));
         hipError_t e = launch_row_parity(d_refs, ix->n_refs, kDim, d_par, s);
         if (e == hipSuccess) e = hipMemcpyAsync(par.data(), d_par, ix->n_refs, hipMemcpyDeviceToHost, s);
         (void)hipFreeAsync(d_par, s);
@@ -922,7 +945,7 @@ static int build_nbnn_layout(lnbnn_index *ix, const uint8_t *d_refs, const int32
     if ((rc = grow(ix, (void **)&iseed, n_nb, 4))) return rc;
     ix->seed[FMT_I8N] = reinterpret_cast<float *>(iseed);
     *bytes = n_nb * (kDim + 4) + n_nb / kTileRows * 4;
-    LN_HIP(hipMallocAsync((void **)&d_perm, n_nb * 4, s));
+    LN_HIP(dmalloc_async((void **)&d_perm, n_nb * 4, s));
     hipError_t e = hipMemcpyAsync(d_perm, h.perm.data(), n_nb * 4, hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
         e = hipMemcpyAsync(ix->tile_class, h.tile_class.data(), h.tile_class.size() * 4, hipMemcpyHostToDevice, s);
@@ -1068,7 +1091,7 @@ extern "C" int lnbnn_build_index(const void *refs, int dtype, int64_t n_refs, in
         d_refs = ix->ref_f32;
     } else if (!dev_in) {
         // stream-ordered staging: freeing it does not synchronise the device
-        hipError_t e = fault_injected("alloc") ? hipErrorOutOfMemory : hipMallocAsync(&staged, (size_t)rbytes, s);
+        hipError_t e = fault_injected("alloc") ? hipErrorOutOfMemory : dmalloc_async(&staged, (size_t)rbytes, s);
         if (e != hipSuccess) return fail(hip_err(e, "hipMallocAsync(staging)"));
         e = hipMemcpyAsync(staged, refs, (size_t)rbytes, hipMemcpyHostToDevice, s);
         if (e != hipSuccess) {
@@ -1132,6 +1155,7 @@ extern "C" int lnbnn_build_index(const void *refs, int dtype, int64_t n_refs, in
     size_t free_b = 0, total_b = 0;
     LN_HIP(hipMemGetInfo(&free_b, &total_b));
     const int64_t env_b = env_budget();
+    free_b += kept_bytes(dev);
     ix->hbm_budget = hbm_budget_bytes ? hbm_budget_bytes : env_b ? env_b : (int64_t)(free_b / 4);
     log_line("index built: %lld references, dim %d, %d classes, modes 0x%x, %lld device bytes, serving budget %lld bytes",
              (long long)ix->n_refs, ix->dim, ix->n_classes, ix->modes, (long long)ix->device_bytes,
@@ -1163,6 +1187,13 @@ extern "C" int lnbnn_index_free(lnbnn_index *ix)
     free_index_buffers(ix);
     free_index_handles(ix);
     delete ix;
+    return LNBNN_OK;
+}
+
+extern "C" int lnbnn_trim(void)
+{
+    std::lock_guard<std::mutex> lock(g_kept_mu);
+    drop_kept_locked(0);
     return LNBNN_OK;
 }
 
@@ -1603,7 +1634,7 @@ extern "C" int lnbnn_autotune(lnbnn_index *ix, const void *queries_dev, int dtyp
     hipStream_t ts = stream ? (hipStream_t)stream : ix->own_stream;
     int32_t *d_cls = nullptr;
     // stream-ordered: freeing it does not synchronise the device
-    LN_HIP(hipMallocAsync((void **)&d_cls, std::max<int32_t>(1, n_images) * 4, ts));
+    LN_HIP(dmalloc_async((void **)&d_cls, std::max<int32_t>(1, n_images) * 4, ts));
     // time of the whole launch sequence with one (variant, chunk) setting: mean of
     // two runs after one warm-up run.  (Not the distance kernel's alone: shared
     // lists leave the rows of the best tiles to the kernel after it.)
