@@ -145,9 +145,9 @@ int lnbnn_build_index(const void *refs, int dtype, int64_t n_refs, int32_t dim,
 
 /* Release an index and every device buffer it owns.  EBUSY while serving
  * tickets are pending (nothing is freed then).  NULL is accepted.  Up to 1 GiB
- * of released buffers per process stays allocated for the next index (given
- * back to the device by lnbnn_trim, and when an allocation of the library fails;
- * the default serving budget counts them as free memory). */
+ * of released buffers per process stays allocated for the next index of the
+ * same size (given back to the device by lnbnn_trim, and when an allocation of
+ * the library fails; the default serving budget counts them as free memory). */
 int lnbnn_index_free(lnbnn_index *ix);
 
 /* Give the buffers kept from released indexes back to the device, for other

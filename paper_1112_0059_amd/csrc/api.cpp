@@ -133,10 +133,11 @@ static hipError_t dmalloc(void **p, size_t bytes)
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     std::lock_guard<std::mutex> lock(g_kept_mu);
-    // the smallest kept block that fits and wastes at most a quarter
+    // the smallest kept block that fits and is no larger by more than a page:
+    // what callers account for is what they asked for
     size_t best = g_kept.size();
     for (size_t i = 0; i < g_kept.size(); ++i)
-        if (g_kept[i].device == dev && g_kept[i].bytes >= bytes && g_kept[i].bytes <= bytes + bytes / 4 + 4096 &&
+        if (g_kept[i].device == dev && g_kept[i].bytes >= bytes && g_kept[i].bytes <= bytes + 4096 &&
             (best == g_kept.size() || g_kept[i].bytes < g_kept[best].bytes))
             best = i;
     if (best < g_kept.size()) {

@@ -1,5 +1,6 @@
 """Device memory around an index's life: buffers kept after an index is freed are
-neither hidden from the next index's budget nor lost to the rest of the process."""
+neither hidden from the next index's budget nor lost to the rest of the process,
+and a kept buffer is never given out where a smaller one was asked for."""
 import pytest
 
 import paper_1112_0059_amd as L
@@ -48,3 +49,18 @@ def test_kept_buffers_count_as_free_for_the_budget():
         _index(6_000_000).free()
     L.lnbnn_trim()
     assert abs(budgets[0] - budgets[1]) < 32 << 20
+
+
+def test_buffers_are_no_larger_than_asked_for():
+    """An index rebuilt a little smaller holds its own size: the serving slots'
+    accounting counts what was asked for."""
+    _index(5000).free()
+    L.lnbnn_trim()
+    before = _free_bytes()
+    _index(4_000_000).free()
+    ix = _index(3_400_000)
+    L.lnbnn_trim()                           # what is kept beside it
+    held = before - _free_bytes()
+    assert held < L.lnbnn_index_info(ix)["device_bytes"] + (48 << 20)
+    ix.free()
+    L.lnbnn_trim()
