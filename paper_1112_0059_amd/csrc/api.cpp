@@ -1060,7 +1060,12 @@ extern "C" int lnbnn_build_index(const void *refs, int dtype, int64_t n_refs, in
     if ((rc = grow(ixp, (void **)&ix->labels, n_refs + 1, 4))) return fail(rc);
     std::vector<int32_t> hl;           // host copy of device labels (the class-sorted layout)
     if (dev_in) {
-        hipError_t e = hipMemcpyAsync(ix->labels, labels, n_refs * 4, hipMemcpyDeviceToDevice, s);
+        // Device inputs may still be written by work on any of the process's
+        // blocking streams.  What is enqueued on the NULL stream follows them, and
+        // the index's own stream follows that; a caller's needs an event.
+        hipError_t e = hipMemcpyAsync(ix->labels, labels, n_refs * 4, hipMemcpyDeviceToDevice, nullptr);
+        if (e == hipSuccess && s != ix->own_stream) e = hipEventRecord(ix->ws_free, nullptr);
+        if (e == hipSuccess && s != ix->own_stream) e = hipStreamWaitEvent(s, ix->ws_free, 0);
         if (e != hipSuccess) return fail(hip_err(e, "hipMemcpyAsync(labels)"));
         int32_t bad = 0, value = 0;    // first label out of range (n_refs: none), in the spare last element
         e = launch_check_labels(ix->labels, n_refs, n_classes, ix->labels + n_refs, s);
