@@ -696,8 +696,9 @@ int make_plan(lnbnn_index *ix, int mode, int k, int64_t q_cap, int64_t n_q, int 
     // against 7.9.  Lists of 20, whose insertions cost more: slices of 60,000
     // tiles 96 ms against 119, 48,000 tiles 36.5 against 39.6, but 8,900 tiles
     // 28.6 against 22.7.  And for lists of up to 4 where whole slices of 512
-    // queries fill the chip anyway (45,500 descriptors over 97,000 references:
-    // 1.34 against 1.45).  One tile elsewhere: its items are twice as many (one
+    // queries fill the chip anyway (45,500 descriptors over 97,000 references,
+    // k = 1, three indexes in turn: 0.79 against 0.89 a call, though alone 1.23
+    // against 1.09).  One tile elsewhere: its items are twice as many (one
     // image, slices of 2,200 tiles, k = 1: 0.85 against 1.38).  Same slices and
     // lists either way.
     const int64_t settled = kpb <= 8 ? 4096 : 24576;
