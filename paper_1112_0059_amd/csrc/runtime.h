@@ -238,8 +238,8 @@ void drop_graphs(std::map<GraphKey, GraphEntry> &graphs);
 GraphKey graph_key(const Plan &p, const BatchIO &io);
 
 // Frees a device buffer that dmalloc gave out and no work uses any more: it is
-// kept for the next allocation of about its size, up to kKeptBytes per process
-// (oldest freed first; all of it when an allocation fails).  An index that is
+// kept for the next allocation of its size, up to kKeptBytes per process (oldest
+// freed first; all of it when an allocation fails, and in lnbnn_trim).  An index that is
 // rebuilt again and again would otherwise outrun the driver, which wipes freed
 // memory at about 40 GB/s: 2.27M references rebuilt every 1.4 ms came to 8 ms
 // and more a build once the wiped memory was used up.

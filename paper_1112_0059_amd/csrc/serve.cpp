@@ -6,7 +6,8 @@
 // fits a slot's capacity, and launches each batch on one of up to four
 // slots; a slot owns a stream, a device workspace sized for its capacity
 // and pinned staging.  Several slots in flight let the next batch's
-// uploads and launches overlap the current batch on the device.  A
+// uploads and launches overlap the current batch on the device; its sweep
+// of the index follows the current batch's last kernel (see launch_slot).  A
 // completion thread waits for slots in launch order and publishes results;
 // lnbnn_poll hands them out.
 //
