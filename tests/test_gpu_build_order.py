@@ -1,5 +1,6 @@
 """An index built from device memory waits for the work of the process's blocking
-streams, in which its inputs may still be written."""
+streams, in which its inputs may still be written, and names the first label out of
+range, whether few labels are read back or many are checked on the device."""
 import ctypes
 
 import numpy as np
@@ -12,9 +13,9 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("mode", [L.LNBNN_EXACT_I8, L.LNBNN_EXACT_F16, L.LNBNN_NBNN_I8])
 @pytest.mark.parametrize("own_stream", [True, False])
-def test_inputs_written_on_a_blocking_stream(mode, own_stream):
+@pytest.mark.parametrize("n", [50_000, 8_000])
+def test_inputs_written_on_a_blocking_stream(mode, own_stream, n):
     import torch
-    n = 50_000
     g = torch.Generator(device="cuda").manual_seed(6)
     R = torch.randint(0, 256, (n, 128), generator=g, device="cuda", dtype=torch.uint8)
     labels = (torch.arange(n, device="cuda") % 7).to(torch.int32)
@@ -41,3 +42,21 @@ def test_inputs_written_on_a_blocking_stream(mode, own_stream):
         assert torch.equal(x, y)
     ix.free()
     ref.free()
+
+
+@pytest.mark.parametrize("mode", [L.LNBNN_EXACT_I8, L.LNBNN_NBNN_I8])
+@pytest.mark.parametrize("n", [8192, 8193])
+@pytest.mark.parametrize("bad", [{}, {0: -1}, {8191: 7}, {1234: 7, 8000: -5}])
+def test_first_bad_label(mode, n, bad):
+    import torch
+    R = torch.randint(0, 256, (n, 128), dtype=torch.uint8, device="cuda")
+    labels = (torch.arange(n, device="cuda") % 7).to(torch.int32)
+    for j, v in bad.items():
+        labels[j] = v
+    if not bad:
+        L.lnbnn_build_index(R, labels, 7, L.LNBNN_MODE_BIT(mode)).free()
+        return
+    with pytest.raises(L.LnbnnError) as e:
+        L.lnbnn_build_index(R, labels, 7, L.LNBNN_MODE_BIT(mode))
+    j = min(bad)
+    assert e.value.code == L.LNBNN_EINVAL and f"label[{j}] = {bad[j]} " in str(e.value)
