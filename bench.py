@@ -197,7 +197,7 @@ def exact_leg(args, L, torch, np, synth):
                    "slices": timing["slices"]},
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_MFMA_I8_TOPS,
                      "unit": "TOP/s", "frac": achieved / PEAK_MFMA_I8_TOPS,
-                     "traffic": traffic_per_launch("exact_i8"), "kernel": "k_dist_topk<OpI8T<4, FMT_I8>, 11, ...>",
+                     "traffic": traffic_per_launch("exact_i8"), "kernel": "k_dist_topk<OpI8Q<FMT_I8>, 11, ...>",
                      "kernel_ms": k1_ms, "algorithmic_ops_per_launch": flop},
         "accuracy_statistic": float(np.mean(cls == true_cls)),
     }
